@@ -9,7 +9,9 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libobte.so")
-SOURCES = ["kernels.hip", "apply.hip", "host.cpp", "ukernels.hip", "umesh.cpp"]
+# one unit per precision and row width of the pass kernels, largest first
+SOURCES = [f"sweep{d}d_{p}_{c}.hip" for c in ("34", "12") for d in (3, 2) for p in ("f64", "f32")] + [
+    "sweep2d_f64_queue.hip", "sweep2d_f32_queue.hip", "kernels.hip", "apply.hip", "host.cpp", "ukernels.hip", "umesh.cpp"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [

@@ -1,0 +1,368 @@
+// Device helpers shared by the gfx950 kernels: wavefront sums and scans,
+// wave-uniform values, buffer resources, per-system constants.
+#pragma once
+#include "obte_internal.h"
+#include <type_traits>
+
+namespace {
+
+constexpr int WAVE = 64;
+
+template <typename T>
+__device__ __forceinline__ T shfl_up(T v, int d) { return __shfl_up(v, d, WAVE); }
+template <typename T>
+__device__ __forceinline__ T shfl_at(T v, int l) { return __shfl(v, l, WAVE); }
+template <typename T>
+__device__ __forceinline__ T shfl_xor(T v, int m) { return __shfl_xor(v, m, WAVE); }
+
+// Butterfly sum: every lane ends with the bitwise-same value.
+template <typename T>
+__device__ __forceinline__ T wave_sum(T v) {
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) v += shfl_xor(v, m);
+    return v;
+}
+
+// N butterfly sums at once, step by step, so the cross-lane reads of the N
+// values are in flight together; each value is summed exactly as wave_sum does.
+template <int N>
+__device__ __forceinline__ void wave_sum_n(double (&v)[N]) {
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) {
+        double t[N];
+#pragma unroll
+        for (int q = 0; q < N; ++q) t[q] = shfl_xor(v[q], m);
+#pragma unroll
+        for (int q = 0; q < N; ++q) v[q] += t[q];
+    }
+}
+
+// Deterministic block sum (blockDim.x multiple of 64, <= 1024).
+[[maybe_unused]] __device__ double block_sum(double v, double* red) {
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, nw = blockDim.x >> 6;
+    v = wave_sum(v);
+    __syncthreads();
+    if (lane == 0) red[wid] = v;
+    __syncthreads();
+    double t = 0.0;
+    if (wid == 0) {
+        t = lane < nw ? red[lane] : 0.0;
+        t = wave_sum(t);
+        if (lane == 0) red[16] = t;
+    }
+    __syncthreads();
+    return red[16];
+}
+
+// Two block sums in one pass (red: at least 34 doubles); each value is summed
+// exactly as block_sum sums it.
+[[maybe_unused]] __device__ void block_sum2(double& a, double& b, double* red) {
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, nw = blockDim.x >> 6;
+    double v[2] = {a, b};
+    wave_sum_n(v);
+    __syncthreads();
+    if (lane == 0) {
+        red[wid] = v[0];
+        red[16 + wid] = v[1];
+    }
+    __syncthreads();
+    if (wid == 0) {
+        double t[2] = {lane < nw ? red[lane] : 0.0, lane < nw ? red[16 + lane] : 0.0};
+        wave_sum_n(t);
+        if (lane == 0) {
+            red[32] = t[0];
+            red[33] = t[1];
+        }
+    }
+    __syncthreads();
+    a = red[32];
+    b = red[33];
+}
+
+// A cell's grid coordinates (one division chain per cell), and its
+// neighbour across face f (2a: '-' side of axis a, 2a + 1: '+' side) with the
+// periodic wrap taken by comparison, so the per-face lookups divide nothing.
+struct CellPos {
+    int ix, iy, iz;
+};
+__device__ __forceinline__ CellPos cell_pos(const GeomDev& g, int cell) {
+    const int q = cell / g.nx, r = q / g.ny;
+    return {cell - q * g.nx, q - r * g.ny, r};
+}
+__device__ __forceinline__ int nbr_cell(const GeomDev& g, int cell, const CellPos& cp, int f) {
+    const int a = f >> 1;
+    const bool up = f & 1;
+    const int n = a == 0 ? g.nx : (a == 1 ? g.ny : g.nz);
+    const int i = a == 0 ? cp.ix : (a == 1 ? cp.iy : cp.iz);
+    const int st = a == 0 ? 1 : (a == 1 ? g.nx : g.nx * g.ny);
+    if (up) return i == n - 1 ? cell - (n - 1) * st : cell + st;
+    return i == 0 ? cell + (n - 1) * st : cell - st;
+}
+
+using rsrc_t = __amdgpu_buffer_rsrc_t;
+
+// Wave-uniform copies of values the compiler cannot prove uniform (loaded
+// after the kernel's first store, or derived from the wave index): scalar
+// registers, so the buffer resources and row offsets built from them are too.
+__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ uint32_t uni(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
+__device__ __forceinline__ double uni(double v) {
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_readfirstlane((int)b), hi = __builtin_amdgcn_readfirstlane((int)(b >> 32));
+    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+__device__ __forceinline__ float uni(float v) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v))); }
+template <typename P>
+__device__ __forceinline__ P* uni(P* p) {
+    const unsigned long long a = (unsigned long long)p;
+    const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)a);
+    const unsigned hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(a >> 32));
+    return (P*)(((unsigned long long)hi << 32) | lo);
+}
+
+__device__ __forceinline__ rsrc_t make_rsrc(const void* p, uint32_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(uni(p)), 0, (int)uni(bytes), 0x00020000);
+}
+
+// ---------------------------------------------------------------------------
+// per-system constants
+// ---------------------------------------------------------------------------
+template <typename T>
+struct SysC {
+    int sys, m, l;
+    int pos[3];          // 1 if the sweep runs towards + along the axis
+    int fin[3], fout[3]; // inflow / outflow face index per axis
+    double cd[3];        // Lambda |s_a| / h_a
+    T c[3];
+    double kw;           // adjoint source k_ml
+    double Dml;
+    double Sg;           // S_ml along the gradient axis
+    double S[3];
+};
+
+template <typename T>
+__device__ __forceinline__ SysC<T> make_sys(const GeomDev& g, int m, int l, int adjoint) {
+    SysC<T> s;
+    s.m = m;
+    s.l = l;
+    s.sys = m * g.n_dir + l;
+    const double lam = g.mfp[m];
+    for (int a = 0; a < 3; ++a) {
+        double sa = (a < g.ndim) ? g.dirs[l * 3 + a] : 0.0;
+        if (adjoint) sa = -sa;   // A_l^T = A_{-l} on a uniform grid
+        s.pos[a] = sa > 0.0;
+        s.fin[a] = 2 * a + (sa > 0.0 ? 0 : 1);
+        s.fout[a] = 2 * a + (sa > 0.0 ? 1 : 0);
+        s.cd[a] = (a < g.ndim) ? lam * fabs(sa) / g.h[a] : 0.0;
+        s.c[a] = (T)s.cd[a];
+        s.S[a] = g.S[s.sys * 3 + a];
+    }
+    s.Dml = g.Dw[s.sys];
+    s.Sg = g.S[s.sys * 3 + g.grad_axis];
+    s.kw = g.L[g.grad_axis] / (g.dT * (double)g.ncells) * s.Sg;
+    // one system per wave: the indices and orientation flags are
+    // wave-uniform (scalar registers; they address the row loads)
+    s.sys = uni(s.sys);
+    s.m = uni(s.m);
+    s.l = uni(s.l);
+    for (int a = 0; a < 3; ++a) {
+        s.pos[a] = uni(s.pos[a]);
+        s.fin[a] = uni(s.fin[a]);
+        s.fout[a] = uni(s.fout[a]);
+    }
+    return s;
+}
+
+// Upper bound of the gain of a system's wrap map G (inflow of the first row
+// -> mask * c_y * outflow of the last row, sources zero).  One row of the
+// sweep solves (D - C_in) x = c_y y, where D = sigma + sum c and C_in holds
+// the in-row (x, and z in 3D) upwind couplings: an M-matrix whose rows and
+// columns both exceed their off-diagonal sums by at least sigma_min + c_y.
+// So every row transfer has max- and 1-norm (hence 2-norm) at most
+// q = c_y / (sigma_min + c_y), walls and pores only lower it, and
+// |G r| <= q^ny |r| for the BiCGSTAB's 2-norm.  1 when sigma_min <= 0.
+// The sweep-free step is taken only where it cuts the wrap residual at least
+// tenfold: with a weaker cut (up to the forcing term 0.3) the mixed outer
+// iteration needed more passes (22 -> 26 on the 128x128 cell), which cost
+// more than the sweeps saved.
+constexpr double RICH_MAX = 0.1;
+
+__device__ __forceinline__ double wrap_gain_bound(double smin, double cy, int ny) {
+    if (!(smin > 0.0)) return 1.0;
+    return pow(cy / (smin + cy), (double)ny);
+}
+
+template <typename T>
+__device__ __forceinline__ const T* sigma_ptr(const GeomDev& g);
+template <>
+__device__ __forceinline__ const double* sigma_ptr<double>(const GeomDev& g) { return g.sigma; }
+template <>
+__device__ __forceinline__ const float* sigma_ptr<float>(const GeomDev& g) { return g.sigma_f; }
+
+
+// ---------------------------------------------------------------------------
+// cross-lane primitives: DPP row shifts / row broadcasts / wave shift and
+// v_readlane.  `old` is what a lane receives when it has no source lane.
+// ---------------------------------------------------------------------------
+template <int CTRL, int RM>
+__device__ __forceinline__ float dpp(float v, float old) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(old), __float_as_int(v), CTRL, RM, 0xf, false));
+}
+template <int CTRL, int RM>
+__device__ __forceinline__ double dpp(double v, double old) {
+    const long long b = __double_as_longlong(v), o = __double_as_longlong(old);
+    const int lo = __builtin_amdgcn_update_dpp((int)o, (int)b, CTRL, RM, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp((int)(o >> 32), (int)(b >> 32), CTRL, RM, 0xf, false);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+__device__ __forceinline__ float readlane(float v, int l) {
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
+}
+__device__ __forceinline__ double readlane(double v, int l) {
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_readlane((int)b, l), hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+
+// One Hillis-Steele step of the affine-map scan: this lane's map x -> A + Q x
+// is composed after the map of the source lane (identity where none).  Only
+// A and P = 1 - Q are carried: P keeps full relative accuracy where it is
+// small (a nearly closed cyclic chain, the closure divides by it), and where
+// 1 - P is inexact (Q tiny) it only scales terms it makes negligible.
+// Full-mask row shifts read the source with bound_ctrl (a lane without
+// source reads 0, the identity's A and P).
+template <int CTRL, int RM>
+__device__ __forceinline__ void scan_step(float& A, float& P) {
+    const bool bc = RM == 0xf;
+    const float A2 = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(A), CTRL, RM, 0xf, bc));
+    const float P2 = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(P), CTRL, RM, 0xf, bc));
+    const float t = 1.0f - P;
+    A = A + t * A2;
+    P = P + t * P2;
+}
+template <int CTRL, int RM>
+__device__ __forceinline__ void scan_step(double& A, double& P) {
+    const double A2 = dpp<CTRL, RM>(A, 0.0), P2 = dpp<CTRL, RM>(P, 0.0);
+    const double t = 1.0 - P;
+    A = A + t * A2;
+    P = P + t * P2;
+}
+
+// Inclusive wavefront scan of the maps (A, P).
+template <typename T>
+__device__ __forceinline__ void wave_scan(T& A, T& P) {
+    scan_step<0x111, 0xf>(A, P);   // row_shr:1
+    scan_step<0x112, 0xf>(A, P);   // row_shr:2
+    scan_step<0x114, 0xf>(A, P);   // row_shr:4
+    scan_step<0x118, 0xf>(A, P);   // row_shr:8
+    scan_step<0x142, 0xa>(A, P);   // row_bcast:15 into rows 1, 3
+    scan_step<0x143, 0xc>(A, P);   // row_bcast:31 into rows 2, 3
+}
+
+// FP32: a step is t = 1 - P and two multiply-adds whose multiplicand is the
+// accumulator itself read from the source lane (a DPP operand may name the
+// destination: the source lanes are read before any is written; and the
+// rows a row_bcast step writes never hold its source lane).  A lane with no
+// source reads 0 (bound_ctrl), a row that a row_bcast step does not write
+// keeps its map: both compose the identity.  The compiler does not fold its
+// own DPP moves into v_fmac, so this saves two moves per step and the zero
+// fills of the row_bcast steps.  Hazard: a DPP read needs two wait states
+// after the VALU write of its register; within a step the v_sub and the
+// other accumulator's update provide them, s_nop 1 covers the first step.
+__device__ __forceinline__ void wave_scan(float& A, float& P) {
+    float t;
+    asm volatile(
+        "s_nop 1\n\t"
+        "v_sub_f32 %2, 1.0, %1\n\t"
+        "v_fmac_f32_dpp %0, %0, %2 row_shr:1 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+        "v_fmac_f32_dpp %1, %1, %2 row_shr:1 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+        "v_sub_f32 %2, 1.0, %1\n\t"
+        "v_fmac_f32_dpp %0, %0, %2 row_shr:2 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+        "v_fmac_f32_dpp %1, %1, %2 row_shr:2 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+        "v_sub_f32 %2, 1.0, %1\n\t"
+        "v_fmac_f32_dpp %0, %0, %2 row_shr:4 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+        "v_fmac_f32_dpp %1, %1, %2 row_shr:4 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+        "v_sub_f32 %2, 1.0, %1\n\t"
+        "v_fmac_f32_dpp %0, %0, %2 row_shr:8 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+        "v_fmac_f32_dpp %1, %1, %2 row_shr:8 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+        "v_sub_f32 %2, 1.0, %1\n\t"
+        "v_fmac_f32_dpp %0, %0, %2 row_bcast:15 row_mask:0xa bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %1, %1, %2 row_bcast:15 row_mask:0xa bank_mask:0xf\n\t"
+        "v_sub_f32 %2, 1.0, %1\n\t"
+        "v_fmac_f32_dpp %0, %0, %2 row_bcast:31 row_mask:0xc bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %1, %1, %2 row_bcast:31 row_mask:0xc bank_mask:0xf"
+        : "+v"(A), "+v"(P), "=&v"(t));
+}
+
+// Loads through these views compile to global (not flat) loads, which keep
+// only the vector-memory counter pending while the row computes.
+template <typename T>
+using gptr_t = const __attribute__((address_space(1))) T*;
+template <typename T>
+__device__ __forceinline__ gptr_t<T> gview(const T* p) { return (gptr_t<T>)p; }
+// Writable global views: stores through them are global (not flat) stores,
+// which a barrier's wait on the LDS counter does not include.
+template <typename T>
+using gmut_t = __attribute__((address_space(1))) T*;
+template <typename T>
+__device__ __forceinline__ gmut_t<T> gmut(T* p) { return (gmut_t<T>)p; }
+
+// Raw buffer access (gfx9 descriptors): a resource for the whole array, a
+// per-lane byte offset fixed for the sweep and a scalar offset per row, so a
+// row's loads need no per-lane address arithmetic.  A raw buffer access is
+// range-checked on its per-lane offset: a store whose offset is at or past
+// the array's size is dropped (used for pores and beyond-row lanes).
+constexpr uint32_t BUF_OOB = 0x80000000u;
+typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t bld16(rsrc_t r, uint32_t vo, uint32_t so) {
+    return (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(r, (int)vo, (int)so, 0);
+}
+__device__ __forceinline__ uint32_t bld32(rsrc_t r, uint32_t vo, uint32_t so) {
+    return __builtin_amdgcn_raw_buffer_load_b32(r, (int)vo, (int)so, 0);
+}
+__device__ __forceinline__ double bld64(rsrc_t r, uint32_t vo, uint32_t so) {
+    const u32x2_t v = __builtin_amdgcn_raw_buffer_load_b64(r, (int)vo, (int)so, 0);
+    return __longlong_as_double(((long long)v.y << 32) | (unsigned long long)v.x);
+}
+template <typename T>
+__device__ __forceinline__ T bldT(rsrc_t r, uint32_t vo, uint32_t so);
+template <>
+__device__ __forceinline__ float bldT<float>(rsrc_t r, uint32_t vo, uint32_t so) {
+    return __uint_as_float(bld32(r, vo, so));
+}
+template <>
+__device__ __forceinline__ double bldT<double>(rsrc_t r, uint32_t vo, uint32_t so) {
+    return bld64(r, vo, so);
+}
+__device__ __forceinline__ void bst(float v, rsrc_t r, uint32_t vo) {
+    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), r, (int)vo, 0, 0);
+}
+__device__ __forceinline__ void bst(double v, rsrc_t r, uint32_t vo) {
+    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+    u32x2_t w;
+    w.x = (unsigned int)b;
+    w.y = (unsigned int)(b >> 32);
+    __builtin_amdgcn_raw_buffer_store_b64(w, r, (int)vo, 0, 0);
+}
+
+// Per-wave state of a sweep that keeps its result: the kappa sums in
+// registers, and the solution stored on the solid cells (the sums over
+// systems per cell and per wall are taken afterwards by the reduction kernel).
+template <typename T>
+struct Red {
+    int store_T;
+    int on;                    // 0: inactive wave (nothing is stored)
+    double kacc, kface;
+    rsrc_t X;                  // this system's solution by solid index
+    rsrc_t Tstore;             // this system's stored state (store_T only)
+};
+
+// 1/d: hardware reciprocal (float), refined by two Newton steps (double).
+__device__ __forceinline__ float recip(float d) { return __builtin_amdgcn_rcpf(d); }
+__device__ __forceinline__ double recip(double d) {
+    double r = __builtin_amdgcn_rcp(d);
+    r = r * (2.0 - d * r);
+    return r * (2.0 - d * r);
+}
+
+}  // namespace

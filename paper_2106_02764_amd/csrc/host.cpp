@@ -53,7 +53,11 @@ void soft(hipError_t e, const char* what) {
 constexpr int HIST_CAP = 1 << 16;
 
 // checkpoint file tag (format: header of 9 ints, then the state arrays)
-constexpr int CKPT_MAGIC = 0x4f425447;
+constexpr int CKPT_MAGIC = 0x4f425448;
+// the tag before 2D wrap inflows were held in units of the solution and for
+// rows along y too: such a file's inflows are converted (rows along x) or
+// start at 0 (rows along y)
+constexpr int CKPT_MAGIC_ROWS_X = 0x4f425447;
 
 }  // namespace
 
@@ -74,6 +78,12 @@ struct obte_mesh {
     int grad_axis = 0;
     std::vector<uint16_t> fc;
     std::vector<int> wall_idx, wall_cell, wall_face;
+    // 2D rows: cells per lane, whether directions may take rows along y, and
+    // the open plane cells (solid indices) at the low / high end of the
+    // gradient axis
+    int q_cpl = 1;
+    bool q_tr = false;
+    std::vector<int> plane[2];
     // material
     bool has_material = false;
     int n_mfp = 0, n_dir = 0, n_sys = 0;
@@ -86,6 +96,8 @@ struct obte_mesh {
     int *d_wall_cell = nullptr, *d_wall_face = nullptr, *d_wall_idx = nullptr;
     double *d_mfp = nullptr, *d_dirs = nullptr, *d_D = nullptr, *d_S = nullptr, *d_wout = nullptr,
            *d_kax = nullptr;
+    unsigned long long* d_mask[2] = {nullptr, nullptr};
+    int* d_plane[2] = {nullptr, nullptr};
     GeomDev* d_geom = nullptr;      // single-geometry view (apply, outputs)
     // results of the last solve
     bool solved = false, adj_ready = false;
@@ -178,7 +190,7 @@ namespace {
 struct Layout {
     size_t sigma, sigma_f, sT, Tw, T_L, U, X, ksys, kfsys, iters, sweeps, hist, hist_face, ctrl, fx, fscal,
         Tstore, lam_psi, lam_phi, grad, bnd, wres, wres_hist, kry, ax, actl, ag,
-        axp, afp, adX, adF, agram, apart, kraw, qrec, qoff, qsg, qalt, total;
+        axp, afp, adX, adF, agram, apart, kraw, qrec, total;
 };
 
 // Linear interpolation weights of x on the sorted values v (clamped to the
@@ -336,7 +348,19 @@ int auto_waves(const obte_mesh* m) {
 
 int n_groups(const obte_mesh* m, int waves) { return (m->n_mfp + waves - 1) / waves; }
 
-Layout make_layout(const obte_mesh* m, const obte_solve_opts* o, int waves) {
+// Records of a 2D row along x (o = 0) or y, and of all rows in one table.
+size_t row_records(const obte_mesh* m, int o) {
+    const int n = o ? m->ny : m->nx;
+    return (size_t)((n + m->q_cpl - 1) / m->q_cpl) * m->q_cpl;
+}
+size_t table_records(const obte_mesh* m, int o) { return row_records(m, o) * (o ? m->nx : m->ny); }
+
+// Stride of one system's wrap inflow (tr: rows along y are in use).
+size_t wrap_stride(const obte_mesh* m, bool tr) {
+    return m->nz > 1 ? (size_t)m->nx * m->nz : (size_t)(tr ? std::max(m->nx, m->ny) : m->nx);
+}
+
+Layout make_layout(const obte_mesh* m, const obte_solve_opts* o, bool tr) {
     Layout L{};
     size_t off = 0;
     auto take = [&](size_t bytes) {
@@ -346,7 +370,7 @@ Layout make_layout(const obte_mesh* m, const obte_solve_opts* o, int waves) {
     };
     const size_t nc = (size_t)m->ncells, nw = (size_t)std::max(m->nwalls, 1);
     const size_t tsz = (o->precision == OBTE_FP32) ? 4 : 8;
-    const size_t nwrap = (size_t)m->nx * m->nz;
+    const size_t nwrap = wrap_stride(m, tr);
     L.sigma = take(nc * 8);
     L.sigma_f = take(nc * 4);
     L.sT = take(2 * nc * 8);
@@ -378,11 +402,13 @@ Layout make_layout(const obte_mesh* m, const obte_solve_opts* o, int waves) {
     const size_t nsol = x_stride(m->nsolid);
     L.Tstore = o->keep_state ? take((size_t)m->n_sys * nsol * 8) : 0;
     L.X = take((size_t)m->n_sys * nsol * tsz);
-    // 2D: the pass inputs in the four sweep orientations' order
-    L.qrec = m->nz == 1 ? take(4 * nc * 4 * tsz) : take((1 + (size_t)m->nf) * nc * tsz);
-    L.qoff = m->nz == 1 ? take(4 * nc * 4) : 0;
-    L.qsg = m->nz == 1 ? take(4 * nc * tsz) : 0;
-    L.qalt = m->nz == 1 ? take(4 * nc * 2 * tsz) : 0;
+    // 2D: the pass inputs in the rows' order: per orientation and row
+    // direction six tables in the compute type, and the store offsets.  The
+    // region holds both orientations whether they are in use or not.
+    const size_t r0 = 2 * (nc + (size_t)m->ny * (m->q_cpl - 1)), r1 = 2 * (nc + (size_t)m->nx * (m->q_cpl - 1));
+    const size_t lead = ROW_SLACK * std::max(row_records(m, 0), row_records(m, 1));
+    L.qrec = m->nz == 1 ? take((r0 + (m->q_tr ? r1 : 0) + lead) * 6 * tsz + (r0 + nc + 2 * lead + 2 * OFF_SLACK) * 4)
+                        : take((1 + (size_t)m->nf) * nc * tsz);
     // last: the mixing history (an adjoint may use another depth than the
     // forward solve whose stored state it reads)
     const size_t M = (size_t)std::max(o->accel, 0);
@@ -397,12 +423,12 @@ Layout make_layout(const obte_mesh* m, const obte_solve_opts* o, int waves) {
     return L;
 }
 
-GeomDev make_view(const obte_mesh* m, char* ws, const Layout& L, int waves, int accel) {
+GeomDev make_view(const obte_mesh* m, char* ws, const Layout& L, int precision, int accel, bool tr) {
     GeomDev g{};
     g.n_aa = m->ncells + m->nwalls;
     g.aa_m = accel;
     g.nx = m->nx; g.ny = m->ny; g.nz = m->nz; g.ndim = m->ndim; g.nf = m->nf;
-    g.ncells = m->ncells; g.nwalls = m->nwalls; g.nwrap = m->nx * m->nz; g.nsolid = m->nsolid;
+    g.ncells = m->ncells; g.nwalls = m->nwalls; g.nwrap = (int)wrap_stride(m, tr); g.nsolid = m->nsolid;
     g.xs = (int)x_stride(m->nsolid);
     for (int a = 0; a < 3; ++a) { g.periodic[a] = m->periodic[a]; g.h[a] = m->h[a]; g.L[a] = m->L[a]; }
     g.grad_axis = m->grad_axis;
@@ -413,29 +439,14 @@ GeomDev make_view(const obte_mesh* m, char* ws, const Layout& L, int waves, int 
     g.mfp = m->d_mfp; g.dirs = m->d_dirs; g.Dw = m->d_D; g.S = m->d_S; g.wout = m->d_wout;
     g.gauge = m->n_modes > 0 ? 1 : 0;
     g.kappa_axis = m->d_kax;
-    // kappa_face plane cells per sweep quadrant (2D): solid cells that are
-    // last along the gradient axis in that quadrant's sweep order and whose
-    // outflow face there is open
-    if (m->nz == 1 && !m->fc.empty())
-        for (int q = 0; q < 4; ++q) {
-            const int negx = q & 1, negy = q >> 1, ga = m->grad_axis;
-            const int fo = ga == 0 ? 1 - negx : 3 - negy;
-            int cnt = 0;
-            if (ga == 0) {
-                const int ix = negx ? 0 : m->nx - 1;
-                for (int iy = 0; iy < m->ny; ++iy) {
-                    const uint16_t w = m->fc[(size_t)iy * m->nx + ix];
-                    cnt += fc_solid(w) && fc_class(w, fo) != FC_WALL;
-                }
-            } else {
-                const int iy = negy ? 0 : m->ny - 1;
-                for (int ix = 0; ix < m->nx; ++ix) {
-                    const uint16_t w = m->fc[(size_t)iy * m->nx + ix];
-                    cnt += fc_solid(w) && fc_class(w, fo) != FC_WALL;
-                }
-            }
-            g.qnk[q] = cnt;
-        }
+    g.q_cpl = m->q_cpl;
+    g.q_tr = tr ? 1 : 0;
+    for (int k = 0; k < 2; ++k) {
+        g.q_rs[k] = (int)row_records(m, k);
+        g.qmask[k] = m->d_mask[k] ? m->d_mask[k] + ROW_SLACK * row_mask_words(m->q_cpl) : nullptr;
+        g.plane[k] = m->d_plane[k];
+        g.n_plane[k] = (int)m->plane[k].size();
+    }
     if (ws) {
         g.sigma = (double*)(ws + L.sigma);
         g.sigma_f = (float*)(ws + L.sigma_f);
@@ -466,9 +477,15 @@ GeomDev make_view(const obte_mesh* m, char* ws, const Layout& L, int waves, int 
         g.kraw = (double*)(ws + L.kraw);
         g.qrec = ws + L.qrec;
         if (m->nz == 1) {
-            g.qoff = (uint32_t*)(ws + L.qoff);
-            g.qsg = ws + L.qsg;
-            g.qalt = ws + L.qalt;
+            const size_t tsz = precision == OBTE_FP32 ? 4 : 8, t0 = table_records(m, 0);
+            const size_t lead = ROW_SLACK * std::max(row_records(m, 0), row_records(m, 1));
+            char* q = ws + L.qrec + lead * tsz;
+            g.qtab[0] = q;
+            q += 12 * t0 * tsz;
+            g.qtab[1] = tr ? q : nullptr;
+            if (tr) q += 12 * table_records(m, 1) * tsz;
+            g.qoff = (uint32_t*)(q + lead * tsz);
+            g.qoffc = g.qoff + 2 * t0 + lead + OFF_SLACK;
         }
         if (accel > 0) {
             g.ag = (double*)(ws + L.ag);
@@ -498,11 +515,13 @@ void free_dev(obte_mesh* m) {
     m->g_adj.reset();
     void* ptrs[] = {m->d_fc, m->d_sidx, m->d_scell, m->d_wall_cell, m->d_wall_face, m->d_wall_idx, m->d_mfp, m->d_dirs,
                     m->d_D, m->d_S, m->d_wout, m->d_kax, m->d_geom, m->d_mode_sys, m->d_mode_w,
-                    m->d_mode_Sg, m->d_kmode};
+                    m->d_mode_Sg, m->d_kmode, m->d_mask[0], m->d_mask[1], m->d_plane[0], m->d_plane[1]};
     for (void* p : ptrs)
         if (p) soft(hipFree(p), "hipFree(table)");
     m->d_fc = nullptr; m->d_sidx = m->d_scell = nullptr; m->d_wall_cell = m->d_wall_face = m->d_wall_idx = nullptr;
     m->d_mfp = m->d_dirs = m->d_D = m->d_S = m->d_wout = m->d_kax = nullptr;
+    m->d_mask[0] = m->d_mask[1] = nullptr;
+    m->d_plane[0] = m->d_plane[1] = nullptr;
     m->d_geom = nullptr;
     m->d_mode_sys = nullptr;
     m->d_mode_w = m->d_mode_Sg = m->d_kmode = nullptr;
@@ -594,12 +613,14 @@ struct Run {
     // so a narrow geometry of a batch does not run the widest row's kernel
     int cls_first[5] = {}, cls_count[5] = {};
     size_t cls_lds[5] = {};
-    int cls_waves[5] = {4, 4, 4, 4, 4};   // systems per workgroup of each launch class
+    int cls_waves[5] = {1, 1, 1, 1, 1};   // waves per workgroup of each launch class
+    int sys_waves[5] = {4, 4, 4, 4, 4};   // systems per workgroup by ceil(nx / 64)
     int cls_full[5] = {1, 1, 1, 1, 1};    // class whose every row is exactly 64 * class cells
     int nzmax = 1, precision = 0, accel = 0;
     // 2D with dispatch = 2: every item in one persistent launch of queue_waves
     // waves per group, the groups taking items from the device counter d_queue
     int queue = 0, queue_waves = 1;
+    size_t queue_lds = 0;
     int* d_queue = nullptr;
     int gauge = 0;                // some geometry has a mode table (re-centred passes)
     int max_cells = 0, max_walls = 0, max_solid = 0;
@@ -691,8 +712,34 @@ obte_status resolve_waves(const obte_mesh* const* meshes, int n, const obte_solv
     return OBTE_OK;
 }
 
+// Launch class of a mesh: the cells per lane of its rows.
+int launch_class(const obte_mesh* m) { return m->nz > 1 ? (m->nx + 63) / 64 : m->q_cpl; }
+
+// Rows along y for direction l (2D, where they are in use at all).
+bool dir_transposed(const obte_mesh* m, int l, bool tr) {
+    return tr && transposed(&m->dirs3[3 * (size_t)l], m->L, m->periodic);
+}
+
+// Systems per workgroup of a mesh's items (W: the resolved value of its
+// class): FP64 kernels of 3 or 4 cells per lane take at most 4, and rows along
+// y as many as have their LDS tiles in 64 KiB.
+int item_waves(const obte_mesh* m, int W, int precision, bool tr_item) {
+    const int c = launch_class(m);
+    if (m->nz == 1 && precision == OBTE_FP64 && c >= 3) W = std::min(W, 4);
+    if (tr_item) W = std::min(W, (int)(65536 / tr_tile_bytes(c)));
+    return std::max(1, W);
+}
+
+size_t count_items(const obte_mesh* m, int W, int precision, bool tr) {
+    size_t k = 0;
+    const int w[2] = {item_waves(m, W, precision, false), item_waves(m, W, precision, true)};
+    for (int l = 0; l < m->n_dir; ++l) k += n_groups(m, w[dir_transposed(m, l, tr)]);
+    return k;
+}
+
+// allow_tr: directions may take rows along y (where the mesh allows it).
 obte_status build_run(Run& R, obte_mesh* const* meshes, int n, const obte_solve_opts* o,
-                      char* ws, std::vector<size_t>* offsets) {
+                      char* ws, std::vector<size_t>* offsets, bool allow_tr = true) {
     R.meshes.assign(meshes, meshes + n);
     R.precision = o->precision;
     R.accel = o->accel;
@@ -700,29 +747,37 @@ obte_status build_run(Run& R, obte_mesh* const* meshes, int n, const obte_solve_
     int Wc[5];
     obte_status s = resolve_waves(meshes, n, o, Wc);
     if (s != OBTE_OK) return s;
-    for (int c = 0; c < 5; ++c) R.cls_waves[c] = Wc[c];
+    for (int c = 0; c < 5; ++c) R.sys_waves[c] = Wc[c];
     size_t off = 0;
     std::vector<Item> by_cls[5];
     for (int gi = 0; gi < n; ++gi) {
         obte_mesh* m = meshes[gi];
-        const int c = (m->nx + 63) / 64;
-        const int W = Wc[c];
-        if (m->nx != 64 * c) R.cls_full[c] = 0;
-        Layout L = make_layout(m, o, W);
+        const int c = launch_class(m);
+        const bool tr = allow_tr && m->q_tr;
+        const int W = Wc[(m->nx + 63) / 64];
+        const int w[2] = {item_waves(m, W, o->precision, false), item_waves(m, W, o->precision, true)};
+        if (m->nx != 64 * c || (tr && m->ny != 64 * c)) R.cls_full[c] = 0;
+        Layout L = make_layout(m, o, tr);
         if (offsets) offsets->push_back(off);
-        GeomDev v = make_view(m, ws + off, L, W, o->accel);
-        const int ng = n_groups(m, W);
+        GeomDev v = make_view(m, ws + off, L, o->precision, o->accel, tr);
         // longest MFPs first: their systems take the most wrap iterations, so
         // the shorter ones dispatched after them fill in behind (a shorter
         // makespan than direction-major order; the results do not depend on it)
-        for (int gp = ng - 1; gp >= 0; --gp)
+        for (int end = m->n_mfp; end > 0; --end)
             for (int l = 0; l < m->n_dir; ++l) {
+                const int t = dir_transposed(m, l, tr) ? 1 : 0;
+                const int m0 = (end - 1) / w[t] * w[t];
+                if (std::min(m0 + w[t], m->n_mfp) != end) continue;
                 Item it;
                 it.geom = gi;
                 it.l = l;
-                it.m0 = gp * W;
-                it.nm = std::min(W, m->n_mfp - gp * W);
+                it.m0 = m0;
+                it.nm = end - m0;
+                it.tr = t;
                 by_cls[c].push_back(it);
+                R.cls_waves[c] = std::max(R.cls_waves[c], w[0]);
+                // rows along y stage their columns in LDS
+                if (t) R.cls_lds[c] = std::max(R.cls_lds[c], w[1] * tr_tile_bytes(c));
             }
         R.views.push_back(v);
         R.nzmax = std::max(R.nzmax, m->nz);
@@ -742,7 +797,8 @@ obte_status build_run(Run& R, obte_mesh* const* meshes, int n, const obte_solve_
         std::vector<Item> all;
         for (int c = 1; c <= 4; ++c) {
             all.insert(all.end(), by_cls[c].begin(), by_cls[c].end());
-            if (!by_cls[c].empty()) R.queue_waves = std::max(R.queue_waves, Wc[c]);
+            if (!by_cls[c].empty()) R.queue_waves = std::max(R.queue_waves, R.cls_waves[c]);
+            R.queue_lds = std::max(R.queue_lds, R.cls_lds[c]);
             by_cls[c].clear();
         }
         std::stable_sort(all.begin(), all.end(), [](const Item& a, const Item& b) { return a.m0 > b.m0; });
@@ -760,7 +816,7 @@ obte_status build_run(Run& R, obte_mesh* const* meshes, int n, const obte_solve_
         R.cls_first[c] = (int)R.items.size();
         R.cls_count[c] = (int)by_cls[c].size();
         R.items.insert(R.items.end(), by_cls[c].begin(), by_cls[c].end());
-        R.cls_lds[c] = R.nzmax > 1 ? (size_t)Wc[c] * R.nzmax * 64 * c * tsz : 0;
+        if (R.nzmax > 1) R.cls_lds[c] = (size_t)R.cls_waves[c] * R.nzmax * 64 * c * tsz;
     }
     R.state_off = off;
     R.state_bytes = run_state_bytes(R.views.size(), R.items.size());
@@ -807,8 +863,8 @@ obte_status launch_sweeps(const Run& R, const PassParams& pp, hipStream_t st, hi
         HIPCHK(launch_pack3(R.precision, R.d_views, (int)R.views.size(), R.max_cells, pp, st));
     if (start) HIPCHK(hipEventRecord(start, st));
     if (R.queue) {
-        HIPCHK(launch_sweep_queue(R.precision, R.d_views, R.d_items, R.cls_count[0], R.queue_waves, pp, st,
-                                  R.d_queue));
+        HIPCHK(launch_sweep_queue(R.precision, R.d_views, R.d_items, R.cls_count[0], R.queue_waves, pp,
+                                  R.queue_lds, st, R.d_queue));
         return OBTE_OK;
     }
     for (int c = 1; c <= 4; ++c)
@@ -915,7 +971,7 @@ obte_status outer_loop(const Run& R, const PassParams& pp, int K, hipStream_t st
     if (K > 1) {
         const auto key = graph_key(R.d_views, R.d_items, (int)R.views.size(), R.cls_first, R.cls_count, R.cls_lds,
                                    R.cls_waves, R.precision, R.nzmax, R.max_cells, R.max_walls, R.gauge, R.accel,
-                                   R.queue, R.queue_waves, pp, K, tm && tm->on);
+                                   R.queue, R.queue_waves, R.queue_lds, R.cls_full, pp, K, tm && tm->on);
         obte_status s = slot_graph(slot, key, st, [&]() -> obte_status {
             obte_status sk = OBTE_OK;
             for (int k = 0; k < K && sk == OBTE_OK; ++k) sk = enqueue_pass(R, pp, st, tm, k);
@@ -1012,7 +1068,7 @@ PassParams base_params(const obte_solve_opts* o) {
 obte_status solve_impl(obte_mesh* const* meshes, int n, const obte_solve_opts* o,
                        const double* const* sigma, void* workspace, size_t ws_bytes, void* stream,
                        double* T_L_out, double* J_out, double* kappa_out, obte_stats* stats,
-                       bool keep_T, bool noalloc = false) {
+                       bool keep_T, bool noalloc = false, bool allow_tr = true) {
     obte_status s = check_opts(o);
     if (s != OBTE_OK) return s;
     if (!meshes || n < 1) return fail(OBTE_ERR_ARG, "no meshes");
@@ -1025,7 +1081,7 @@ obte_status solve_impl(obte_mesh* const* meshes, int n, const obte_solve_opts* o
     hipStream_t st = (hipStream_t)stream;
     Run R;
     std::vector<size_t> offs;
-    s = build_run(R, meshes, n, o, (char*)workspace, &offs);
+    s = build_run(R, meshes, n, o, (char*)workspace, &offs, allow_tr);
     if (s != OBTE_OK) return s;
     {
         const size_t need = R.state_off + R.state_bytes;
@@ -1039,7 +1095,7 @@ obte_status solve_impl(obte_mesh* const* meshes, int n, const obte_solve_opts* o
     }
     for (int i = 0; i < n; ++i) {
         obte_mesh* m = meshes[i];
-        Layout L = make_layout(m, o, R.cls_waves[1]);
+        Layout L = make_layout(m, o, allow_tr && m->q_tr);
         char* ws = (char*)workspace + offs[i];
         if (R.h_views)
             HIPCHK(hipMemcpyAsync(m->d_geom, R.h_views + i, sizeof(GeomDev), hipMemcpyHostToDevice, st));
@@ -1047,9 +1103,10 @@ obte_status solve_impl(obte_mesh* const* meshes, int n, const obte_solve_opts* o
             HIPCHK(hipMemcpy(m->d_geom, &R.views[i], sizeof(GeomDev), hipMemcpyHostToDevice));
         m->host_view = R.views[i];
         HIPCHK(launch_prep_sigma(m->d_geom, m->ncells, sigma ? sigma[i] : nullptr, st));
+        if (m->nz == 1 && !o->only_fourier) HIPCHK(launch_pack_static(R.precision, m->d_geom, m->ncells, st));
         if (o->init == 0) {
             const size_t tsz = o->precision == OBTE_FP32 ? 4 : 8;
-            HIPCHK(hipMemsetAsync(ws + L.U, 0, 2 * (size_t)m->n_sys * m->nx * m->nz * tsz, st));
+            HIPCHK(hipMemsetAsync(ws + L.U, 0, 2 * (size_t)m->n_sys * R.views[i].nwrap * tsz, st));
         }
         HIPCHK(hipMemsetAsync(ws + L.iters, 0, 2 * (size_t)m->n_sys * 8, st));
         HIPCHK(hipMemsetAsync(ws + L.wres, 0, (size_t)m->n_sys * 8, st));
@@ -1094,6 +1151,7 @@ obte_status solve_impl(obte_mesh* const* meshes, int n, const obte_solve_opts* o
             rp.store_T = keep_T ? 1 : 0;
             s = launch_sweeps(R, rp, st);
             if (s != OBTE_OK) return s;
+            if (keep_T && R.nzmax == 1) HIPCHK(launch_keep(R.precision, meshes[0]->d_geom, st));
         }
     }
     if (n == 1 && (T_L_out || J_out)) HIPCHK(launch_output(meshes[0]->d_geom, R.precision, meshes[0]->ncells, T_L_out, o->only_fourier ? nullptr : J_out, nullptr, st));
@@ -1166,8 +1224,8 @@ obte_status solve_impl(obte_mesh* const* meshes, int n, const obte_solve_opts* o
         m->last_ws = workspace;
         m->last_sigma = sigma ? sigma[i] : nullptr;
         m->last_precision = o->precision;
-        m->last_waves = R.cls_waves[(m->nx + 63) / 64];
-        for (int c = 0; c < 4; ++c) m->last_waves_cls[c] = R.cls_waves[c + 1];
+        m->last_waves = R.sys_waves[(m->nx + 63) / 64];
+        for (int c = 0; c < 4; ++c) m->last_waves_cls[c] = R.sys_waves[c + 1];
         m->last_dispatch = o->dispatch;
         m->last_max_outer = o->max_outer;
         m->last_keep = o->keep_state;
@@ -1319,6 +1377,25 @@ obte_status obte_mesh_create(const obte_mesh_desc* d, obte_mesh** out) {
         m->fc[c] = w;
     }
     m->nwalls = (int)m->wall_cell.size();
+    // plane cells of the gradient axis: solid, at its low / high end, with the
+    // face across the periodic plane open
+    {
+        const int ga = m->grad_axis, n = ga == 0 ? m->nx : m->ny;
+        for (int side = 0; side < 2; ++side)
+            for (long long c = 0; c < nc; ++c) {
+                const int i = ga == 0 ? (int)(c % m->nx) : (int)((c / m->nx) % m->ny);
+                if (i == (side ? n - 1 : 0) && m->sidx[c] >= 0 && fc_class(m->fc[c], 2 * ga + side) != FC_WALL)
+                    m->plane[side].push_back(m->sidx[c]);
+            }
+    }
+    // 2D rows along y: where y is periodic (else there is no coupling across
+    // rows along x to begin with), fit on a wave, and do not make the rows
+    // along x more than twice as wide on its lanes
+    if (nz == 1) {
+        const int cx = (m->nx + 63) / 64, cy = (m->ny + 63) / 64;
+        m->q_tr = m->periodic[1] && cy <= 4 && cy <= 2 * cx;
+        m->q_cpl = m->q_tr ? std::max(cx, cy) : cx;
+    }
     if (m->nsolid == 0) { delete m; return fail(OBTE_ERR_ARG, "the mesh has no solid cell"); }
     *out = m;
     return OBTE_OK;
@@ -1498,6 +1575,17 @@ obte_status obte_material_set(obte_mesh* m, const obte_material_desc* d) {
     if ((s = upload(&m->d_S, m->S)) != OBTE_OK) return s;
     if ((s = upload(&m->d_wout, m->wout)) != OBTE_OK) return s;
     if ((s = upload(&m->d_kax, m->kappa_axis)) != OBTE_OK) return s;
+    for (int k = 0; k < 2; ++k)
+        if ((s = upload(&m->d_plane[k], m->plane[k])) != OBTE_OK) return s;
+    if (m->nz == 1) {
+        for (int o = 0; o < (m->q_tr ? 2 : 1); ++o) {
+            const size_t rows = o ? m->nx : m->ny;
+            const size_t words = row_mask_words(m->q_cpl);
+            HIPCHK(hipMalloc((void**)&m->d_mask[o], (2 * rows + 2 * ROW_SLACK) * words * sizeof(unsigned long long)));
+            HIPCHK(launch_row_masks(m->d_fc, m->nx, m->ny, m->q_cpl, o, m->d_mask[o] + ROW_SLACK * words, nullptr));
+        }
+        HIPCHK(hipStreamSynchronize(nullptr));      // solves run on other streams
+    }
     if (m->n_modes > 0) {
         if ((s = upload(&m->d_mode_sys, m->mode_sys)) != OBTE_OK) return s;
         if ((s = upload(&m->d_mode_w, m->mode_w)) != OBTE_OK) return s;
@@ -1506,7 +1594,7 @@ obte_status obte_material_set(obte_mesh* m, const obte_material_desc* d) {
     }
     m->modes_solved = false;
     HIPCHK(hipMalloc((void**)&m->d_geom, sizeof(GeomDev)));
-    GeomDev v = make_view(m, nullptr, Layout{}, 0, 0);
+    GeomDev v = make_view(m, nullptr, Layout{}, 0, 0, m->q_tr);
     HIPCHK(hipMemcpy(m->d_geom, &v, sizeof v, hipMemcpyHostToDevice));
     m->host_view = v;
     m->has_material = true;
@@ -1519,8 +1607,8 @@ obte_status obte_workspace_size(const obte_mesh* m, const obte_solve_opts* o, si
     return obte_workspace_size_batch(&m, 1, o, bytes);
 }
 
-obte_status obte_workspace_size_batch(const obte_mesh* const* meshes, int n, const obte_solve_opts* o,
-                                      size_t* bytes) {
+static obte_status workspace_size(const obte_mesh* const* meshes, int n, const obte_solve_opts* o, size_t* bytes,
+                                  bool allow_tr) {
     if (!meshes || n < 1 || !bytes) return fail(OBTE_ERR_ARG, "NULL argument or no meshes");
     obte_status s = check_opts(o);
     if (s != OBTE_OK) return s;
@@ -1533,12 +1621,16 @@ obte_status obte_workspace_size_batch(const obte_mesh* const* meshes, int n, con
     if (s != OBTE_OK) return s;
     size_t total = 0, items = 0;
     for (int i = 0; i < n; ++i) {
-        const int W = Wc[(meshes[i]->nx + 63) / 64];
-        total += align256(make_layout(meshes[i], o, W).total);
-        items += (size_t)meshes[i]->n_dir * n_groups(meshes[i], W);
+        total += align256(make_layout(meshes[i], o, meshes[i]->q_tr && allow_tr).total);
+        items += count_items(meshes[i], Wc[(meshes[i]->nx + 63) / 64], o->precision, meshes[i]->q_tr && allow_tr);
     }
     *bytes = total + run_state_bytes(n, items);
     return OBTE_OK;
+}
+
+obte_status obte_workspace_size_batch(const obte_mesh* const* meshes, int n, const obte_solve_opts* o,
+                                      size_t* bytes) {
+    return workspace_size(meshes, n, o, bytes, true);
 }
 
 obte_status obte_solve(obte_mesh* m, const obte_solve_opts* o, const double* sigma_dev,
@@ -1559,7 +1651,10 @@ obte_status obte_solve(obte_mesh* m, const obte_solve_opts* o, const double* sig
 // ---------------------------------------------------------------------------
 namespace {
 constexpr size_t NOALLOC_BYTES = (size_t)32 << 20;
-static __device__ __align__(256) unsigned char scratch[NOALLOC_BYTES];
+// over the stated size: the slack rows of the pass inputs, so that they take
+// nothing from a workspace that just fits
+constexpr size_t NOALLOC_SLACK = (size_t)64 << 10;
+static __device__ __align__(256) unsigned char scratch[NOALLOC_BYTES + NOALLOC_SLACK];
 constexpr int NOALLOC_MAX_DEV = 64;
 std::mutex g_scratch_mu;
 void* g_scratch_ptr[NOALLOC_MAX_DEV] = {};
@@ -1597,16 +1692,23 @@ obte_status obte_solve_noalloc(obte_mesh* m, const obte_solve_opts* o, const dou
     HIPCHK(hipGetDevice(&dev));
     if (m->has_material && m->device != dev)
         return fail(OBTE_ERR_ARG, "the mesh tables are on device %d, the current device is %d", m->device, dev);
+    // rows along y need a longer wrap inflow where ny > nx: without them where
+    // it does not fit
     size_t need = 0;
-    obte_status s = obte_workspace_size(m, o, &need);
+    bool tr = true;
+    obte_status s = workspace_size(&m, 1, o, &need, true);
+    if (s == OBTE_OK && need > NOALLOC_BYTES + NOALLOC_SLACK) {
+        tr = false;
+        s = workspace_size(&m, 1, o, &need, false);
+    }
     if (s != OBTE_OK) return s;
-    if (need > NOALLOC_BYTES)
+    if (need > NOALLOC_BYTES + NOALLOC_SLACK)
         return fail(OBTE_ERR_NOMEM, "this solve needs %zu bytes of scratch; obte_solve_noalloc has %zu "
                                     "(use obte_solve with a caller workspace)", need, NOALLOC_BYTES);
     void* ws = nullptr;
     if ((s = scratch_on_current_device(&ws)) != OBTE_OK) return s;
     const double* sg[1] = {sigma_dev};
-    return solve_impl(&m, 1, o, sg, ws, NOALLOC_BYTES, stream, T_L_dev, J_dev, nullptr, stats, false, true);
+    return solve_impl(&m, 1, o, sg, ws, NOALLOC_BYTES + NOALLOC_SLACK, stream, T_L_dev, J_dev, nullptr, stats, false, true, tr);
 }
 
 obte_status obte_solve_batch(obte_mesh* const* meshes, int n, const obte_solve_opts* o,
@@ -1666,7 +1768,7 @@ obte_status obte_adjoint(obte_mesh* m, const obte_solve_opts* o, const double* s
     obte_mesh* mp = m;
     s = build_run(R, &mp, 1, &oo, (char*)workspace, nullptr);
     if (s != OBTE_OK) return s;
-    Layout L = make_layout(m, &oo, R.cls_waves[1]);
+    Layout L = make_layout(m, &oo, m->q_tr);
     if (ws_bytes < R.state_off + R.state_bytes)
         return fail(OBTE_ERR_NOMEM, "workspace too small for the adjoint (accel deeper than the forward solve's?)");
     if ((s = upload_run(R, (char*)workspace)) != OBTE_OK) return s;
@@ -1677,7 +1779,7 @@ obte_status obte_adjoint(obte_mesh* m, const obte_solve_opts* o, const double* s
     HIPCHK(hipMemsetAsync(ws + L.lam_psi, 0, 2 * (size_t)m->ncells * 8, st));
     HIPCHK(hipMemsetAsync(ws + L.lam_phi, 0, 2 * (size_t)std::max(m->nwalls, 1) * 8, st));
     const size_t tsz = o->precision == OBTE_FP32 ? 4 : 8;
-    const size_t half = (size_t)m->n_sys * m->nx * m->nz * tsz;
+    const size_t half = (size_t)m->n_sys * R.views[0].nwrap * tsz;
     HIPCHK(hipMemsetAsync(ws + L.U + half, 0, half, st));
     HIPCHK(hipMemsetAsync(ws + L.bnd + 2 * (size_t)m->nf * m->ncells * 8, 0,
                           2 * (size_t)m->nf * m->ncells * 8, st));
@@ -1686,6 +1788,7 @@ obte_status obte_adjoint(obte_mesh* m, const obte_solve_opts* o, const double* s
     HIPCHK(hipMemsetAsync(ws + L.ctrl, 0, CTRL_N * sizeof(int), st));
     HIPCHK(hipMemsetAsync(ws + L.ax, 0, ((size_t)m->ncells + m->nwalls) * 8, st));
     HIPCHK(hipMemsetAsync(ws + L.actl, 0, 8 * sizeof(int), st));
+    if (m->nz == 1) HIPCHK(launch_pack_static(R.precision, R.d_views, m->ncells, st));
     PassParams pp = base_params(o);
     pp.adjoint = 1;
     pp.sigma1 = sigma_dev ? 0 : 1;
@@ -1747,7 +1850,7 @@ obte_status obte_checkpoint_save(const obte_mesh* m, const void* workspace, cons
     if (!f) return fail(OBTE_ERR_ARG, "cannot open %s", path);
     // header: magic, sizes; body: ctrl, T_L, sT (2), Tw (2), U, hist
     const GeomDev& v = m->host_view;
-    const int hdr[9] = {CKPT_MAGIC, m->ncells, m->nwalls, m->n_sys, m->nx * m->nz, m->last_precision,
+    const int hdr[9] = {CKPT_MAGIC, m->ncells, m->nwalls, m->n_sys, v.nwrap, m->last_precision,
                         m->last_waves, m->last_max_outer, m->last_keep};
     fwrite(hdr, sizeof hdr, 1, f);
     auto dump = [&](const void* dptr, size_t bytes) -> bool {
@@ -1761,7 +1864,7 @@ obte_status obte_checkpoint_save(const obte_mesh* m, const void* workspace, cons
     const size_t tsz = m->last_precision == OBTE_FP32 ? 4 : 8;
     ok = ok && dump(v.T_L, (size_t)m->ncells * 8) && dump(v.sT, 2 * (size_t)m->ncells * 8) &&
          dump(v.Tw, 2 * (size_t)std::max(m->nwalls, 1) * 8) &&
-         dump(v.U, (size_t)m->n_sys * m->nx * m->nz * tsz) &&
+         dump(v.U, (size_t)m->n_sys * v.nwrap * tsz) &&
          dump(v.bnd, 2 * (size_t)m->nf * m->ncells * 8) &&
          dump(v.ax, ((size_t)m->ncells + m->nwalls) * 8);
     const int passes = ctrl[CTRL_PASS];
@@ -1778,8 +1881,11 @@ obte_status obte_checkpoint_load(obte_mesh* m, void* workspace, const char* path
     FILE* f = fopen(path, "rb");
     if (!f) return fail(OBTE_ERR_ARG, "cannot open %s", path);
     int hdr[9];
-    if (fread(hdr, sizeof hdr, 1, f) != 1 || hdr[0] != CKPT_MAGIC || hdr[1] != m->ncells ||
-        hdr[2] != m->nwalls || hdr[3] != m->n_sys || hdr[4] != m->nx * m->nz) {
+    const bool head = fread(hdr, sizeof hdr, 1, f) == 1;
+    const bool rows_x = head && hdr[0] == CKPT_MAGIC_ROWS_X;      // 2D inflows of rows along x only, or a 3D file
+    const int nwrap = rows_x ? m->nx * m->nz : (int)wrap_stride(m, m->q_tr);
+    if (!head || (hdr[0] != CKPT_MAGIC && !rows_x) || hdr[1] != m->ncells ||
+        hdr[2] != m->nwalls || hdr[3] != m->n_sys || hdr[4] != nwrap) {
         fclose(f);
         return fail(OBTE_ERR_ARG, "checkpoint does not match this mesh / precision");
     }
@@ -1788,16 +1894,31 @@ obte_status obte_checkpoint_load(obte_mesh* m, void* workspace, const char* path
     o.precision = hdr[5];
     o.max_outer = hdr[7];
     o.keep_state = hdr[8];
-    const GeomDev v = make_view(m, (char*)workspace, make_layout(m, &o, hdr[6]), hdr[6], 0);
+    const GeomDev v = make_view(m, (char*)workspace, make_layout(m, &o, m->q_tr), o.precision, 0, m->q_tr);
     auto load = [&](void* dptr, size_t bytes) -> bool {
         std::vector<char> buf(bytes);
         if (fread(buf.data(), 1, bytes, f) != bytes) return false;
         return hipMemcpy(dptr, buf.data(), bytes, hipMemcpyHostToDevice) == hipSuccess;
     };
     const size_t tsz = hdr[5] == OBTE_FP32 ? 4 : 8;
+    auto load_rows_x = [&]() -> bool {
+        std::vector<char> in((size_t)m->n_sys * nwrap * tsz), out((size_t)m->n_sys * v.nwrap * tsz, 0);
+        if (fread(in.data(), 1, in.size(), f) != in.size()) return false;
+        for (int sys = 0; sys < m->n_sys; ++sys) {
+            const int l = sys % m->n_dir;
+            const double c = m->mfp[sys / m->n_dir] * std::fabs(m->dirs3[3 * l + 1]) / m->h[1];
+            if (dir_transposed(m, l, m->q_tr) || !(c > 0.0)) continue;
+            for (int p = 0; p < nwrap; ++p) {
+                const size_t a = (size_t)sys * nwrap + p, b = (size_t)sys * v.nwrap + p;
+                if (tsz == 4) ((float*)out.data())[b] = (float)(((const float*)in.data())[a] / c);
+                else ((double*)out.data())[b] = ((const double*)in.data())[a] / c;
+            }
+        }
+        return hipMemcpy(v.U, out.data(), out.size(), hipMemcpyHostToDevice) == hipSuccess;
+    };
     bool ok = load(v.ctrl, CTRL_N * sizeof(int)) && load(v.T_L, (size_t)m->ncells * 8) &&
               load(v.sT, 2 * (size_t)m->ncells * 8) && load(v.Tw, 2 * (size_t)std::max(m->nwalls, 1) * 8) &&
-              load(v.U, (size_t)m->n_sys * m->nx * m->nz * tsz) &&
+              (rows_x && m->nz == 1 ? load_rows_x() : load(v.U, (size_t)m->n_sys * nwrap * tsz)) &&
               load(v.bnd, 2 * (size_t)m->nf * m->ncells * 8) &&
               load(v.ax, ((size_t)m->ncells + m->nwalls) * 8);
     int passes = 0;

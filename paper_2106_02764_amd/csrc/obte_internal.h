@@ -21,7 +21,8 @@ constexpr int KRY3_VECS = 11;
 // Per-geometry view used by every kernel: static tables (library-owned) plus
 // the per-solve workspace carve (caller-owned).
 struct GeomDev {
-    int nx, ny, nz, ndim, nf, ncells, nwalls, nwrap;
+    int nx, ny, nz, ndim, nf, ncells, nwalls;
+    int nwrap;                   // stride of one system's wrap inflow in U: nx nz in 3D, the longer row in 2D
     int nsolid;                  // solid cells: the length of one system's stored solution
     int xs;                      // stride of one system's row in X and Tstore: nsolid rounded up
                                  // to 64 values, so the reductions' 64-cell strips start on lines
@@ -90,24 +91,51 @@ struct GeomDev {
     // (ax[n_aa] holds the shift between the two gauge kernels)
     int gauge;
     int* actl;                   // 2 x 4 (by pass parity): stored columns, ring head, previous pass valid
-    // ---- 2D sweep inputs of the pass in each sweep orientation's order,
-    // written by the pack kernel before the pass's sweeps.  Quadrant
-    // q = [s_x < 0] + 2 [s_y < 0]; entry q * ncells + r * nx + p is the cell
-    // at row r (y-upwind order) and position p (x-upwind order).
-    void* qrec;                  // 4 * ncells records {sb, bx, by, meta} of 4 compute-type words
-                                 // (meta: byte 0 x inflow open, 1 y inflow open, 2 kappa_face
-                                 // plane cell, 3 solid).  3D: the pass's sources (ncells) and
-                                 // inflow tables (nf * ncells) in the compute type
-    uint32_t* qoff;              // 4 * ncells: byte offset of the cell's stored value, QOFF_NONE in pores
-    void* qsg;                   // 4 * ncells: sigma in the compute type
-    void* qalt;                  // adjoint passes: 4 * ncells pairs {bx, by} of the outflow faces
-                                 // (with a mode table S may leave against the sweep direction)
-    int qnk[4];                  // per quadrant: cells flagged as kappa_face plane cells
+    // ---- 2D sweep inputs in the rows' order, per orientation o (rows along
+    // x / along y) and row direction negr: tables of rows * q_rs[o] records,
+    // negr * 6 + {0 sources, 1 boundary value of the row's inflow face, 2 and 3
+    // of the '-' and '+' face across the rows, 4 (adjoint) of the row's
+    // outflow face, 5 sigma}, in the compute type
+    void* qtab[2];
+    int q_cpl;                   // cells per lane of this mesh's 2D rows
+    int q_tr;                    // 1: directions may take rows along y
+    int q_rs[2];                 // records per row: the row's cells rounded up to q_cpl
+    uint32_t* qoff;              // rows along x, per negr: byte offset of the cell's stored value, QOFF_NONE in pores
+    uint32_t* qoffc;             // the same by cell
+    const unsigned long long* qmask[2];   // lane masks of the rows (k_row_masks)
+    const int* plane[2];         // solid indices of the open plane cells at the low / high end of the gradient axis
+    int n_plane[2];
+    void* qrec;                  // 3D: the pass's sources (ncells) and inflow tables (nf * ncells) in the
+                                 // compute type
 };
 
 // Store offset of a pore cell: past any stored array, also when doubled for
 // the FP64 copy of an FP32 solution (raw buffer stores there are dropped).
 constexpr uint32_t QOFF_NONE = 0x7FFFFFF0u;
+
+// Rows along y (2D): the row's own periodic closure is solved exactly and
+// only the coupling across the rows is iterated, so rows run along the axis
+// that the direction crosses more often per cell length, where the coupling
+// left is the weaker one.
+inline bool transposed(const double* s, const double* L, const int* periodic) {
+    const double ax = (s[0] < 0 ? -s[0] : s[0]) / L[0], ay = (s[1] < 0 ? -s[1] : s[1]) / L[1];
+    return !periodic[0] || ay > ax;
+}
+
+// Threads per workgroup of a 2D pass kernel: FP64 rows of 3 or 4 cells per
+// lane hold more registers than two waves per SIMD leave (they spilled to
+// scratch), so those kernels take at most 4 waves per group (the host caps
+// the systems per workgroup to match).
+template <typename T, int CPL>
+constexpr int pass_threads() { return (sizeof(T) == 8 && CPL >= 3) ? 256 : 512; }
+// LDS of a wave whose rows run along y: two batches of 32 bytes worth of columns
+constexpr size_t tr_tile_bytes(int cpl) { return 64 * (64 * (size_t)cpl + 4); }
+// The sweeps prefetch rows unconditionally: the 2D row tables and masks have
+// this many rows of slack before and behind them, the store offsets by cell
+// as many entries.
+constexpr int ROW_SLACK = 4, OFF_SLACK = 16;
+// words of one row's lane masks
+__host__ __device__ constexpr int row_mask_words(int cpl) { return 8 + 4 * cpl; }
 
 constexpr int AA_MAX = 8;
 
@@ -116,6 +144,7 @@ struct Item {
     int l;       // direction
     int m0;      // first MFP of the group
     int nm;      // MFPs in the group (<= waves per group)
+    int tr;      // 2D: rows along y
 };
 
 struct PassParams {
@@ -150,12 +179,16 @@ hipError_t launch_sweep_pass(int precision, int cpl, int nz, const GeomDev* geom
 // 2D: every item of a batch in one persistent launch; the groups take items
 // from the device counter *queue, which launch_pack_rows sets to 0.
 hipError_t launch_sweep_queue(int precision, const GeomDev* geoms_dev, const Item* items_dev, int n_items,
-                              int waves, PassParams pp, hipStream_t st, int* queue);
-// 2D: the pass inputs in the quadrant layout (GeomDev::qrec, qoff, qsg) of
-// every geometry, read from the buffers the pass's sweeps consume; a non-null
+                              int waves, PassParams pp, size_t lds_bytes, hipStream_t st, int* queue);
+// 2D: the pass inputs in the rows' order (GeomDev::qtab) of every geometry, read from the buffers the pass's sweeps consume; a non-null
 // queue (the persistent launch's item counter) is set to 0.
 hipError_t launch_pack_rows(int precision, const GeomDev* geoms_dev, int n_geoms, int max_cells, PassParams pp,
                             hipStream_t st, int* queue);
+// 2D: sigma and the store offsets in the rows' order (once per solve), the
+// rows' lane masks (once per mesh), the FP64 copy of a replayed pass.
+hipError_t launch_pack_static(int precision, const GeomDev* geom_dev, int ncells, hipStream_t st);
+hipError_t launch_row_masks(const uint16_t* fc, int nx, int ny, int cpl, int o, unsigned long long* out, hipStream_t st);
+hipError_t launch_keep(int precision, const GeomDev* geom_dev, hipStream_t st);
 // 3D: the pass's sources and inflow tables in the compute type (GeomDev::qrec).
 hipError_t launch_pack3(int precision, const GeomDev* geoms_dev, int n_geoms, int max_cells, PassParams pp,
                         hipStream_t st);

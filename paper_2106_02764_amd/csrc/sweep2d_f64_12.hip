@@ -1,0 +1,5 @@
+// 2D pass kernels, double, 1 and 2 cells per lane.
+#include "sweep2d.h"
+
+template hipError_t launch_sweep2<double, 1>(const GeomDev*, const Item*, int, int, PassParams, size_t, hipStream_t, int);
+template hipError_t launch_sweep2<double, 2>(const GeomDev*, const Item*, int, int, PassParams, size_t, hipStream_t, int);
