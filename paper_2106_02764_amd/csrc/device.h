@@ -124,55 +124,6 @@ __device__ __forceinline__ rsrc_t make_rsrc(const void* p, uint32_t bytes) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(uni(p)), 0, (int)uni(bytes), 0x00020000);
 }
 
-// ---------------------------------------------------------------------------
-// per-system constants
-// ---------------------------------------------------------------------------
-template <typename T>
-struct SysC {
-    int sys, m, l;
-    int pos[3];          // 1 if the sweep runs towards + along the axis
-    int fin[3], fout[3]; // inflow / outflow face index per axis
-    double cd[3];        // Lambda |s_a| / h_a
-    T c[3];
-    double kw;           // adjoint source k_ml
-    double Dml;
-    double Sg;           // S_ml along the gradient axis
-    double S[3];
-};
-
-template <typename T>
-__device__ __forceinline__ SysC<T> make_sys(const GeomDev& g, int m, int l, int adjoint) {
-    SysC<T> s;
-    s.m = m;
-    s.l = l;
-    s.sys = m * g.n_dir + l;
-    const double lam = g.mfp[m];
-    for (int a = 0; a < 3; ++a) {
-        double sa = (a < g.ndim) ? g.dirs[l * 3 + a] : 0.0;
-        if (adjoint) sa = -sa;   // A_l^T = A_{-l} on a uniform grid
-        s.pos[a] = sa > 0.0;
-        s.fin[a] = 2 * a + (sa > 0.0 ? 0 : 1);
-        s.fout[a] = 2 * a + (sa > 0.0 ? 1 : 0);
-        s.cd[a] = (a < g.ndim) ? lam * fabs(sa) / g.h[a] : 0.0;
-        s.c[a] = (T)s.cd[a];
-        s.S[a] = g.S[s.sys * 3 + a];
-    }
-    s.Dml = g.Dw[s.sys];
-    s.Sg = g.S[s.sys * 3 + g.grad_axis];
-    s.kw = g.L[g.grad_axis] / (g.dT * (double)g.ncells) * s.Sg;
-    // one system per wave: the indices and orientation flags are
-    // wave-uniform (scalar registers; they address the row loads)
-    s.sys = uni(s.sys);
-    s.m = uni(s.m);
-    s.l = uni(s.l);
-    for (int a = 0; a < 3; ++a) {
-        s.pos[a] = uni(s.pos[a]);
-        s.fin[a] = uni(s.fin[a]);
-        s.fout[a] = uni(s.fout[a]);
-    }
-    return s;
-}
-
 // Upper bound of the gain of a system's wrap map G (inflow of the first row
 // -> mask * c_y * outflow of the last row, sources zero).  One row of the
 // sweep solves (D - C_in) x = c_y y, where D = sigma + sum c and C_in holds
@@ -222,76 +173,6 @@ __device__ __forceinline__ double readlane(double v, int l) {
     const long long b = __double_as_longlong(v);
     const int lo = __builtin_amdgcn_readlane((int)b, l), hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
     return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-}
-
-// One Hillis-Steele step of the affine-map scan: this lane's map x -> A + Q x
-// is composed after the map of the source lane (identity where none).  Only
-// A and P = 1 - Q are carried: P keeps full relative accuracy where it is
-// small (a nearly closed cyclic chain, the closure divides by it), and where
-// 1 - P is inexact (Q tiny) it only scales terms it makes negligible.
-// Full-mask row shifts read the source with bound_ctrl (a lane without
-// source reads 0, the identity's A and P).
-template <int CTRL, int RM>
-__device__ __forceinline__ void scan_step(float& A, float& P) {
-    const bool bc = RM == 0xf;
-    const float A2 = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(A), CTRL, RM, 0xf, bc));
-    const float P2 = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(P), CTRL, RM, 0xf, bc));
-    const float t = 1.0f - P;
-    A = A + t * A2;
-    P = P + t * P2;
-}
-template <int CTRL, int RM>
-__device__ __forceinline__ void scan_step(double& A, double& P) {
-    const double A2 = dpp<CTRL, RM>(A, 0.0), P2 = dpp<CTRL, RM>(P, 0.0);
-    const double t = 1.0 - P;
-    A = A + t * A2;
-    P = P + t * P2;
-}
-
-// Inclusive wavefront scan of the maps (A, P).
-template <typename T>
-__device__ __forceinline__ void wave_scan(T& A, T& P) {
-    scan_step<0x111, 0xf>(A, P);   // row_shr:1
-    scan_step<0x112, 0xf>(A, P);   // row_shr:2
-    scan_step<0x114, 0xf>(A, P);   // row_shr:4
-    scan_step<0x118, 0xf>(A, P);   // row_shr:8
-    scan_step<0x142, 0xa>(A, P);   // row_bcast:15 into rows 1, 3
-    scan_step<0x143, 0xc>(A, P);   // row_bcast:31 into rows 2, 3
-}
-
-// FP32: a step is t = 1 - P and two multiply-adds whose multiplicand is the
-// accumulator itself read from the source lane (a DPP operand may name the
-// destination: the source lanes are read before any is written; and the
-// rows a row_bcast step writes never hold its source lane).  A lane with no
-// source reads 0 (bound_ctrl), a row that a row_bcast step does not write
-// keeps its map: both compose the identity.  The compiler does not fold its
-// own DPP moves into v_fmac, so this saves two moves per step and the zero
-// fills of the row_bcast steps.  Hazard: a DPP read needs two wait states
-// after the VALU write of its register; within a step the v_sub and the
-// other accumulator's update provide them, s_nop 1 covers the first step.
-__device__ __forceinline__ void wave_scan(float& A, float& P) {
-    float t;
-    asm volatile(
-        "s_nop 1\n\t"
-        "v_sub_f32 %2, 1.0, %1\n\t"
-        "v_fmac_f32_dpp %0, %0, %2 row_shr:1 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-        "v_fmac_f32_dpp %1, %1, %2 row_shr:1 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-        "v_sub_f32 %2, 1.0, %1\n\t"
-        "v_fmac_f32_dpp %0, %0, %2 row_shr:2 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-        "v_fmac_f32_dpp %1, %1, %2 row_shr:2 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-        "v_sub_f32 %2, 1.0, %1\n\t"
-        "v_fmac_f32_dpp %0, %0, %2 row_shr:4 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-        "v_fmac_f32_dpp %1, %1, %2 row_shr:4 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-        "v_sub_f32 %2, 1.0, %1\n\t"
-        "v_fmac_f32_dpp %0, %0, %2 row_shr:8 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-        "v_fmac_f32_dpp %1, %1, %2 row_shr:8 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-        "v_sub_f32 %2, 1.0, %1\n\t"
-        "v_fmac_f32_dpp %0, %0, %2 row_bcast:15 row_mask:0xa bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %1, %1, %2 row_bcast:15 row_mask:0xa bank_mask:0xf\n\t"
-        "v_sub_f32 %2, 1.0, %1\n\t"
-        "v_fmac_f32_dpp %0, %0, %2 row_bcast:31 row_mask:0xc bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %1, %1, %2 row_bcast:31 row_mask:0xc bank_mask:0xf"
-        : "+v"(A), "+v"(P), "=&v"(t));
 }
 
 // Loads through these views compile to global (not flat) loads, which keep
@@ -344,18 +225,6 @@ __device__ __forceinline__ void bst(double v, rsrc_t r, uint32_t vo) {
     w.y = (unsigned int)(b >> 32);
     __builtin_amdgcn_raw_buffer_store_b64(w, r, (int)vo, 0, 0);
 }
-
-// Per-wave state of a sweep that keeps its result: the kappa sums in
-// registers, and the solution stored on the solid cells (the sums over
-// systems per cell and per wall are taken afterwards by the reduction kernel).
-template <typename T>
-struct Red {
-    int store_T;
-    int on;                    // 0: inactive wave (nothing is stored)
-    double kacc, kface;
-    rsrc_t X;                  // this system's solution by solid index
-    rsrc_t Tstore;             // this system's stored state (store_T only)
-};
 
 // 1/d: hardware reciprocal (float), refined by two Newton steps (double).
 __device__ __forceinline__ float recip(float d) { return __builtin_amdgcn_rcpf(d); }

@@ -54,7 +54,7 @@ constexpr int HIST_CAP = 1 << 16;
 
 // checkpoint file tag (format: header of 9 ints, then the state arrays)
 constexpr int CKPT_MAGIC = 0x4f425448;
-// the tag before 2D wrap inflows were held in units of the solution and for
+// the tag before wrap inflows were held in units of the solution, and for 2D
 // rows along y too: such a file's inflows are converted (rows along x) or
 // start at 0 (rows along y)
 constexpr int CKPT_MAGIC_ROWS_X = 0x4f425447;
@@ -355,6 +355,9 @@ size_t row_records(const obte_mesh* m, int o) {
 }
 size_t table_records(const obte_mesh* m, int o) { return row_records(m, o) * (o ? m->nx : m->ny); }
 
+// words of one row's lane masks
+size_t mask_words(const obte_mesh* m) { return m->nz > 1 ? row_mask_words3(m->q_cpl) : row_mask_words(m->q_cpl); }
+
 // Stride of one system's wrap inflow (tr: rows along y are in use).
 size_t wrap_stride(const obte_mesh* m, bool tr) {
     return m->nz > 1 ? (size_t)m->nx * m->nz : (size_t)(tr ? std::max(m->nx, m->ny) : m->nx);
@@ -443,7 +446,7 @@ GeomDev make_view(const obte_mesh* m, char* ws, const Layout& L, int precision, 
     g.q_tr = tr ? 1 : 0;
     for (int k = 0; k < 2; ++k) {
         g.q_rs[k] = (int)row_records(m, k);
-        g.qmask[k] = m->d_mask[k] ? m->d_mask[k] + ROW_SLACK * row_mask_words(m->q_cpl) : nullptr;
+        g.qmask[k] = m->d_mask[k] ? m->d_mask[k] + ROW_SLACK * mask_words(m) : nullptr;
         g.plane[k] = m->d_plane[k];
         g.n_plane[k] = (int)m->plane[k].size();
     }
@@ -713,7 +716,7 @@ obte_status resolve_waves(const obte_mesh* const* meshes, int n, const obte_solv
 }
 
 // Launch class of a mesh: the cells per lane of its rows.
-int launch_class(const obte_mesh* m) { return m->nz > 1 ? (m->nx + 63) / 64 : m->q_cpl; }
+int launch_class(const obte_mesh* m) { return m->q_cpl; }
 
 // Rows along y for direction l (2D, where they are in use at all).
 bool dir_transposed(const obte_mesh* m, int l, bool tr) {
@@ -1148,10 +1151,9 @@ obte_status solve_impl(obte_mesh* const* meshes, int n, const obte_solve_opts* o
         if ((J_out || keep_T) && n == 1) {
             PassParams rp = pp;
             rp.mode = 1;
-            rp.store_T = keep_T ? 1 : 0;
             s = launch_sweeps(R, rp, st);
             if (s != OBTE_OK) return s;
-            if (keep_T && R.nzmax == 1) HIPCHK(launch_keep(R.precision, meshes[0]->d_geom, st));
+            if (keep_T) HIPCHK(launch_keep(R.precision, meshes[0]->d_geom, st));
         }
     }
     if (n == 1 && (T_L_out || J_out)) HIPCHK(launch_output(meshes[0]->d_geom, R.precision, meshes[0]->ncells, T_L_out, o->only_fourier ? nullptr : J_out, nullptr, st));
@@ -1391,9 +1393,9 @@ obte_status obte_mesh_create(const obte_mesh_desc* d, obte_mesh** out) {
     // 2D rows along y: where y is periodic (else there is no coupling across
     // rows along x to begin with), fit on a wave, and do not make the rows
     // along x more than twice as wide on its lanes
-    if (nz == 1) {
+    {
         const int cx = (m->nx + 63) / 64, cy = (m->ny + 63) / 64;
-        m->q_tr = m->periodic[1] && cy <= 4 && cy <= 2 * cx;
+        m->q_tr = nz == 1 && m->periodic[1] && cy <= 4 && cy <= 2 * cx;
         m->q_cpl = m->q_tr ? std::max(cx, cy) : cx;
     }
     if (m->nsolid == 0) { delete m; return fail(OBTE_ERR_ARG, "the mesh has no solid cell"); }
@@ -1577,15 +1579,13 @@ obte_status obte_material_set(obte_mesh* m, const obte_material_desc* d) {
     if ((s = upload(&m->d_kax, m->kappa_axis)) != OBTE_OK) return s;
     for (int k = 0; k < 2; ++k)
         if ((s = upload(&m->d_plane[k], m->plane[k])) != OBTE_OK) return s;
-    if (m->nz == 1) {
-        for (int o = 0; o < (m->q_tr ? 2 : 1); ++o) {
-            const size_t rows = o ? m->nx : m->ny;
-            const size_t words = row_mask_words(m->q_cpl);
-            HIPCHK(hipMalloc((void**)&m->d_mask[o], (2 * rows + 2 * ROW_SLACK) * words * sizeof(unsigned long long)));
-            HIPCHK(launch_row_masks(m->d_fc, m->nx, m->ny, m->q_cpl, o, m->d_mask[o] + ROW_SLACK * words, nullptr));
-        }
-        HIPCHK(hipStreamSynchronize(nullptr));      // solves run on other streams
+    for (int o = 0; o < (m->q_tr ? 2 : 1); ++o) {
+        const size_t rows = o ? m->nx : (size_t)m->ny * m->nz;
+        const size_t words = mask_words(m);
+        HIPCHK(hipMalloc((void**)&m->d_mask[o], (2 * rows + 2 * ROW_SLACK) * words * sizeof(unsigned long long)));
+        HIPCHK(launch_row_masks(m->d_fc, m->nx, m->ny, m->nz, m->q_cpl, o, m->d_mask[o] + ROW_SLACK * words, nullptr));
     }
+    HIPCHK(hipStreamSynchronize(nullptr));      // solves run on other streams
     if (m->n_modes > 0) {
         if ((s = upload(&m->d_mode_sys, m->mode_sys)) != OBTE_OK) return s;
         if ((s = upload(&m->d_mode_w, m->mode_w)) != OBTE_OK) return s;
@@ -1882,7 +1882,7 @@ obte_status obte_checkpoint_load(obte_mesh* m, void* workspace, const char* path
     if (!f) return fail(OBTE_ERR_ARG, "cannot open %s", path);
     int hdr[9];
     const bool head = fread(hdr, sizeof hdr, 1, f) == 1;
-    const bool rows_x = head && hdr[0] == CKPT_MAGIC_ROWS_X;      // 2D inflows of rows along x only, or a 3D file
+    const bool rows_x = head && hdr[0] == CKPT_MAGIC_ROWS_X;      // inflows of rows along x only
     const int nwrap = rows_x ? m->nx * m->nz : (int)wrap_stride(m, m->q_tr);
     if (!head || (hdr[0] != CKPT_MAGIC && !rows_x) || hdr[1] != m->ncells ||
         hdr[2] != m->nwalls || hdr[3] != m->n_sys || hdr[4] != nwrap) {
@@ -1918,7 +1918,7 @@ obte_status obte_checkpoint_load(obte_mesh* m, void* workspace, const char* path
     };
     bool ok = load(v.ctrl, CTRL_N * sizeof(int)) && load(v.T_L, (size_t)m->ncells * 8) &&
               load(v.sT, 2 * (size_t)m->ncells * 8) && load(v.Tw, 2 * (size_t)std::max(m->nwalls, 1) * 8) &&
-              (rows_x && m->nz == 1 ? load_rows_x() : load(v.U, (size_t)m->n_sys * nwrap * tsz)) &&
+              (rows_x ? load_rows_x() : load(v.U, (size_t)m->n_sys * nwrap * tsz)) &&
               load(v.bnd, 2 * (size_t)m->nf * m->ncells * 8) &&
               load(v.ax, ((size_t)m->ncells + m->nwalls) * 8);
     int passes = 0;

@@ -1245,36 +1245,39 @@ hipError_t launch_pack_static(int precision, const GeomDev* geom_dev, int ncells
     return hipGetLastError();
 }
 
-// Lane masks of every sweep row (one wave per orientation, row direction and
-// row): row_mask_words(cpl) words, [0..5] the lanes whose segment before scan
-// step k has no cell closed to its x inflow, [6] the lanes reached from the
-// row's start without one, [7] all ones when the row has none, then per cell
-// of a lane: inflow along the row open (set in the padding), inflow through
-// the '-' / '+' face across the rows open, solid.
-__global__ void __launch_bounds__(64) k_row_masks(const uint16_t* __restrict__ fc, int nx, int ny, int cpl, int o,
+// Lane masks of every sweep row (one wave per row direction and row; o: rows
+// along y): row_mask_words(cpl) words, [0..5] the lanes whose segment before
+// scan step k has no cell closed to its inflow along the row, [6] the lanes
+// reached from the row's start without one, [7] all ones when the row has
+// none, then per cell of a lane: inflow along the row open (set in the
+// padding), inflow through the '-' / '+' face across the rows (y in 3D) open,
+// 3D: through the '-' / '+' z face, solid.
+__global__ void __launch_bounds__(64) k_row_masks(const uint16_t* __restrict__ fc, int nx, int ny, int nz, int cpl, int o,
                                                   unsigned long long* __restrict__ out) {
-    const int nr = o ? ny : nx, nw = o ? nx : ny, row = blockIdx.x % nw, negr = blockIdx.x / nw;
-    const int lane = threadIdx.x, pad = WAVE * cpl - nr, fr = 2 * o, fw = 2 - fr;
-    unsigned long long* w = out + (size_t)blockIdx.x * row_mask_words(cpl);
+    const int nr = o ? ny : nx, nw = o ? nx : ny * nz, row = blockIdx.x % nw, negr = blockIdx.x / nw;
+    const int lane = threadIdx.x, pad = WAVE * cpl - nr, fr = 2 * o, fw = 2 - fr, d3 = nz > 1;
+    unsigned long long* w = out + (size_t)blockIdx.x * (d3 ? row_mask_words3(cpl) : row_mask_words(cpl));
     bool ok = true;
     for (int c = 0; c < cpl; ++c) {
         const int p = lane * cpl + c - pad;
-        bool xo = true, y0 = false, y1 = false, sol = false;
+        bool xo = true, f[5] = {false, false, false, false, false};
         if (p >= 0) {
             const int pp = negr ? nr - 1 - p : p;
             const uint16_t v = fc[o ? pp * nx + row : row * nx + pp];
-            sol = fc_solid(v);
+            const bool sol = fc_solid(v);
             xo = sol && fc_class(v, fr + negr) != FC_WALL;
-            y0 = sol && fc_class(v, fw) != FC_WALL;
-            y1 = sol && fc_class(v, fw + 1) != FC_WALL;
+            f[0] = sol && fc_class(v, fw) != FC_WALL;
+            f[1] = sol && fc_class(v, fw + 1) != FC_WALL;
+            f[2] = d3 ? sol && fc_class(v, 4) != FC_WALL : sol;
+            f[3] = sol && fc_class(v, 5) != FC_WALL;
+            f[4] = sol;
         }
         ok = ok && xo;
-        const unsigned long long bx = __ballot(xo), b0 = __ballot(y0), b1 = __ballot(y1), bs = __ballot(sol);
-        if (lane == 0) {
-            w[8 + c] = bx;
-            w[8 + cpl + c] = b0;
-            w[8 + 2 * cpl + c] = b1;
-            w[8 + 3 * cpl + c] = bs;
+        const unsigned long long bx = __ballot(xo);
+        if (lane == 0) w[8 + c] = bx;
+        for (int q = 0; q < (d3 ? 5 : 3); ++q) {
+            const unsigned long long b = __ballot(f[q]);
+            if (lane == 0) w[8 + (1 + q) * cpl + c] = b;
         }
     }
     const unsigned long long good = __ballot(ok);
@@ -1296,9 +1299,10 @@ __global__ void __launch_bounds__(64) k_row_masks(const uint16_t* __restrict__ f
     if (lane == 0) w[7] = good == ~0ull ? ~0ull : 0ull;
 }
 
-hipError_t launch_row_masks(const uint16_t* fc, int nx, int ny, int cpl, int o, unsigned long long* out, hipStream_t st) {
+hipError_t launch_row_masks(const uint16_t* fc, int nx, int ny, int nz, int cpl, int o, unsigned long long* out,
+                            hipStream_t st) {
     (void)hipGetLastError();
-    hipLaunchKernelGGL(k_row_masks, dim3(2 * (o ? nx : ny)), dim3(64), 0, st, fc, nx, ny, cpl, o, out);
+    hipLaunchKernelGGL(k_row_masks, dim3(2 * (o ? nx : ny * nz)), dim3(64), 0, st, fc, nx, ny, nz, cpl, o, out);
     return hipGetLastError();
 }
 

@@ -102,7 +102,7 @@ struct GeomDev {
     int q_rs[2];                 // records per row: the row's cells rounded up to q_cpl
     uint32_t* qoff;              // rows along x, per negr: byte offset of the cell's stored value, QOFF_NONE in pores
     uint32_t* qoffc;             // the same by cell
-    const unsigned long long* qmask[2];   // lane masks of the rows (k_row_masks)
+    const unsigned long long* qmask[2];   // lane masks of the rows (k_row_masks; 3D: the first)
     const int* plane[2];         // solid indices of the open plane cells at the low / high end of the gradient axis
     int n_plane[2];
     void* qrec;                  // 3D: the pass's sources (ncells) and inflow tables (nf * ncells) in the
@@ -136,6 +136,7 @@ constexpr size_t tr_tile_bytes(int cpl) { return 64 * (64 * (size_t)cpl + 4); }
 constexpr int ROW_SLACK = 4, OFF_SLACK = 16;
 // words of one row's lane masks
 __host__ __device__ constexpr int row_mask_words(int cpl) { return 8 + 4 * cpl; }
+__host__ __device__ constexpr int row_mask_words3(int cpl) { return 8 + 6 * cpl; }
 
 constexpr int AA_MAX = 8;
 
@@ -151,7 +152,6 @@ struct PassParams {
     double inner_tol;
     int max_inner;
     int mode;          // 0 = full pass, 1 = replay the last pass's final sweep only (J / store)
-    int store_T;       // write the final x of every system to Tstore
     int adjoint;       // 1 = transposed system with adjoint sources
     int max_outer;
     double outer_tol;
@@ -184,10 +184,12 @@ hipError_t launch_sweep_queue(int precision, const GeomDev* geoms_dev, const Ite
 // queue (the persistent launch's item counter) is set to 0.
 hipError_t launch_pack_rows(int precision, const GeomDev* geoms_dev, int n_geoms, int max_cells, PassParams pp,
                             hipStream_t st, int* queue);
-// 2D: sigma and the store offsets in the rows' order (once per solve), the
-// rows' lane masks (once per mesh), the FP64 copy of a replayed pass.
+// 2D: sigma and the store offsets in the rows' order (once per solve).  The
+// rows' lane masks (once per mesh; nz > 1: the 3D form), the FP64 copy of a
+// replayed pass.
 hipError_t launch_pack_static(int precision, const GeomDev* geom_dev, int ncells, hipStream_t st);
-hipError_t launch_row_masks(const uint16_t* fc, int nx, int ny, int cpl, int o, unsigned long long* out, hipStream_t st);
+hipError_t launch_row_masks(const uint16_t* fc, int nx, int ny, int nz, int cpl, int o, unsigned long long* out,
+                            hipStream_t st);
 hipError_t launch_keep(int precision, const GeomDev* geom_dev, hipStream_t st);
 // 3D: the pass's sources and inflow tables in the compute type (GeomDev::qrec).
 hipError_t launch_pack3(int precision, const GeomDev* geoms_dev, int n_geoms, int max_cells, PassParams pp,

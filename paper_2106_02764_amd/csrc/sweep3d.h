@@ -1,456 +1,317 @@
-// The 3D pass: see kernels.hip for the method.
+// The 3D pass (see kernels.hip for the method): one wavefront owns one (m, l)
+// system and sweeps rows along x, the planes of a y row in z-upwind order.
+// The previous y row of every plane is in the wave's LDS, which also brings
+// the wrap inflow in (as the row before the first) and the last y row out;
+// the row below in z is in registers.  The wrap plane of a system (nx nz
+// values) is too large for registers, so its Krylov vectors live in a
+// per-system slab of the workspace (KRY3_VECS planes), where every element is
+// read and written only by the lane owning its column.
+//
+// Bound: vector issue (5 waves per SIMD keep it busy).  With the row's face
+// classes as lane masks, constant scan weights (rows.h) and one running row
+// index, a row of 64 FP32 cells takes 36 vector and 30 scalar instructions
+// where decoding the face words per system and scanning Q along took 79 and
+// 53 (64 x 64 x 16 membrane, 288 directions x 30 MFPs: 1.64 -> 0.86 ms a
+// launch on average).
 #pragma once
-#include "device.h"
+#include "rows.h"
 
 namespace {
 
-// per-row inputs of one lane (prefetched ahead of use; the 3D-only fields
-// have one dummy entry in 2D, so the rotation buffers stay in registers)
-template <typename T, int CPL, bool D3>
-struct RowIn {
-    uint32_t w[CPL];
-    T sg[CPL];
-    T sb[CPL];          // base source (sigma T_L, or k + D Psi), compute type
-    T bx[CPL], by[CPL];                 // inflow boundary values per axis
-    T bz[D3 ? CPL : 1];
-    int si[CPL];        // solid index of the cell (sweeps that store), -1 in pores
-    T ui[D3 ? CPL : 1]; // 3D: the wrap-plane input of the row's plane (used on the first y-row)
-};
-
-// Row results of a storing sweep, kept in registers until a group of rows is
-// stored together.  A wave's global loads and stores share one counter on
-// gfx9, and with both kinds in flight every wait for a prefetched row must
-// drain the whole counter; storing once per group keeps the row prefetch
-// overlapped everywhere else.
-template <typename T, int CPL>
-struct RowOut {
-    T x[CPL];
-    int si[CPL];        // -1: nothing to store
-};
-
-// per-sweep constant views: buffer resources of the per-cell tables and of
-// the 3D wrap-plane input, and this lane's byte offsets within a row
-template <typename T, int CPL>
-struct Views {
-    rsrc_t fc, sidx, sg, u, src, bx, by, bz;
-    uint32_t o2[CPL], o4[CPL], oT[CPL], ou[CPL];
-    // geometry scalars read once per sweep: the row loop stores to global
-    // memory, after which the compiler would reload them from the view
-    int nx, ny, nz, ga;
-    int lx, cx;                        // lane and register of a row's last cell (p = nx - 1)
-    double dT;
-};
-
-template <typename T, int CPL, bool D3, bool WITH_B, bool S1, bool ST>
-__device__ __forceinline__ void load_row(const GeomDev& g, const SysC<T>& s, const Views<T, CPL>& v, int lane,
-                                         int jj, int kk, RowIn<T, CPL, D3>& r) {
-    // every lane loads (beyond the row: the row's first cell, masked by the
-    // row step), so no load sits in a branch or feeds a select here: the
-    // compiler then counts the loads in flight exactly and waits only for
-    // the row it is about to use
-    const int iy = s.pos[1] ? jj : v.ny - 1 - jj;
-    const int iz = D3 ? (s.pos[2] ? kk : v.nz - 1 - kk) : 0;
-    const uint32_t rowbase = uni((uint32_t)(v.nx * (iy + v.ny * iz)));
-#pragma unroll
-    for (int c = 0; c < CPL; ++c) {
-        r.w[c] = bld16(v.fc, v.o2[c], rowbase * 2u);
-        if (ST) r.si[c] = (int)bld32(v.sidx, v.o4[c], rowbase * 4u);
-        r.sg[c] = S1 ? T(1) : bldT<T>(v.sg, v.oT[c], rowbase * (uint32_t)sizeof(T));
-        if (WITH_B) {
-            const uint32_t rb = rowbase * (uint32_t)sizeof(T);
-            r.sb[c] = bldT<T>(v.src, v.oT[c], rb);
-            r.bx[c] = bldT<T>(v.bx, v.oT[c], rb);
-            r.by[c] = bldT<T>(v.by, v.oT[c], rb);
-            if (D3) r.bz[c] = bldT<T>(v.bz, v.oT[c], rb);
-        }
-        if (D3) r.ui[c] = bldT<T>(v.u, v.ou[c], uni((uint32_t)(kk * v.nx)) * (uint32_t)sizeof(T));
-    }
-}
-
-// Row storage of the sweep.  2D: the previous row in registers.  3D: the
-// previous y-row of every z-plane in this wave's LDS region (the plane index
-// is a runtime value), and the row just below in z in registers.
-template <typename T, int CPL, bool D3>
-struct Rows {
-    T xr[CPL];    // 2D: row jj-1; 3D: row (jj, kk-1)
-    T* xz;        // 3D: nz * ROW values, plane kk holds row (jj-1, kk) until overwritten
-    int ROW;
-    __device__ __forceinline__ T prev_y(int kk, int c, int lane) const {
-        return D3 ? xz[kk * ROW + lane * CPL + c] : xr[c];
-    }
-    __device__ __forceinline__ T prev_z(int c) const { return D3 ? xr[c] : T(0); }
-    __device__ __forceinline__ void put(int kk, int c, int lane, T v) {
-        if (D3) xz[kk * ROW + lane * CPL + c] = v;
-        xr[c] = v;
-    }
-};
-
-// Wrap-row input (inflow u of the first row) and output (the last row).
-// 2D: register arrays of this lane.  3D: the system's nz x nx plane in
-// global memory, element (kk, p) at kk * nx + p, always touched by the lane
-// that owns column p, so no cross-lane ordering is needed.
-template <typename T, int CPL>
-struct RegIO {
-    const T (&u)[CPL];
-    T (&xl)[CPL];
-    __device__ __forceinline__ T in(int, int c, int) const { return u[c]; }
-    __device__ __forceinline__ const T* input() const { return nullptr; }
-    __device__ __forceinline__ void out(int, int c, int, T v) { xl[c] = v; }
-};
-template <typename T, int CPL>
-struct GlobIO {
-    gptr_t<T> u;
-    rsrc_t xl;           // size 0 when the last row is not needed (or the wave is inactive)
-    int nx;
-    __device__ __forceinline__ const T* input() const { return (const T*)u; }
-    // the row loads prefetch the input (Views::u); nothing is read here
-    __device__ __forceinline__ T in(int, int, int) const { return T(0); }
-    // a buffer store in no per-lane branch (beyond the row: an offset past
-    // the plane, dropped), so the compiler keeps counting the row prefetches
-    // in flight exactly across it
-    __device__ __forceinline__ void out(int kk, int c, int lane, T v) {
-        const int p = lane * CPL + c;
-        bst(v, xl, p < nx ? (uint32_t)(kk * nx + p) * (uint32_t)sizeof(T) : BUF_OOB);
-    }
-};
-// out_plane: the nz x nx plane receiving the last row, or nullptr
-template <typename T, int CPL>
-__device__ __forceinline__ GlobIO<T, CPL> make_gio(gptr_t<T> u, gmut_t<T> out_plane, int nx, int nz, int active) {
-    GlobIO<T, CPL> io;
-    io.u = u;
-    io.xl = make_rsrc((const T*)out_plane, (out_plane && active) ? (uint32_t)(nx * nz) * (uint32_t)sizeof(T) : 0u);
-    io.nx = nx;
-    return io;
-}
-
-// One row step of the sweep (cells of row (jj, kk) in upwind order).  FULL:
-// the row fills every lane (nx = 64 CPL), so no lane holds cells beyond it.
-template <typename T, int CPL, bool D3, bool WITH_B, bool RED, bool ADD, bool S1, int GA, bool FULL = false,
-          class IO>
-__device__ __forceinline__ void row_step(const GeomDev& g, const SysC<T>& s, const Views<T, CPL>& vw,
-                                         int active, int lane, int adj, int jj, int kk,
-                                         const RowIn<T, CPL, D3>& cur, Rows<T, CPL, D3>& rows, IO& io,
-                                         const double (&mb)[3], Red<T>* rd, RowOut<T, CPL>& ro) {
-    const int nx = vw.nx, ny = vw.ny;
-    const T cz = D3 ? s.c[2] : T(0);
-    // diagonal without sigma (2D: no z term, so no +0 is left in the chain)
-    const T cdiag = D3 ? s.c[0] + s.c[1] + cz : s.c[0] + s.c[1];
-    const T cyz = D3 ? s.c[1] + cz : s.c[1];
-    // sigma = 1: the cell coefficients are this system's constants
-    const T rdv1 = S1 ? recip(T(1) + cdiag) : T(0);
-    const T q1 = s.c[0] * rdv1, pxs1 = (T(1) + cyz) * rdv1, pnx1 = (T(1) + cdiag) * rdv1;
-    T a[CPL], q[CPL];
-    T Al, Pl;
-#pragma unroll
-    for (int c = 0; c < CPL; ++c) {
-        const int p = lane * CPL + c;
-        const uint32_t w = (FULL || p < nx) ? cur.w[c] : 0u;     // beyond the row: not solid
-        const bool sol = active && fc_solid(w);
-        const int clx = fc_class(w, s.fin[0]);
-        const int cly = fc_class(w, s.fin[1]);
-        const int clz = D3 ? fc_class(w, s.fin[2]) : FC_WALL;
-        // sigma = 1 everywhere (no multiplier given): rdv is this system's constant
-        const T sg = S1 ? T(1) : cur.sg[c];
-        const T rdv = S1 ? rdv1 : recip(sg + cdiag);
-        // kk and jj are wave-uniform: the wrap input is used on the first row
-        // only (3D: prefetched with every row, so its load is in no branch)
-        const T uin = D3 ? ((FULL || p < nx) ? cur.ui[c] : T(0)) : io.in(kk, c, lane);
-        // the row below in y is read unconditionally (no branch around the
-        // LDS load) and selected
-        const T py = rows.prev_y(kk, c, lane);
-        const T yin = cly != FC_WALL ? ((jj == 0) ? uin : s.c[1] * py) : T(0);
-        T rhs = yin;
-        if (WITH_B) {
-            // in the compute type (the sources were converted once per pass)
-            T sd = adj ? (T)s.kw + (T)s.Dml * cur.sb[c] : cur.sb[c];
-            sd += (T)mb[0] * cur.bx[c] + (T)mb[1] * cur.by[c];
-            if (D3) sd += (T)mb[2] * cur.bz[c];
-            rhs = sd + yin;
-        }
-        if (D3) rhs += (clz != FC_WALL && kk > 0) ? cz * rows.prev_z(c) : T(0);
-        const bool xs = (clx != FC_WALL);
-        T av = rhs * rdv;
-        T qv = xs ? (S1 ? q1 : s.c[0] * rdv) : T(0);
-        T pv = S1 ? (xs ? pxs1 : pnx1) : (sg + (xs ? cyz : cdiag)) * rdv;
-        // pore: (0, 0, 1) breaks the chain; beyond the row (face word 0, so
-        // not solid either): the identity (0, 1, 0)
-        const bool beyond = !FULL && p >= nx;
-        av = sol ? av : T(0);
-        qv = sol ? qv : (beyond ? T(1) : T(0));
-        pv = sol ? pv : (beyond ? T(0) : T(1));
-        a[c] = av;
-        q[c] = qv;
-        if (c == 0) {
-            Al = av;
-            Pl = pv;
-        } else {
-            Al = av + qv * Al;
-            Pl = pv + qv * Pl;
-        }
-    }
-    T A = Al, P = Pl;
-    wave_scan(A, P);
-    const T At = readlane(A, WAVE - 1), Pt = readlane(P, WAVE - 1);
-    const T xin = (Pt > T(0)) ? At * recip(Pt) : T(0);   // cyclic closure x_{-1} = x_{nx-1}
-    const T Ae = dpp<0x138, 0xf>(A, T(0)), Pe = dpp<0x138, 0xf>(P, T(0));   // wave_shr:1
-    T xp = Ae + (T(1) - Pe) * xin;
-    T xrow[CPL];
-#pragma unroll
-    for (int c = 0; c < CPL; ++c) {
-        const T xv = a[c] + q[c] * xp;
-        const int p = lane * CPL + c;
-        xrow[c] = (FULL || p < nx) ? xv : T(0);
-        rows.put(kk, c, lane, xrow[c]);
-        xp = xv;
-    }
-    if (jj == ny - 1) {
-#pragma unroll
-        for (int c = 0; c < CPL; ++c) io.out(kk, c, lane, xrow[c]);
-    }
-    if (RED) {
-        // branch-free: cells that contribute nothing add an exact 0 (an
-        // inactive wave's sums are dropped, its stores skipped)
-        // the row's cells summed in the compute type, the rows in double
-        T rsum = T(0);
-#pragma unroll
-        for (int c = 0; c < CPL; ++c) {
-            const int p = lane * CPL + c;
-            const uint32_t wv = (FULL || p < nx) ? cur.w[c] : 0u;
-            const bool sol = fc_solid(wv);
-            ro.x[c] = xrow[c];
-            ro.si[c] = sol ? cur.si[c] : -1;
-            rsum += sol ? xrow[c] : T(0);
-        }
-        rd->kacc += (double)rsum;
-        // Flux through the periodic plane of the gradient axis (kappa_face;
-        // the adjoint: p^T lambda of the jump inflow, on the forward's jump
-        // faces = this sweep's outflow faces).  The jump term belongs to the
-        // b sweep only.
-        if (GA == 0) {
-            // the plane's cell of a row is its last cell in sweep order
-            // (p = nx - 1): one lane's value, read into a scalar, added on
-            // lane 0 (the wave sum then equals the sum over the rows)
-            // (each register is read into a scalar and the scalars are
-            // selected: selecting the registers first would let the compiler
-            // index the row buffers at run time, which puts them in memory)
-            T xl = readlane(xrow[0], vw.lx);
-            uint32_t wl = (uint32_t)__builtin_amdgcn_readlane((int)cur.w[0], vw.lx);
-#pragma unroll
-            for (int c = 1; c < CPL; ++c) {
-                const T xc = readlane(xrow[c], vw.lx);
-                const uint32_t wc = (uint32_t)__builtin_amdgcn_readlane((int)cur.w[c], vw.lx);
-                xl = (c == vw.cx) ? xc : xl;
-                wl = (c == vw.cx) ? wc : wl;
-            }
-            double add = 0.0;
-            if (fc_solid(wl)) {
-                const int cl = fc_class(wl, s.fout[0]);
-                const double xd = (double)xl;
-                if (adj) {
-                    const double cj = s.cd[0] * vw.dT;
-                    add = cl == FC_JUMP_P ? cj * xd : (cl == FC_JUMP_M ? -cj * xd : 0.0);
-                } else {
-                    add = cl != FC_WALL ? xd + ((!ADD && s.pos[0]) ? vw.dT : 0.0) : 0.0;
-                }
-            }
-            rd->kface += lane == 0 ? add : 0.0;
-        } else if (GA == 1 && jj == ny - 1) {
-#pragma unroll
-            for (int c = 0; c < CPL; ++c) {
-                const int p = lane * CPL + c;
-                const uint32_t wv = (FULL || p < nx) ? cur.w[c] : 0u;
-                // selects, not per-lane branches: a divergent region in the
-                // row loop makes the compiler wait for every row prefetch
-                const double xv = (double)xrow[c];
-                const int cl = fc_class(wv, s.fout[1]);
-                double add;
-                if (adj) {
-                    const double cj = s.cd[1] * vw.dT;
-                    add = cl == FC_JUMP_P ? cj * xv : (cl == FC_JUMP_M ? -cj * xv : 0.0);
-                } else {
-                    add = cl != FC_WALL ? xv + ((!ADD && s.pos[1]) ? vw.dT : 0.0) : 0.0;
-                }
-                rd->kface += fc_solid(wv) ? add : 0.0;
-            }
-        }
-    }
-}
-
-// Store a group of rows of a storing sweep (ADD: add to the stored values);
-// cells with nothing to store get an out-of-range offset, so every lane
-// issues the same stores and the hardware drops those.
-template <typename T, int CPL, int NR, bool ADD>
-__device__ __forceinline__ void store_rows(Red<T>* rd, const RowOut<T, CPL> (&ro)[NR]) {
-    // no branch on rd->on: an inactive wave's resources have size 0
-#pragma unroll
-    for (int r = 0; r < NR; ++r)
-#pragma unroll
-        for (int c = 0; c < CPL; ++c) {
-            const int i = ro[r].si[c];
-            const uint32_t vo = i >= 0 ? (uint32_t)i * (uint32_t)sizeof(T) : BUF_OOB;
-            T v = ro[r].x[c];
-            if (ADD) v += bldT<T>(rd->X, vo, 0);
-            bst(v, rd->X, vo);
-            if (rd->store_T) bst((double)ro[r].x[c], rd->Tstore, i >= 0 ? (uint32_t)i * 8u : BUF_OOB);
-        }
-}
-
-// ---------------------------------------------------------------------------
-// The upwind sweep x = M^{-1}(src + P u): rows in y-upwind order (planes in
-// z-upwind order), each row's cyclic x-recurrence solved by a wavefront scan.
-// WITH_B: the pass sources are included, otherwise the only source is the
-// wrap inflow u.  RED: lockstep reductions (every wave of the block calls
-// it); ADD: add to the partials written by an earlier RED sweep of the same
-// block.  Returns the last row (jj = ny-1) in xl.  Row inputs are prefetched
-// two rows ahead (2D) through a three-buffer rotation without copies.
-// ---------------------------------------------------------------------------
-
-
-template <typename T, int CPL, bool D3, bool WITH_B, bool RED, bool ADD, bool S1, int GA, bool FULL = false,
-          class IO>
-__device__ __forceinline__ void sweep(const GeomDev& g, const SysC<T>& s, int active, int lane, int adj,
-                                      const T* __restrict__ srcbase, const T* __restrict__ bnd,
-                                      IO& io, Red<T>* rd, T* zrows) {
-    constexpr int ND = D3 ? 3 : 2;
-    double mb[3];
-    // boundary input face per axis: forward, the wall this direction enters
-    // from; adjoint, the wall whose temperature takes this system, the one
-    // that S leaves through (with kappa_m weights: the reversed inflow face)
-    int fb[3];
-#pragma unroll
-    for (int ax = 0; ax < 3; ++ax) {
-        fb[ax] = adj ? 2 * ax + (s.S[ax] > 0.0 ? 1 : 0) : s.fin[ax];
-        mb[ax] = adj ? (ax < ND ? g.wout[fb[ax] * g.n_sys + s.sys] : 0.0) : s.cd[ax];
-    }
-    Views<T, CPL> vw;
-    const uint32_t nc = (uint32_t)g.ncells;
-    vw.fc = make_rsrc(g.fc, nc * 2u);
-    vw.sidx = make_rsrc(g.sidx, nc * 4u);
-    vw.sg = make_rsrc(sigma_ptr<T>(g), nc * (uint32_t)sizeof(T));
-    vw.u = make_rsrc(io.input(), (uint32_t)(g.nx * g.nz) * (uint32_t)sizeof(T));
-    const uint32_t tb = nc * (uint32_t)sizeof(T);
-    vw.src = make_rsrc(srcbase, tb);
-    vw.bx = make_rsrc(bnd + (size_t)fb[0] * g.ncells, tb);
-    vw.by = make_rsrc(bnd + (size_t)fb[1] * g.ncells, tb);
-    vw.bz = make_rsrc(bnd + (size_t)(D3 ? fb[2] : 0) * g.ncells, tb);
-#pragma unroll
-    for (int c = 0; c < CPL; ++c) {
-        // cell of this lane within a row (beyond the row: the row's first cell)
-        const int p = lane * CPL + c;
-        const uint32_t lo = p < g.nx ? (uint32_t)(s.pos[0] ? p : g.nx - 1 - p) : 0u;
-        vw.o2[c] = lo * 2u;
-        vw.o4[c] = lo * 4u;
-        vw.oT[c] = lo * (uint32_t)sizeof(T);
-        vw.ou[c] = (uint32_t)min(p, g.nx - 1) * (uint32_t)sizeof(T);
-    }
-    vw.nx = uni(g.nx);
-    vw.ny = uni(g.ny);
-    vw.nz = uni(g.nz);
-    vw.ga = uni(g.grad_axis);
-    vw.lx = (vw.nx - 1) / CPL;
-    vw.cx = (vw.nx - 1) % CPL;
-    vw.dT = uni(g.dT);
-    Rows<T, CPL, D3> rows;
-#pragma unroll
-    for (int c = 0; c < CPL; ++c) rows.xr[c] = T(0);
-    rows.xz = zrows;
-    rows.ROW = WAVE * CPL;
-    const int ny = g.ny;
-    // Rows (jj, kk) in order, kk inner (2D: kk = 0).  A three-buffer
-    // rotation keeps the inputs two rows ahead; prefetches are never skipped
-    // (past the last row they reload it): a load inside a branch would leave
-    // the compiler unsure how many loads are in flight at the join, and it
-    // would then wait for all.  A storing sweep stores each group of three
-    // rows after the group's last row.
-    const int nz = D3 ? g.nz : 1, nrows = ny * nz;
-    // row r -> (r / nz, r % nz) by a multiply with mz = ceil(2^32 / nz), not a
-    // division per row: r mz / 2^32 = r / nz + r e / (nz 2^32) with e = mz nz
-    // - 2^32 < nz, so the floor is exact while r e < 2^32, i.e. for every
-    // r < 2^25 (nz <= 128)
-    const uint64_t mz = D3 ? ((1ull << 32) + (uint64_t)nz - 1) / (uint64_t)nz : 1ull;
-    auto row_j = [&](int r) { return D3 ? (int)(((uint64_t)(uint32_t)r * mz) >> 32) : r; };
-    auto pre = [&](int r, RowIn<T, CPL, D3>& b) {
-        const int rr = min(r, nrows - 1);
-        const int jr = row_j(rr);
-        load_row<T, CPL, D3, WITH_B, S1, RED>(g, s, vw, lane, jr, D3 ? rr - jr * nz : 0, b);
-    };
-    auto step = [&](int r, const RowIn<T, CPL, D3>& b, RowOut<T, CPL>& ro) {
-        const int jr = row_j(r);
-        row_step<T, CPL, D3, WITH_B, RED, ADD, S1, GA, FULL>(g, s, vw, active, lane, adj, jr, D3 ? r - jr * nz : 0,
-                                                       b, rows, io, mb, rd, ro);
-    };
-    RowIn<T, CPL, D3> b0, b1, b2;
-    pre(0, b0);
-    pre(1, b1);
-    for (int r = 0; r < nrows; r += 3) {
-        RowOut<T, CPL> ro[3];
-#pragma unroll
-        for (int q = 0; q < 3; ++q)
-#pragma unroll
-            for (int c = 0; c < CPL; ++c) ro[q].si[c] = -1;
-        pre(r + 2, b2);
-        step(r, b0, ro[0]);
-        pre(r + 3, b0);
-        if (r + 1 < nrows) step(r + 1, b1, ro[1]);
-        pre(r + 4, b1);
-        if (r + 2 < nrows) step(r + 2, b2, ro[2]);
-        if (RED) store_rows<T, CPL, 3, ADD>(rd, ro);
-    }
-}
+enum { KV_R, KV_E, KV_EB, KV_RH, KV_P, KV_V, KV_S, KV_T, KV_N };
+static_assert(KV_N <= KRY3_VECS, "workspace carve and kernel disagree on the 3D slab");
 
 template <typename T>
-__device__ __forceinline__ Red<T> make_red(const GeomDev& g, const SysC<T>& s, int active, const PassParams& pp) {
-    Red<T> rd;
-    rd.kacc = 0.0;
-    rd.kface = 0.0;
-    rd.on = active;
-    // size 0 for an inactive wave: every store through it is dropped
-    rd.X = make_rsrc(reinterpret_cast<T*>(g.X) + (size_t)s.sys * g.xs,
-                     active ? (uint32_t)g.nsolid * (uint32_t)sizeof(T) : 0u);
-    rd.Tstore = make_rsrc(g.Tstore ? g.Tstore + (size_t)s.sys * g.xs : nullptr,
-                          (g.Tstore && active) ? (uint32_t)g.nsolid * 8u : 0u);
-    rd.store_T = pp.store_T && g.Tstore != nullptr;
-    return rd;
-}
+struct Sys3 {
+    int sys;
+    int neg[3];              // the sweep runs towards - along the axis
+    double cd[3];            // Lambda |s_a| / h_a
+    T sk, sdm;               // adjoint: constant source and T_L weight
+    T mb[3], mo[3];          // weights of the boundary values of the inflow / outflow faces
+    double kw, Sg;
+};
 
 template <typename T>
-__device__ __forceinline__ void finish_system(const GeomDev& g, const SysC<T>& s, int active, int lane,
-                                              int adj, const PassParams& pp, const Red<T>& rd,
-                                              long long n_it, long long n_sw) {
-    const double ks = wave_sum(rd.kacc), kf = wave_sum(rd.kface);
-    if (active && lane == 0) {
+__device__ __forceinline__ Sys3<T> make_sys3(const GeomDev& g, int m, int l, int adj) {
+    Sys3<T> s;
+    s.sys = uni(m * g.n_dir + l);
+    const double lam = g.mfp[m];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        double sa = g.dirs[l * 3 + a];
+        if (adj) sa = -sa;   // A_l^T = A_{-l} on a uniform grid
+        s.neg[a] = uni(sa > 0.0 ? 0 : 1);
+        s.cd[a] = uni(lam * fabs(sa) / g.h[a]);
+        s.mb[a] = uni((T)s.cd[a]);
+        s.mo[a] = T(0);
         if (adj) {
-            g.ksys[s.sys] = kf;                 // this system's share of p^T lambda
-            g.kfsys[s.sys] = 0.0;
-        } else {
-            g.kraw[s.sys] = ks;
-            g.ksys[s.sys] = g.L[g.grad_axis] / (g.dT * (double)g.ncells) * s.Sg * ks;
-            g.kfsys[s.sys] = g.L[g.grad_axis] / (g.dT * (double)g.n_perp) * s.Sg * kf;
-        }
-        if (pp.mode == 0) {
-            g.iters[s.sys] += n_it;
-            g.sweeps[s.sys] += n_sw;
+            // the outgoing wall weight of the face S leaves through (the
+            // sweep's inflow face, or with a mode table possibly its outflow
+            // face)
+            const int f = 2 * a + (g.S[s.sys * 3 + a] > 0.0 ? 1 : 0);
+            const T wv = (T)g.wout[(size_t)f * g.n_sys + s.sys];
+            const bool in = f == 2 * a + s.neg[a];
+            s.mb[a] = uni(in ? wv : T(0));
+            s.mo[a] = uni(in ? T(0) : wv);
         }
     }
+    s.Sg = g.S[s.sys * 3 + g.grad_axis];
+    s.kw = g.L[g.grad_axis] / (g.dT * (double)g.ncells) * s.Sg;
+    s.sk = uni((T)s.kw);
+    s.sdm = uni((T)g.Dw[s.sys]);
+    return s;
 }
 
-// ---------------------------------------------------------------------------
-// The 3D pass.  Same phases as the 2D kernel; the wrap plane of a system
-// (nx * nz values) is too large for registers, so its Krylov vectors live in
-// a per-system slab of the workspace (KV_N planes).  Every element (k, p) is
-// read and written only by the lane owning column p, as in the sweep.
-// ---------------------------------------------------------------------------
-enum { KV_XL, KV_MK, KV_DU, KV_R, KV_E, KV_EB, KV_RH, KV_P, KV_V, KV_S, KV_T, KV_N };
-static_assert(KV_N == KRY3_VECS, "workspace carve and kernel disagree on the 3D slab");
+template <typename T, int CPL, bool ST, bool WITH_B, bool ADJ, bool S1, bool FULL>
+struct Sweep3 {
+    static constexpr bool ADJB = ADJ && WITH_B;
+    static constexpr int ROW = WAVE * CPL;
+    using Mask = RowMask<CPL, S1, ADJB, true>;
+    const Sys3<T>& s;
+    const QConst<T, CPL, FULL>& k;
+    const int lane, nx, ny, nz;
+    T* const zl;             // this lane's cells in the wave's LDS rows: plane p at zl + p * ROW
+    const rsrc_t X;
+    rsrc_t src, b[3], o[3], sg, sidx;
+    uint32_t oc[CPL];        // this lane's cells within a row (OOB in the padding)
+    mview_t mask;
+    double kt;
+    T xz[CPL];               // the row below in z
 
-#define PLOOP(body)                                     \
-    for (int k = 0; k < nz; ++k)                        \
-        _Pragma("unroll") for (int c = 0; c < CPL; ++c) { \
-            const int p_ = lane * CPL + c;              \
-            if (p_ < nx) {                              \
-                const int i = k * nx + p_;              \
-                body;                                   \
-            }                                           \
+    struct In {
+        T sb[CPL], b[3][CPL], o[3][CPL], sg[CPL];
+        int si[CPL];
+    };
+    // rows in sweep order: plane within y row, and the grid row iy + ny iz
+    struct Pos {
+        int j, kk;
+    };
+
+    __device__ __forceinline__ Sweep3(const GeomDev& g, const Sys3<T>& s_, const QConst<T, CPL, FULL>& k_, int lane_, T* zrows,
+                                      rsrc_t X_)
+        : s(s_), k(k_), lane(lane_), nx(uni(g.nx)), ny(uni(g.ny)), nz(uni(g.nz)), zl(zrows + lane_ * CPL), X(X_) {
+        const uint32_t nc = (uint32_t)g.ncells, tb = nc * (uint32_t)sizeof(T);
+        const T* base = static_cast<const T*>(g.qrec);
+        src = make_rsrc(base, tb);
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            b[a] = make_rsrc(base + (size_t)(1 + 2 * a + s.neg[a]) * nc, tb);
+            if (ADJB) o[a] = make_rsrc(base + (size_t)(2 + 2 * a - s.neg[a]) * nc, tb);
+        }
+        if (!S1) sg = make_rsrc(sigma_ptr<T>(g), tb);
+        sidx = make_rsrc(g.sidx, nc * 4u);
+#pragma unroll
+        for (int c = 0; c < CPL; ++c) {
+            const int p = lane * CPL + c - (WAVE * CPL - nx);
+            oc[c] = p >= 0 ? (uint32_t)(s.neg[0] ? nx - 1 - p : p) : BUF_OOB / 8u;
+        }
+        mask = (mview_t)(uni(g.qmask[0]) + (size_t)s.neg[0] * ny * nz * row_mask_words3(CPL));
+        kt = 0.0;
+    }
+
+    __device__ __forceinline__ uint32_t grid_row(const Pos& p) const {
+        return uni((uint32_t)((s.neg[1] ? ny - 1 - p.j : p.j) + ny * (s.neg[2] ? nz - 1 - p.kk : p.kk)));
+    }
+    // the next row (past the last: within the last y row, unused)
+    __device__ __forceinline__ void next(Pos& p) const {
+        const bool end = p.kk + 1 == nz;
+        p.kk = uni(end ? 0 : p.kk + 1);
+        p.j = uni(end ? min(p.j + 1, ny - 1) : p.j);
+    }
+    __device__ __forceinline__ void load(uint32_t row, In& r) const {
+        const uint32_t k0 = uni(row * (uint32_t)nx), oT = k0 * (uint32_t)sizeof(T);
+#pragma unroll
+        for (int c = 0; c < CPL; ++c) {
+            const uint32_t v = oc[c] * (uint32_t)sizeof(T);
+            if (WITH_B) {
+                r.sb[c] = bldT<T>(src, v, oT);
+#pragma unroll
+                for (int a = 0; a < 3; ++a) {
+                    r.b[a][c] = bldT<T>(b[a], v, oT);
+                    if (ADJB) r.o[a][c] = bldT<T>(o[a], v, oT);
+                }
+            }
+            if (!S1) r.sg[c] = bldT<T>(sg, v, oT);
+            if (ST) {
+                r.si[c] = (int)bld32(sidx, oc[c] * 4u, k0 * 4u);
+                if (!FULL) r.si[c] = oc[c] == BUF_OOB / 8u ? -1 : r.si[c];
+            }
+        }
+    }
+    __device__ __forceinline__ void masks(uint32_t row, Mask& m) const {
+        load_mask(mask + (size_t)row * row_mask_words3(CPL), s.neg[1], s.neg[2], m);
+    }
+    __device__ __forceinline__ T source(const In& r, const Mask& m, int c, T ksb, const T (&kb)[3], const T (&ko)[3], T kk) const {
+        T a;
+        if (ADJB) {
+            a = kk + ksb * r.sb[c];
+#pragma unroll
+            for (int x = 0; x < 3; ++x) a += kb[x] * r.b[x][c] + ko[x] * r.o[x][c];
+            a = sel0(m.sol[c], a);
+        } else {
+            a = ksb * r.sb[c];
+#pragma unroll
+            for (int x = 0; x < 3; ++x) a += kb[x] * r.b[x][c];
+        }
+        return a;
+    }
+    __device__ __forceinline__ void finish_row(const T (&a)[CPL], const T (&q)[CPL], T xp, const In& r, T* zr) {
+#pragma unroll
+        for (int c = 0; c < CPL; ++c) {
+            xp = a[c] + q[c] * xp;
+            xz[c] = xp;
+            zr[c] = xp;
+        }
+        if (ST) {
+            T t = FULL ? xz[0] : k.val[0] * xz[0];
+#pragma unroll
+            for (int c = 1; c < CPL; ++c) t = FULL ? t + xz[c] : t + k.val[c] * xz[c];
+            kt += (double)t;
+#pragma unroll
+            for (int c = 0; c < CPL; ++c) bst(xz[c], X, (uint32_t)r.si[c] * (uint32_t)sizeof(T));   // -1: out of range
+        }
+    }
+
+    // Rows are read two ahead in a rotation of three buffers and their masks
+    // one ahead, with no load and no store inside a branch; the y neighbours
+    // of the next row are read from LDS before this row's chain.
+    __device__ __forceinline__ void run() {
+#pragma unroll
+        for (int c = 0; c < CPL; ++c) xz[c] = T(0);
+        const int nrows = ny * nz;
+        In b0, b1, b2;
+        Pos pl{0, 0}, pc{0, 0};              // next row to load, row being solved
+        uint32_t g0 = grid_row(pl);
+        load(g0, b0);
+        next(pl);
+        uint32_t g1 = grid_row(pl);
+        load(g1, b1);
+        next(pl);
+        T py[CPL];
+#pragma unroll
+        for (int c = 0; c < CPL; ++c) py[c] = zl[c];
+        int r = 0;
+        // LDS row of the next solved row, read ahead; this row's address
+        auto advance = [&](T (&pn)[CPL]) -> T* {
+            T* zr = zl + pc.kk * ROW;
+            next(pc);
+            const T* zn = zl + pc.kk * ROW;
+#pragma unroll
+            for (int c = 0; c < CPL; ++c) pn[c] = zn[c];
+            return zr;
+        };
+        if constexpr (S1) {
+            const T rdv = k.rdv;
+            const T ky = (T)s.cd[1] * rdv, kz = (T)s.cd[2] * rdv, kk = s.sk * rdv, ksb = ADJ ? s.sdm * rdv : rdv;
+            const T kb[3] = {s.mb[0] * rdv, s.mb[1] * rdv, s.mb[2] * rdv};
+            const T ko[3] = {s.mo[0] * rdv, s.mo[1] * rdv, s.mo[2] * rdv};
+            Mask m;
+            masks(g0, m);
+            auto one = [&](const In& in, In& fill) {
+                Mask n;
+                masks(g1, n);
+                g1 = grid_row(pl);
+                load(g1, fill);
+                next(pl);
+                T pn[CPL];
+                T* zr = advance(pn);
+                T a[CPL], q[CPL];
+                T Al;
+#pragma unroll
+                for (int c = 0; c < CPL; ++c) {
+                    a[c] = ky * sel0(m.yo[c], py[c]) + kz * sel0(m.zo[c], xz[c]);
+                    if (WITH_B) a[c] += source(in, m, c, ksb, kb, ko, kk);
+                    q[c] = sel0(m.xo[c], FULL ? k.q : k.qc[FULL ? 0 : c]);
+                    Al = c == 0 ? a[c] : a[c] + q[c] * Al;
+                }
+                T A = Al;
+                const T om = ascan(A, k, m);
+                const T xin = readlane(A, WAVE - 1) * (lane_in(m.nb) ? k.rpt : T(1));
+                const T xe = A + om * xin;
+                finish_row(a, q, dpp<0x138, 0xf>(xe, xin), in, zr);      // wave_shr:1
+#pragma unroll
+                for (int c = 0; c < CPL; ++c) py[c] = pn[c];
+                m = n;
+            };
+            if (nrows >= 3) {
+                one(b0, b2);
+                one(b1, b0);
+                one(b2, b1);
+                for (r = 3; r + 3 <= nrows; r += 3) {
+                    one(b0, b2);
+                    one(b1, b0);
+                    one(b2, b1);
+                }
+            }
+            if (r < nrows) one(b0, b2);
+            if (r + 1 < nrows) one(b1, b0);
+        } else {
+            const T c0 = (T)s.cd[0], cr = (T)(s.cd[1] + s.cd[2]), cy = (T)s.cd[1], cz = (T)s.cd[2];
+            Mask m0, m1;
+            QPart<T, CPL> p0, p1;
+            masks(g0, m0);
+            masks(g1, m1);
+            {
+                T P = qpart_cells(c0, cr, k, m0, b0.sg, p0);
+                pscan(P, p0.t);
+                qpart_close<T, CPL>(P, p0);
+            }
+            auto one = [&](const In& in, const In& nxt, In& fill) {
+                const uint32_t gl = grid_row(pl);
+                load(gl, fill);
+                next(pl);
+                Mask n;
+                masks(gl, n);
+                T pn[CPL];
+                T* zr = advance(pn);
+                T Pn = qpart_cells(c0, cr, k, m1, nxt.sg, p1);
+                T a[CPL];
+                T Al;
+#pragma unroll
+                for (int c = 0; c < CPL; ++c) {
+                    a[c] = cy * sel0(m0.yo[c], py[c]) + cz * sel0(m0.zo[c], xz[c]);
+                    if (WITH_B) a[c] += source(in, m0, c, ADJ ? s.sdm : T(1), s.mb, s.mo, s.sk);
+                    a[c] *= p0.rdv[c];
+                    Al = c == 0 ? a[c] : a[c] + p0.q[c] * Al;
+                }
+                T A = Al;
+                scan_pair(A, p0.t, Pn, p1.t);
+                qpart_close<T, CPL>(Pn, p1);
+                const T xin = readlane(A, WAVE - 1) * p0.rPt;
+                const T xe = A + p0.omP * xin;
+                finish_row(a, p0.q, dpp<0x138, 0xf>(xe, xin), in, zr);
+#pragma unroll
+                for (int c = 0; c < CPL; ++c) py[c] = pn[c];
+                m0 = m1;
+                m1 = n;
+                p0 = p1;
+            };
+            if (nrows >= 3) {
+                one(b0, b1, b2);
+                one(b1, b2, b0);
+                one(b2, b0, b1);
+                for (r = 3; r + 3 <= nrows; r += 3) {
+                    one(b0, b1, b2);
+                    one(b1, b2, b0);
+                    one(b2, b0, b1);
+                }
+            }
+            if (r < nrows) one(b0, b1, b2);
+            if (r + 1 < nrows) one(b1, b2, b0);
+        }
+    }
+};
+
+// every element of the wrap plane this lane owns: plane kp, cell c, index i,
+// value z of the wave's LDS row
+#define PLOOP(body)                                            \
+    for (int kp = 0; kp < nz; ++kp)                            \
+        _Pragma("unroll") for (int c = 0; c < CPL; ++c) {      \
+            if (p0 + c >= 0) {                                 \
+                const int i = kp * nx + p0 + c;                \
+                [[maybe_unused]] T& z = zrows[kp * WAVE * CPL + lane * CPL + c]; \
+                body;                                          \
+            }                                                  \
         }
 
 template <typename T, int CPL, int ADJ, int SIG1, bool FULL>
@@ -467,35 +328,40 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(CPL ==
     // per-system quantity (and the buffer resources built from it) is too
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int m = item.m0 + w;
-    const int active = (w < item.nm) && (m < g.n_mfp);
+    // inactive waves leave: the waves of a group never wait for each other
+    if (!(w < item.nm && m < g.n_mfp)) return;
     constexpr int adj = ADJ;
-    const SysC<T> s = make_sys<T>(g, active ? m : item.m0, item.l, adj);
-    // the pass's sources and inflow tables, converted to the compute type by
-    // k_pack3 before the pass
-    const T* srcbase = static_cast<const T*>(g.qrec);
-    const T* bnd = srcbase + g.ncells;
+    const Sys3<T> s = make_sys3<T>(g, m, item.l, adj);
     const int nx = g.nx, nz = g.nz, nw = g.nwrap;
+    QConst<T, CPL, FULL> qk;
+    make_qconst<T, CPL, SIG1 != 0, FULL>(s.cd[0], s.cd[1] + s.cd[2], nx, lane, qk);
     const size_t half = adj ? (size_t)g.n_sys : 0;
     const gmut_t<T> U = gmut(reinterpret_cast<T*>(g.U) + (half + s.sys) * (size_t)nw);
-    const gmut_t<T> K = gmut(reinterpret_cast<T*>(g.kry) + (size_t)s.sys * KV_N * nw);
-    const gmut_t<T> xl = K + (size_t)KV_XL * nw;
-    const gmut_t<T> du = K + (size_t)KV_DU * nw;
-    // per-wave LDS: nz rows of this wave
+    const gmut_t<T> K = gmut(reinterpret_cast<T*>(g.kry) + (size_t)s.sys * KRY3_VECS * nw);
     T* zrows = reinterpret_cast<T*>(lds) + (size_t)w * nz * WAVE * CPL;
-    Red<T> rd = make_red<T>(g, s, active, pp);
-    // ---- phase A
-    {
-        GlobIO<T, CPL> io = make_gio<T, CPL>(U, xl, nx, nz, active);
-        if (g.grad_axis == 0)
-            sweep<T, CPL, true, true, true, false, SIG1 != 0, 0, FULL>(g, s, active, lane, adj, srcbase, bnd, io, &rd, zrows);
-        else
-            sweep<T, CPL, true, true, true, false, SIG1 != 0, 1, FULL>(g, s, active, lane, adj, srcbase, bnd, io, &rd, zrows);
-    }
-    long long n_it = 0, n_sw = 1;
-    int need = 0;
+    const rsrc_t X = make_rsrc(reinterpret_cast<T*>(g.X) + (size_t)s.sys * g.xs, (uint32_t)g.nsolid * (uint32_t)sizeof(T));
+    const int p0 = lane * CPL - (WAVE * CPL - nx);       // row position of this lane's first cell
+    // pairs across the wrap: the first y row's inflow along y
+    const mview_t mrow = (mview_t)(uni(g.qmask[0]) + (size_t)(s.neg[0] * g.ny * nz + (s.neg[1] ? g.ny - 1 : 0)) * row_mask_words3(CPL));
+    auto open = [&](int kp, int c) {
+        return lane_in(mrow[(size_t)(g.ny * (s.neg[2] ? nz - 1 - kp : kp)) * row_mask_words3(CPL) + 8 + (1 + s.neg[1]) * CPL + c]);
+    };
     const bool has_wrap = g.periodic[1] != 0;
-    if (pp.mode == 0 && active && has_wrap) {
-        const gmut_t<T> mk = K + (size_t)KV_MK * nw;
+    long long n_it = 0, n_sw = 0;
+    int need = 0;
+    double kt = 0.0;
+    for (int round = 0;; ++round) {
+        // ---- phase A
+        PLOOP(z = U[i]);
+        {
+            Sweep3<T, CPL, true, true, ADJ != 0, SIG1 != 0, FULL> a(g, s, qk, lane, zrows, X);
+            a.run();
+            kt = a.kt;
+        }
+        ++n_sw;
+        if (round > 0 || pp.mode != 0 || !has_wrap) break;
+        // ---- phase B: the residual of the wrap system (in units of the
+        // solution) and its correction
         const gmut_t<T> r = K + (size_t)KV_R * nw;
         const gmut_t<T> e = K + (size_t)KV_E * nw;
         const gmut_t<T> eb = K + (size_t)KV_EB * nw;
@@ -504,20 +370,11 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(CPL ==
         const gmut_t<T> v = K + (size_t)KV_V * nw;
         const gmut_t<T> sv = K + (size_t)KV_S * nw;
         const gmut_t<T> t = K + (size_t)KV_T * nw;
-        // wrap mask E' (c_y where the pair across the y-wrap is solid), the
-        // inflow produced by the sweep and the residual of the wrap system
-        const int iy = s.pos[1] ? 0 : g.ny - 1;
         double ss = 0.0, rr = 0.0;
         PLOOP({
-            const int ix = s.pos[0] ? p_ : nx - 1 - p_;
-            const int iz = s.pos[2] ? k : nz - 1 - k;
-            const uint32_t wv = g.fc[ix + nx * (iy + g.ny * iz)];
-            const T mv = (fc_solid(wv) && fc_class(wv, s.fin[1]) != FC_WALL) ? s.c[1] : T(0);
-            mk[i] = mv;
-            const T ez = mv * xl[i];
+            const T ez = open(kp, c) ? z : T(0);
             const T rv = ez - U[i];
             r[i] = rv;
-            du[i] = T(0);
             ss += (double)ez * (double)ez;
             rr += (double)rv * (double)rv;
         });
@@ -529,7 +386,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(CPL ==
         const double rho_g = wrap_gain_bound(g.fscal[5], s.cd[1], g.ny);
         if (rn > thr && scale > 0.0 && rho_g * rn <= fmin(thr, fmax(thr_final, RICH_MAX * rn))) {
             // weakly coupled wrap: e = r, no sweep (as in 2D)
-            PLOOP(du[i] = r[i]);
+            PLOOP(U[i] += r[i]);
             rn = rho_g * rn;
         } else if (rn > thr && scale > 0.0) {
             // BiCGSTAB on (I - G) e = r with the best iterate kept (as in 2D)
@@ -537,6 +394,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(CPL ==
             double best = rn;
             int restarts = 0;
             double rho_old = 1.0, alpha = 1.0, omega = 1.0;
+            Sweep3<T, CPL, false, false, ADJ != 0, SIG1 != 0, FULL> h(g, s, qk, lane, zrows, X);
             for (int iter = 0; iter < pp.max_inner; ++iter) {
                 double acc = 0.0;
                 PLOOP(acc += (double)rh[i] * (double)r[i]);
@@ -548,15 +406,12 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(CPL ==
                     rho_old = 1.0; alpha = 1.0; omega = 1.0;
                 }
                 const double beta = (rho / rho_old) * (alpha / omega);
-                PLOOP(p[i] = r[i] + (T)beta * (p[i] - (T)omega * v[i]));
-                {
-                    GlobIO<T, CPL> io = make_gio<T, CPL>(p, xl, nx, nz, 1);
-                    sweep<T, CPL, true, false, false, false, SIG1 != 0, -1, FULL>(g, s, active, lane, adj, srcbase, bnd, io, nullptr, zrows);
-                }
+                PLOOP({ z = r[i] + (T)beta * (p[i] - (T)omega * v[i]); p[i] = z; });
+                h.run();
                 ++n_sw;
                 acc = 0.0;
                 PLOOP({
-                    const T vv = p[i] - mk[i] * xl[i];
+                    const T vv = p[i] - (open(kp, c) ? z : T(0));
                     v[i] = vv;
                     acc += (double)rh[i] * (double)vv;
                 });
@@ -572,6 +427,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(CPL ==
                 PLOOP({
                     const T x = r[i] - (T)alpha * v[i];
                     sv[i] = x;
+                    z = x;
                     acc += (double)x * (double)x;
                 });
                 const double sn = sqrt(wave_sum(acc));
@@ -584,14 +440,11 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(CPL ==
                     }
                     break;
                 }
-                {
-                    GlobIO<T, CPL> io = make_gio<T, CPL>(sv, xl, nx, nz, 1);
-                    sweep<T, CPL, true, false, false, false, SIG1 != 0, -1, FULL>(g, s, active, lane, adj, srcbase, bnd, io, nullptr, zrows);
-                }
+                h.run();
                 ++n_sw;
                 double tt = 0.0, ts = 0.0;
                 PLOOP({
-                    const T x = sv[i] - mk[i] * xl[i];
+                    const T x = sv[i] - (open(kp, c) ? z : T(0));
                     t[i] = x;
                     tt += (double)x * (double)x;
                     ts += (double)x * (double)sv[i];
@@ -616,21 +469,38 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(CPL ==
                 if (rn <= thr) break;
             }
             rn = best;
-            PLOOP(du[i] += eb[i]);
+            PLOOP(U[i] += eb[i]);
         }
         if (lane == 0) g.wres[s.sys] = scale > 0.0 ? rn / scale : 0.0;
-        if (need) PLOOP(U[i] += du[i]);
+        // ---- the solution for the corrected inflow (skipped when the
+        // correction is lagged into the next pass)
+        if (pp.lag_wrap || !need) break;
     }
-    // ---- phase C (see the 2D kernel)
-    if (!pp.lag_wrap && need) {
-        GlobIO<T, CPL> io = make_gio<T, CPL>(du, nullptr, nx, nz, 0);
-        if (g.grad_axis == 0)
-            sweep<T, CPL, true, false, true, true, SIG1 != 0, 0, FULL>(g, s, active, lane, adj, srcbase, bnd, io, &rd, zrows);
-        else
-            sweep<T, CPL, true, false, true, true, SIG1 != 0, 1, FULL>(g, s, active, lane, adj, srcbase, bnd, io, &rd, zrows);
-        ++n_sw;
+    // kappa sums (see the 2D kernel)
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+    const bool ga0 = g.grad_axis == 0;
+    const bool pos = !(ga0 ? s.neg[0] : s.neg[1]);
+    const int np = g.n_plane[pos ? 1 : 0];
+    const int* plane = pos ? g.plane[1] : g.plane[0];
+    double kf = 0.0;
+    for (int i = lane; i < np; i += WAVE) kf += (double)bldT<T>(X, (uint32_t)plane[i] * (uint32_t)sizeof(T), 0u);
+    const double ks = wave_sum(kt);
+    kf = wave_sum(kf);
+    if (lane == 0) {
+        if (adj) {
+            g.ksys[s.sys] = kf * ((pos ? -1.0 : 1.0) * (ga0 ? s.cd[0] : s.cd[1]) * g.dT);
+            g.kfsys[s.sys] = 0.0;
+        } else {
+            if (pos) kf += g.dT * (double)np;
+            g.kraw[s.sys] = ks;
+            g.ksys[s.sys] = g.L[g.grad_axis] / (g.dT * (double)g.ncells) * s.Sg * ks;
+            g.kfsys[s.sys] = g.L[g.grad_axis] / (g.dT * (double)g.n_perp) * s.Sg * kf;
+        }
+        if (pp.mode == 0) {
+            g.iters[s.sys] += n_it;
+            g.sweeps[s.sys] += n_sw;
+        }
     }
-    finish_system(g, s, active, lane, adj, pp, rd, n_it, n_sw);
 }
 #undef PLOOP
 
