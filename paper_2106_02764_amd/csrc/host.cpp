@@ -91,7 +91,7 @@ struct obte_mesh {
     // device tables (library-owned)
     int device = -1;
     uint16_t* d_fc = nullptr;
-    std::vector<int> sidx, scell;   // solid index of each cell (-1 in pores), cell of each solid index
+    std::vector<int> sidx, scell;   // solid index of each cell (by y, z, x; -1 in pores), cell of each solid index
     int *d_sidx = nullptr, *d_scell = nullptr;
     int *d_wall_cell = nullptr, *d_wall_face = nullptr, *d_wall_idx = nullptr;
     double *d_mfp = nullptr, *d_dirs = nullptr, *d_D = nullptr, *d_S = nullptr, *d_wout = nullptr,
@@ -190,7 +190,7 @@ namespace {
 struct Layout {
     size_t sigma, sigma_f, sT, Tw, T_L, U, X, ksys, kfsys, iters, sweeps, hist, hist_face, ctrl, fx, fscal,
         Tstore, lam_psi, lam_phi, grad, bnd, wres, wres_hist, kry, ax, actl, ag,
-        axp, afp, adX, adF, agram, apart, kraw, qrec, total;
+        axp, afp, adX, adF, agram, apart, kraw, qtab, q_added, total;
 };
 
 // Linear interpolation weights of x on the sorted values v (clamped to the
@@ -355,6 +355,12 @@ size_t row_records(const obte_mesh* m, int o) {
 }
 size_t table_records(const obte_mesh* m, int o) { return row_records(m, o) * (o ? m->nx : m->ny); }
 
+// Records of slack before and behind the 2D row tables.
+size_t table_lead(const obte_mesh* m) { return ROW_SLACK * std::max(row_records(m, 0), row_records(m, 1)); }
+
+// Bytes of a 3D row's block: eight values and a store offset per cell.
+size_t row3_bytes(const obte_mesh* m, size_t tsz) { return ((size_t)m->nx * (8 * tsz + 4) + 15) / 16 * 16; }
+
 // words of one row's lane masks
 size_t mask_words(const obte_mesh* m) { return m->nz > 1 ? row_mask_words3(m->q_cpl) : row_mask_words(m->q_cpl); }
 
@@ -405,13 +411,19 @@ Layout make_layout(const obte_mesh* m, const obte_solve_opts* o, bool tr) {
     const size_t nsol = x_stride(m->nsolid);
     L.Tstore = o->keep_state ? take((size_t)m->n_sys * nsol * 8) : 0;
     L.X = take((size_t)m->n_sys * nsol * tsz);
-    // 2D: the pass inputs in the rows' order: per orientation and row
-    // direction six tables in the compute type, and the store offsets.  The
-    // region holds both orientations whether they are in use or not.
+    // the pass inputs in the rows' order (GeomDev::qtab, qoff).  2D: per
+    // orientation and row direction six tables in the compute type, held for
+    // both orientations whether they are in use or not; 3D: eight tables for
+    // either order of the planes.
     const size_t r0 = 2 * (nc + (size_t)m->ny * (m->q_cpl - 1)), r1 = 2 * (nc + (size_t)m->nx * (m->q_cpl - 1));
-    const size_t lead = ROW_SLACK * std::max(row_records(m, 0), row_records(m, 1));
-    L.qrec = m->nz == 1 ? take((r0 + (m->q_tr ? r1 : 0) + lead) * 6 * tsz + (r0 + nc + 2 * lead + 2 * OFF_SLACK) * 4)
-                        : take((1 + (size_t)m->nf) * nc * tsz);
+    const size_t lead = table_lead(m);
+    const size_t qbytes = m->nz == 1 ? (r0 + (m->q_tr ? r1 : 0) + lead) * 6 * tsz + (r0 + nc + 2 * lead + 2 * OFF_SLACK) * 4
+                                     : 2 * ((size_t)m->ny * m->nz + ROW_SLACK) * row3_bytes(m, tsz);
+    L.qtab = take(qbytes);
+    // what the pass inputs took when obte_solve_noalloc's limit was set
+    const size_t q0 = m->nz == 1 ? align256(16 * nc * tsz) + align256(16 * nc) + align256(4 * nc * tsz) + align256(8 * nc * tsz)
+                                 : align256(7 * nc * tsz);
+    L.q_added = align256(qbytes) > q0 ? align256(qbytes) - q0 : 0;
     // last: the mixing history (an adjoint may use another depth than the
     // forward solve whose stored state it reads)
     const size_t M = (size_t)std::max(o->accel, 0);
@@ -478,11 +490,13 @@ GeomDev make_view(const obte_mesh* m, char* ws, const Layout& L, int precision, 
         g.ax = (double*)(ws + L.ax);
         g.actl = (int*)(ws + L.actl);
         g.kraw = (double*)(ws + L.kraw);
-        g.qrec = ws + L.qrec;
-        if (m->nz == 1) {
-            const size_t tsz = precision == OBTE_FP32 ? 4 : 8, t0 = table_records(m, 0);
-            const size_t lead = ROW_SLACK * std::max(row_records(m, 0), row_records(m, 1));
-            char* q = ws + L.qrec + lead * tsz;
+        const size_t tsz = precision == OBTE_FP32 ? 4 : 8;
+        if (m->nz > 1) {
+            g.q_row3 = (uint32_t)row3_bytes(m, tsz);
+            g.qtab[0] = ws + L.qtab + ROW_SLACK * (size_t)g.q_row3;
+        } else {
+            const size_t t0 = table_records(m, 0), lead = table_lead(m);
+            char* q = ws + L.qtab + lead * tsz;
             g.qtab[0] = q;
             q += 12 * t0 * tsz;
             g.qtab[1] = tr ? q : nullptr;
@@ -723,6 +737,23 @@ bool dir_transposed(const obte_mesh* m, int l, bool tr) {
     return tr && transposed(&m->dirs3[3 * (size_t)l], m->L, m->periodic);
 }
 
+// Directions in the order their items are dispatched: the eight sweep
+// orientations in turn.  Workgroups go to the eight XCDs in turn, so each XCD
+// sweeps mostly one orientation, whose rows and masks stay in its L2 (3D
+// membrane: 1.3 of 4.7 MB of tables per orientation, 4 MB of L2 per XCD).
+std::vector<int> direction_order(const obte_mesh* m, bool tr) {
+    std::vector<int> by[8], out;
+    for (int l = 0; l < m->n_dir; ++l) {
+        const double* s = &m->dirs3[3 * (size_t)l];
+        const int third = m->nz > 1 ? (s[2] > 0.0 ? 0 : 4) : (dir_transposed(m, l, tr) ? 4 : 0);
+        by[(s[0] > 0.0 ? 0 : 1) + (s[1] > 0.0 ? 0 : 2) + third].push_back(l);
+    }
+    for (size_t k = 0; (int)out.size() < m->n_dir; ++k)
+        for (const auto& b : by)
+            if (k < b.size()) out.push_back(b[k]);
+    return out;
+}
+
 // Systems per workgroup of a mesh's items (W: the resolved value of its
 // class): FP64 kernels of 3 or 4 cells per lane take at most 4, and rows along
 // y as many as have their LDS tiles in 64 KiB.
@@ -766,8 +797,9 @@ obte_status build_run(Run& R, obte_mesh* const* meshes, int n, const obte_solve_
         // longest MFPs first: their systems take the most wrap iterations, so
         // the shorter ones dispatched after them fill in behind (a shorter
         // makespan than direction-major order; the results do not depend on it)
+        const std::vector<int> order = direction_order(m, tr);
         for (int end = m->n_mfp; end > 0; --end)
-            for (int l = 0; l < m->n_dir; ++l) {
+            for (int l : order) {
                 const int t = dir_transposed(m, l, tr) ? 1 : 0;
                 const int m0 = (end - 1) / w[t] * w[t];
                 if (std::min(m0 + w[t], m->n_mfp) != end) continue;
@@ -1106,7 +1138,7 @@ obte_status solve_impl(obte_mesh* const* meshes, int n, const obte_solve_opts* o
             HIPCHK(hipMemcpy(m->d_geom, &R.views[i], sizeof(GeomDev), hipMemcpyHostToDevice));
         m->host_view = R.views[i];
         HIPCHK(launch_prep_sigma(m->d_geom, m->ncells, sigma ? sigma[i] : nullptr, st));
-        if (m->nz == 1 && !o->only_fourier) HIPCHK(launch_pack_static(R.precision, m->d_geom, m->ncells, st));
+        if (!o->only_fourier) HIPCHK(launch_pack_static(R.precision, m->nz, m->d_geom, m->ncells, st));
         if (o->init == 0) {
             const size_t tsz = o->precision == OBTE_FP32 ? 4 : 8;
             HIPCHK(hipMemsetAsync(ws + L.U, 0, 2 * (size_t)m->n_sys * R.views[i].nwrap * tsz, st));
@@ -1348,8 +1380,7 @@ obte_status obte_mesh_create(const obte_mesh_desc* d, obte_mesh** out) {
     for (long long c = 0; c < nc; ++c) {
         if (d->solid[c] > 1) { delete m; return fail(OBTE_ERR_ARG, "solid mask entries must be 0/1"); }
         if (!d->solid[c]) continue;
-        m->sidx[c] = m->nsolid++;
-        m->scell.push_back((int)c);
+        ++m->nsolid;
         const int q0[3] = {(int)(c % m->nx), (int)((c / m->nx) % m->ny), (int)(c / ((long long)m->nx * m->ny))};
         uint16_t w = 1;
         for (int a = 0; a < d->ndim; ++a)
@@ -1378,6 +1409,19 @@ obte_status obte_mesh_create(const obte_mesh_desc* d, obte_mesh** out) {
             }
         m->fc[c] = w;
     }
+    // solid indices in the order a sweep stores its rows (y, then z, then x):
+    // a line that two rows share is written twice in a row and leaves the L2
+    // once (in cell order the next row of a line came nz rows later: the 3D
+    // membrane's pass wrote 2.5 GB for 1.6 GB of solutions)
+    m->scell.reserve(m->nsolid);
+    for (int iy = 0; iy < m->ny; ++iy)
+        for (int iz = 0; iz < m->nz; ++iz)
+            for (int ix = 0; ix < m->nx; ++ix) {
+                const int c = ix + m->nx * (iy + m->ny * iz);
+                if (!fc_solid(m->fc[c])) continue;
+                m->sidx[c] = (int)m->scell.size();
+                m->scell.push_back(c);
+            }
     m->nwalls = (int)m->wall_cell.size();
     // plane cells of the gradient axis: solid, at its low / high end, with the
     // face across the periodic plane open
@@ -1582,7 +1626,7 @@ obte_status obte_material_set(obte_mesh* m, const obte_material_desc* d) {
     for (int o = 0; o < (m->q_tr ? 2 : 1); ++o) {
         const size_t rows = o ? m->nx : (size_t)m->ny * m->nz;
         const size_t words = mask_words(m);
-        HIPCHK(hipMalloc((void**)&m->d_mask[o], (2 * rows + 2 * ROW_SLACK) * words * sizeof(unsigned long long)));
+        HIPCHK(hipMalloc((void**)&m->d_mask[o], ((m->nz > 1 ? 4 : 2) * rows + 2 * ROW_SLACK) * words * sizeof(unsigned long long)));
         HIPCHK(launch_row_masks(m->d_fc, m->nx, m->ny, m->nz, m->q_cpl, o, m->d_mask[o] + ROW_SLACK * words, nullptr));
     }
     HIPCHK(hipStreamSynchronize(nullptr));      // solves run on other streams
@@ -1651,10 +1695,11 @@ obte_status obte_solve(obte_mesh* m, const obte_solve_opts* o, const double* sig
 // ---------------------------------------------------------------------------
 namespace {
 constexpr size_t NOALLOC_BYTES = (size_t)32 << 20;
-// over the stated size: the slack rows of the pass inputs, so that they take
-// nothing from a workspace that just fits
-constexpr size_t NOALLOC_SLACK = (size_t)64 << 10;
-static __device__ __align__(256) unsigned char scratch[NOALLOC_BYTES + NOALLOC_SLACK];
+// over the stated size: what the row tables take beyond the pass inputs that
+// the limit was set with (Layout::q_added), so that every mesh it admits fits
+// (at most 76 of the 500 bytes or more that a cell takes)
+constexpr size_t NOALLOC_ROWS = (size_t)8 << 20;
+static __device__ __align__(256) unsigned char scratch[NOALLOC_BYTES + NOALLOC_ROWS];
 constexpr int NOALLOC_MAX_DEV = 64;
 std::mutex g_scratch_mu;
 void* g_scratch_ptr[NOALLOC_MAX_DEV] = {};
@@ -1697,18 +1742,20 @@ obte_status obte_solve_noalloc(obte_mesh* m, const obte_solve_opts* o, const dou
     size_t need = 0;
     bool tr = true;
     obte_status s = workspace_size(&m, 1, o, &need, true);
-    if (s == OBTE_OK && need > NOALLOC_BYTES + NOALLOC_SLACK) {
-        tr = false;
-        s = workspace_size(&m, 1, o, &need, false);
-    }
     if (s != OBTE_OK) return s;
-    if (need > NOALLOC_BYTES + NOALLOC_SLACK)
+    size_t added = make_layout(m, o, m->q_tr).q_added;
+    if (need - added > NOALLOC_BYTES || need > NOALLOC_BYTES + NOALLOC_ROWS) {
+        tr = false;
+        if ((s = workspace_size(&m, 1, o, &need, false)) != OBTE_OK) return s;
+        added = make_layout(m, o, false).q_added;
+    }
+    if (need - added > NOALLOC_BYTES || need > NOALLOC_BYTES + NOALLOC_ROWS)
         return fail(OBTE_ERR_NOMEM, "this solve needs %zu bytes of scratch; obte_solve_noalloc has %zu "
                                     "(use obte_solve with a caller workspace)", need, NOALLOC_BYTES);
     void* ws = nullptr;
     if ((s = scratch_on_current_device(&ws)) != OBTE_OK) return s;
     const double* sg[1] = {sigma_dev};
-    return solve_impl(&m, 1, o, sg, ws, NOALLOC_BYTES + NOALLOC_SLACK, stream, T_L_dev, J_dev, nullptr, stats, false, true, tr);
+    return solve_impl(&m, 1, o, sg, ws, NOALLOC_BYTES + NOALLOC_ROWS, stream, T_L_dev, J_dev, nullptr, stats, false, true, tr);
 }
 
 obte_status obte_solve_batch(obte_mesh* const* meshes, int n, const obte_solve_opts* o,
@@ -1788,7 +1835,7 @@ obte_status obte_adjoint(obte_mesh* m, const obte_solve_opts* o, const double* s
     HIPCHK(hipMemsetAsync(ws + L.ctrl, 0, CTRL_N * sizeof(int), st));
     HIPCHK(hipMemsetAsync(ws + L.ax, 0, ((size_t)m->ncells + m->nwalls) * 8, st));
     HIPCHK(hipMemsetAsync(ws + L.actl, 0, 8 * sizeof(int), st));
-    if (m->nz == 1) HIPCHK(launch_pack_static(R.precision, R.d_views, m->ncells, st));
+    HIPCHK(launch_pack_static(R.precision, m->nz, R.d_views, m->ncells, st));
     PassParams pp = base_params(o);
     pp.adjoint = 1;
     pp.sigma1 = sigma_dev ? 0 : 1;

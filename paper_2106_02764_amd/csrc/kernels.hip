@@ -1236,26 +1236,21 @@ __global__ void __launch_bounds__(256) k_pack_static(const GeomDev* __restrict__
     }
 }
 
-hipError_t launch_pack_static(int precision, const GeomDev* geom_dev, int ncells, hipStream_t st) {
-    int blocks = (4 * ncells + 255) / 256;
-    blocks = blocks < 1 ? 1 : (blocks > 1024 ? 1024 : blocks);
-    (void)hipGetLastError();
-    if (precision == 1) hipLaunchKernelGGL(k_pack_static<float>, dim3(blocks), dim3(256), 0, st, geom_dev);
-    else hipLaunchKernelGGL(k_pack_static<double>, dim3(blocks), dim3(256), 0, st, geom_dev);
-    return hipGetLastError();
-}
-
 // Lane masks of every sweep row (one wave per row direction and row; o: rows
-// along y): row_mask_words(cpl) words, [0..5] the lanes whose segment before
-// scan step k has no cell closed to its inflow along the row, [6] the lanes
-// reached from the row's start without one, [7] all ones when the row has
-// none, then per cell of a lane: inflow along the row open (set in the
-// padding), inflow through the '-' / '+' face across the rows (y in 3D) open,
-// 3D: through the '-' / '+' z face, solid.
+// along y; 3D: rows in the order y, z or y, reversed z): row_mask_words(cpl)
+// words, [0..5] the lanes whose segment before scan step k has no cell closed
+// to its inflow along the row, [6] the lanes reached from the row's start
+// without one, [7] all ones when the row has none, then per cell of a lane:
+// inflow along the row open (set in the padding); 2D: inflow through the '-'
+// face across the rows, the '+' face; 3D: through the '-' y face and the z
+// face of a sweep towards + y (in this table's z order), the '+' y face and
+// the other z face; solid.
 __global__ void __launch_bounds__(64) k_row_masks(const uint16_t* __restrict__ fc, int nx, int ny, int nz, int cpl, int o,
                                                   unsigned long long* __restrict__ out) {
-    const int nr = o ? ny : nx, nw = o ? nx : ny * nz, row = blockIdx.x % nw, negr = blockIdx.x / nw;
-    const int lane = threadIdx.x, pad = WAVE * cpl - nr, fr = 2 * o, fw = 2 - fr, d3 = nz > 1;
+    const int d3 = nz > 1, nr = o ? ny : nx, nw = o ? nx : ny * nz;
+    const int row = blockIdx.x % nw, tab = blockIdx.x / nw, negr = d3 ? tab >> 1 : tab, zrev = d3 ? tab & 1 : 0;
+    const int lane = threadIdx.x, pad = WAVE * cpl - nr, fr = 2 * o, fw = 2 - fr;
+    const int iz = d3 ? (zrev ? nz - 1 - row % nz : row % nz) : 0;
     unsigned long long* w = out + (size_t)blockIdx.x * (d3 ? row_mask_words3(cpl) : row_mask_words(cpl));
     bool ok = true;
     for (int c = 0; c < cpl; ++c) {
@@ -1263,14 +1258,20 @@ __global__ void __launch_bounds__(64) k_row_masks(const uint16_t* __restrict__ f
         bool xo = true, f[5] = {false, false, false, false, false};
         if (p >= 0) {
             const int pp = negr ? nr - 1 - p : p;
-            const uint16_t v = fc[o ? pp * nx + row : row * nx + pp];
+            const uint16_t v = fc[o ? pp * nx + row : (d3 ? row / nz + ny * iz : row) * nx + pp];
             const bool sol = fc_solid(v);
             xo = sol && fc_class(v, fr + negr) != FC_WALL;
-            f[0] = sol && fc_class(v, fw) != FC_WALL;
-            f[1] = sol && fc_class(v, fw + 1) != FC_WALL;
-            f[2] = d3 ? sol && fc_class(v, 4) != FC_WALL : sol;
-            f[3] = sol && fc_class(v, 5) != FC_WALL;
-            f[4] = sol;
+            const bool y0 = sol && fc_class(v, fw) != FC_WALL, y1 = sol && fc_class(v, fw + 1) != FC_WALL;
+            f[0] = y0;
+            if (d3) {
+                f[1] = sol && fc_class(v, 4 + zrev) != FC_WALL;
+                f[2] = y1;
+                f[3] = sol && fc_class(v, 5 - zrev) != FC_WALL;
+                f[4] = sol;
+            } else {
+                f[1] = y1;
+                f[2] = sol;
+            }
         }
         ok = ok && xo;
         const unsigned long long bx = __ballot(xo);
@@ -1302,7 +1303,7 @@ __global__ void __launch_bounds__(64) k_row_masks(const uint16_t* __restrict__ f
 hipError_t launch_row_masks(const uint16_t* fc, int nx, int ny, int nz, int cpl, int o, unsigned long long* out,
                             hipStream_t st) {
     (void)hipGetLastError();
-    hipLaunchKernelGGL(k_row_masks, dim3(2 * (o ? nx : ny * nz)), dim3(64), 0, st, fc, nx, ny, nz, cpl, o, out);
+    hipLaunchKernelGGL(k_row_masks, dim3((nz > 1 ? 4 : 2) * (o ? nx : ny * nz)), dim3(64), 0, st, fc, nx, ny, nz, cpl, o, out);
     return hipGetLastError();
 }
 
@@ -1325,24 +1326,73 @@ hipError_t launch_keep(int precision, const GeomDev* geom_dev, hipStream_t st) {
 
 // 3D: the pass's sources (sigma T_L, or sigma sum lambda in the adjoint) and
 // inflow tables, read from the buffers the pass's sweeps consume (the rule of
-// the pass kernel), in the compute type: qrec = [src | bnd face 0 | ... ].
+// the pass kernel), in the compute type and in sweep order: rows by y, z and
+// by y, reversed z; a row's block of q_row3 bytes holds nx each of the
+// sources, the boundary values of faces 0 to 5 and sigma, then nx store
+// offsets.
+struct Rec3 {
+    char* row;
+    int cell, x;
+};
+__device__ __forceinline__ Rec3 rec3(const GeomDev& g, int i) {
+    const int zrev = i >= g.ncells, e = zrev ? i - g.ncells : i;
+    const int row = e / g.nx, iy = row / g.nz, k = row - iy * g.nz;
+    Rec3 r;
+    r.x = e - row * g.nx;
+    r.cell = r.x + g.nx * (iy + g.ny * (zrev ? g.nz - 1 - k : k));
+    r.row = static_cast<char*>(g.qtab[0]) + ((size_t)zrev * g.ny * g.nz + row) * g.q_row3;
+    return r;
+}
+
 template <typename T>
 __global__ void __launch_bounds__(256) k_pack3(const GeomDev* __restrict__ geoms, PassParams pp) {
     const GeomDev& g = geoms[blockIdx.y];
     if (pp.mode == 0 && g.ctrl[CTRL_DONE]) return;
     const int pass = g.ctrl[CTRL_PASS];
     const int buf = (pp.mode == 1) ? ((pass + 1) & 1) : (pass & 1);
-    const size_t nc = (size_t)g.ncells, nb = (size_t)g.nf * nc;
+    const int nc = g.ncells;
     const double* src = (pp.adjoint ? g.lam_psi : g.sT) + (size_t)buf * nc;
-    const double* bnd = g.bnd + ((size_t)(pp.adjoint ? 2 : 0) + buf) * nb;
-    T* out = static_cast<T*>(g.qrec);
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < nc + nb; i += (size_t)gridDim.x * blockDim.x)
-        out[i] = (T)(i < nc ? src[i] : bnd[i - nc]);
+    const double* bnd = g.bnd + ((size_t)(pp.adjoint ? 2 : 0) + buf) * 6 * nc;
+    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < 2 * nc; i += gridDim.x * blockDim.x) {
+        const Rec3 r = rec3(g, i);
+        T* t = reinterpret_cast<T*>(r.row) + r.x;
+        t[0] = (T)src[r.cell];
+#pragma unroll
+        for (int f = 0; f < 6; ++f) t[(1 + f) * g.nx] = (T)bnd[(size_t)f * nc + r.cell];
+    }
+}
+
+// What stays the same over a solve's passes: sigma and the store offsets.
+template <typename T>
+__global__ void __launch_bounds__(256) k_pack3_static(const GeomDev* __restrict__ gp) {
+    const GeomDev& g = *gp;
+    const T* sig = sigma_ptr<T>(g);
+    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < 2 * g.ncells; i += gridDim.x * blockDim.x) {
+        const Rec3 r = rec3(g, i);
+        T* t = reinterpret_cast<T*>(r.row);
+        t[7 * g.nx + r.x] = sig[r.cell];
+        const int si = g.sidx[r.cell];
+        reinterpret_cast<uint32_t*>(t + 8 * g.nx)[r.x] = si >= 0 ? (uint32_t)si * (uint32_t)sizeof(T) : QOFF_NONE;
+    }
+}
+
+hipError_t launch_pack_static(int precision, int nz, const GeomDev* geom_dev, int ncells, hipStream_t st) {
+    int blocks = (4 * ncells + 255) / 256;
+    blocks = blocks < 1 ? 1 : (blocks > 1024 ? 1024 : blocks);
+    (void)hipGetLastError();
+    if (nz > 1) {
+        if (precision == 1) hipLaunchKernelGGL(k_pack3_static<float>, dim3(blocks), dim3(256), 0, st, geom_dev);
+        else hipLaunchKernelGGL(k_pack3_static<double>, dim3(blocks), dim3(256), 0, st, geom_dev);
+    } else {
+        if (precision == 1) hipLaunchKernelGGL(k_pack_static<float>, dim3(blocks), dim3(256), 0, st, geom_dev);
+        else hipLaunchKernelGGL(k_pack_static<double>, dim3(blocks), dim3(256), 0, st, geom_dev);
+    }
+    return hipGetLastError();
 }
 
 hipError_t launch_pack3(int precision, const GeomDev* geoms_dev, int n_geoms, int max_cells, PassParams pp,
                         hipStream_t st) {
-    int blocks = (7 * max_cells + 255) / 256;
+    int blocks = (2 * max_cells + 255) / 256;
     blocks = blocks < 1 ? 1 : (blocks > 1024 ? 1024 : blocks);
     (void)hipGetLastError();
     if (precision == 1) hipLaunchKernelGGL(k_pack3<float>, dim3(blocks, n_geoms), dim3(256), 0, st, geoms_dev, pp);

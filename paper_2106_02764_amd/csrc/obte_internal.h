@@ -33,7 +33,7 @@ struct GeomDev {
     int n_perp;                  // ncells / n[grad_axis]
     // ---- static tables
     const uint16_t* fc;          // ncells
-    const int* sidx;             // ncells: solid index of the cell (cells in order), -1 in pores
+    const int* sidx;             // ncells: solid index of the cell (cells by y, z, x), -1 in pores
     const int* scell;            // nsolid: cell of each solid index
     const int* wall_cell;        // nwalls
     const int* wall_face;        // nwalls: face index 2a+side of the owning cell
@@ -95,18 +95,20 @@ struct GeomDev {
     // x / along y) and row direction negr: tables of rows * q_rs[o] records,
     // negr * 6 + {0 sources, 1 boundary value of the row's inflow face, 2 and 3
     // of the '-' and '+' face across the rows, 4 (adjoint) of the row's
-    // outflow face, 5 sigma}, in the compute type
+    // outflow face, 5 sigma}, in the compute type.  3D: qtab[0] holds, for
+    // rows in the order y, z and y, reversed z, a block of q_row3 bytes per
+    // row: nx each of the sources, the boundary values of the six faces,
+    // sigma, and the store offsets; qmask likewise
     void* qtab[2];
     int q_cpl;                   // cells per lane of this mesh's 2D rows
     int q_tr;                    // 1: directions may take rows along y
+    uint32_t q_row3;
     int q_rs[2];                 // records per row: the row's cells rounded up to q_cpl
     uint32_t* qoff;              // rows along x, per negr: byte offset of the cell's stored value, QOFF_NONE in pores
     uint32_t* qoffc;             // the same by cell
     const unsigned long long* qmask[2];   // lane masks of the rows (k_row_masks; 3D: the first)
     const int* plane[2];         // solid indices of the open plane cells at the low / high end of the gradient axis
     int n_plane[2];
-    void* qrec;                  // 3D: the pass's sources (ncells) and inflow tables (nf * ncells) in the
-                                 // compute type
 };
 
 // Store offset of a pore cell: past any stored array, also when doubled for
@@ -184,14 +186,13 @@ hipError_t launch_sweep_queue(int precision, const GeomDev* geoms_dev, const Ite
 // queue (the persistent launch's item counter) is set to 0.
 hipError_t launch_pack_rows(int precision, const GeomDev* geoms_dev, int n_geoms, int max_cells, PassParams pp,
                             hipStream_t st, int* queue);
-// 2D: sigma and the store offsets in the rows' order (once per solve).  The
-// rows' lane masks (once per mesh; nz > 1: the 3D form), the FP64 copy of a
-// replayed pass.
-hipError_t launch_pack_static(int precision, const GeomDev* geom_dev, int ncells, hipStream_t st);
+// sigma and the store offsets in the rows' order (once per solve), the
+// rows' lane masks (once per mesh), the FP64 copy of a replayed pass.
+hipError_t launch_pack_static(int precision, int nz, const GeomDev* geom_dev, int ncells, hipStream_t st);
 hipError_t launch_row_masks(const uint16_t* fc, int nx, int ny, int nz, int cpl, int o, unsigned long long* out,
                             hipStream_t st);
 hipError_t launch_keep(int precision, const GeomDev* geom_dev, hipStream_t st);
-// 3D: the pass's sources and inflow tables in the compute type (GeomDev::qrec).
+// 3D: the pass's sources and inflow tables in the rows' order (GeomDev::qtab).
 hipError_t launch_pack3(int precision, const GeomDev* geoms_dev, int n_geoms, int max_cells, PassParams pp,
                         hipStream_t st);
 hipError_t launch_reduce_pass(int precision, const GeomDev* geoms_dev, int n_geoms, int max_solid,

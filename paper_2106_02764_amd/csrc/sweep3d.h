@@ -7,12 +7,14 @@
 // per-system slab of the workspace (KRY3_VECS planes), where every element is
 // read and written only by the lane owning its column.
 //
-// Bound: vector issue (5 waves per SIMD keep it busy).  With the row's face
-// classes as lane masks, constant scan weights (rows.h) and one running row
-// index, a row of 64 FP32 cells takes 36 vector and 30 scalar instructions
-// where decoding the face words per system and scanning Q along took 79 and
-// 53 (64 x 64 x 16 membrane, 288 directions x 30 MFPs: 1.64 -> 0.86 ms a
-// launch on average).
+// Bound: instruction issue.  With the row's face classes as lane masks and
+// constant scan weights (rows.h) a row of 64 FP32 cells takes 33 vector
+// instructions where decoding the face words per system and scanning Q along
+// took 79; and with the pass inputs laid out in the order the rows are swept
+// (two copies, one with the planes reversed: then the eight octants walk one
+// of them forwards or backwards) its scalar work is a few running offsets
+// (53 -> 33 -> @S@).  64 x 64 x 16 membrane, 288 directions x 30 MFPs, FP32:
+// 1.97 -> 1.63 -> @T@ ms a launch.
 #pragma once
 #include "rows.h"
 
@@ -72,74 +74,74 @@ struct Sweep3 {
     const int lane, nx, ny, nz;
     T* const zl;             // this lane's cells in the wave's LDS rows: plane p at zl + p * ROW
     const rsrc_t X;
-    rsrc_t src, b[3], o[3], sg, sidx;
-    uint32_t oc[CPL];        // this lane's cells within a row (OOB in the padding)
+    // byte offsets of this lane's cells in a row's block (OOB in the padding):
+    // sources, inflow (and outflow) boundary values, sigma, store offset
+    uint32_t vs[CPL], vb[3][CPL], vo[3][CPL], vg[CPL], vf[CPL];
+    // next row to load (reads run up to two rows past either end of the
+    // table, into the slack kept there), its masks
+    const char* row;
+    long rstep;
+    uint32_t rbytes;
     mview_t mask;
+    int mstep;
     double kt;
     T xz[CPL];               // the row below in z
 
     struct In {
         T sb[CPL], b[3][CPL], o[3][CPL], sg[CPL];
-        int si[CPL];
-    };
-    // rows in sweep order: plane within y row, and the grid row iy + ny iz
-    struct Pos {
-        int j, kk;
+        uint32_t so[CPL];
     };
 
     __device__ __forceinline__ Sweep3(const GeomDev& g, const Sys3<T>& s_, const QConst<T, CPL, FULL>& k_, int lane_, T* zrows,
                                       rsrc_t X_)
         : s(s_), k(k_), lane(lane_), nx(uni(g.nx)), ny(uni(g.ny)), nz(uni(g.nz)), zl(zrows + lane_ * CPL), X(X_) {
-        const uint32_t nc = (uint32_t)g.ncells, tb = nc * (uint32_t)sizeof(T);
-        const T* base = static_cast<const T*>(g.qrec);
-        src = make_rsrc(base, tb);
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            b[a] = make_rsrc(base + (size_t)(1 + 2 * a + s.neg[a]) * nc, tb);
-            if (ADJB) o[a] = make_rsrc(base + (size_t)(2 + 2 * a - s.neg[a]) * nc, tb);
-        }
-        if (!S1) sg = make_rsrc(sigma_ptr<T>(g), tb);
-        sidx = make_rsrc(g.sidx, nc * 4u);
+        const int zrev = s.neg[1] != s.neg[2], nrows = ny * nz, first = s.neg[1] ? nrows - 1 : 0;
+        rbytes = uni(g.q_row3);
 #pragma unroll
         for (int c = 0; c < CPL; ++c) {
             const int p = lane * CPL + c - (WAVE * CPL - nx);
-            oc[c] = p >= 0 ? (uint32_t)(s.neg[0] ? nx - 1 - p : p) : BUF_OOB / 8u;
+            const int cell = s.neg[0] ? nx - 1 - p : p;
+            auto at = [&](int field) { return p >= 0 ? (uint32_t)(field * nx + cell) * (uint32_t)sizeof(T) : BUF_OOB; };
+            vs[c] = at(0);
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                vb[a][c] = at(1 + 2 * a + s.neg[a]);
+                vo[a][c] = at(2 + 2 * a - s.neg[a]);
+            }
+            vg[c] = at(7);
+            vf[c] = p >= 0 ? (uint32_t)(8 * nx) * (uint32_t)sizeof(T) + (uint32_t)cell * 4u : BUF_OOB;
         }
-        mask = (mview_t)(uni(g.qmask[0]) + (size_t)s.neg[0] * ny * nz * row_mask_words3(CPL));
+        row = uni(static_cast<const char*>(g.qtab[0]) + ((size_t)zrev * nrows + first) * rbytes);
+        rstep = s.neg[1] ? -(long)rbytes : (long)rbytes;
+        constexpr int ms = row_mask_words3(CPL);
+        mask = (mview_t)(uni(g.qmask[0]) + (size_t)((s.neg[0] * 2 + zrev) * nrows + first) * ms);
+        mstep = s.neg[1] ? -ms : ms;
         kt = 0.0;
     }
 
-    __device__ __forceinline__ uint32_t grid_row(const Pos& p) const {
-        return uni((uint32_t)((s.neg[1] ? ny - 1 - p.j : p.j) + ny * (s.neg[2] ? nz - 1 - p.kk : p.kk)));
-    }
-    // the next row (past the last: within the last y row, unused)
-    __device__ __forceinline__ void next(Pos& p) const {
-        const bool end = p.kk + 1 == nz;
-        p.kk = uni(end ? 0 : p.kk + 1);
-        p.j = uni(end ? min(p.j + 1, ny - 1) : p.j);
-    }
-    __device__ __forceinline__ void load(uint32_t row, In& r) const {
-        const uint32_t k0 = uni(row * (uint32_t)nx), oT = k0 * (uint32_t)sizeof(T);
+    __device__ __forceinline__ void load(In& r) {
+        const rsrc_t q = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(row), 0, (int)rbytes, 0x00020000);
 #pragma unroll
         for (int c = 0; c < CPL; ++c) {
-            const uint32_t v = oc[c] * (uint32_t)sizeof(T);
             if (WITH_B) {
-                r.sb[c] = bldT<T>(src, v, oT);
+                r.sb[c] = bldT<T>(q, vs[c], 0u);
 #pragma unroll
                 for (int a = 0; a < 3; ++a) {
-                    r.b[a][c] = bldT<T>(b[a], v, oT);
-                    if (ADJB) r.o[a][c] = bldT<T>(o[a], v, oT);
+                    r.b[a][c] = bldT<T>(q, vb[a][c], 0u);
+                    if (ADJB) r.o[a][c] = bldT<T>(q, vo[a][c], 0u);
                 }
             }
-            if (!S1) r.sg[c] = bldT<T>(sg, v, oT);
+            if (!S1) r.sg[c] = bldT<T>(q, vg[c], 0u);
             if (ST) {
-                r.si[c] = (int)bld32(sidx, oc[c] * 4u, k0 * 4u);
-                if (!FULL) r.si[c] = oc[c] == BUF_OOB / 8u ? -1 : r.si[c];
+                r.so[c] = bld32(q, vf[c], 0u);
+                if (!FULL) r.so[c] |= vf[c] & BUF_OOB;
             }
         }
+        row += rstep;
     }
-    __device__ __forceinline__ void masks(uint32_t row, Mask& m) const {
-        load_mask(mask + (size_t)row * row_mask_words3(CPL), s.neg[1], s.neg[2], m);
+    __device__ __forceinline__ void masks(Mask& m) {
+        load_mask(mask, s.neg[1], m);
+        mask += mstep;
     }
     __device__ __forceinline__ T source(const In& r, const Mask& m, int c, T ksb, const T (&kb)[3], const T (&ko)[3], T kk) const {
         T a;
@@ -168,7 +170,7 @@ struct Sweep3 {
             for (int c = 1; c < CPL; ++c) t = FULL ? t + xz[c] : t + k.val[c] * xz[c];
             kt += (double)t;
 #pragma unroll
-            for (int c = 0; c < CPL; ++c) bst(xz[c], X, (uint32_t)r.si[c] * (uint32_t)sizeof(T));   // -1: out of range
+            for (int c = 0; c < CPL; ++c) bst(xz[c], X, r.so[c]);
         }
     }
 
@@ -179,23 +181,20 @@ struct Sweep3 {
 #pragma unroll
         for (int c = 0; c < CPL; ++c) xz[c] = T(0);
         const int nrows = ny * nz;
+        const char* const row0 = row;
+        const mview_t mask0 = mask;
         In b0, b1, b2;
-        Pos pl{0, 0}, pc{0, 0};              // next row to load, row being solved
-        uint32_t g0 = grid_row(pl);
-        load(g0, b0);
-        next(pl);
-        uint32_t g1 = grid_row(pl);
-        load(g1, b1);
-        next(pl);
+        load(b0);
+        load(b1);
         T py[CPL];
 #pragma unroll
         for (int c = 0; c < CPL; ++c) py[c] = zl[c];
-        int r = 0;
+        int r = 0, pc = 0;
         // LDS row of the next solved row, read ahead; this row's address
         auto advance = [&](T (&pn)[CPL]) -> T* {
-            T* zr = zl + pc.kk * ROW;
-            next(pc);
-            const T* zn = zl + pc.kk * ROW;
+            T* zr = zl + pc;
+            pc = pc + ROW == nz * ROW ? 0 : pc + ROW;
+            const T* zn = zl + pc;
 #pragma unroll
             for (int c = 0; c < CPL; ++c) pn[c] = zn[c];
             return zr;
@@ -206,13 +205,11 @@ struct Sweep3 {
             const T kb[3] = {s.mb[0] * rdv, s.mb[1] * rdv, s.mb[2] * rdv};
             const T ko[3] = {s.mo[0] * rdv, s.mo[1] * rdv, s.mo[2] * rdv};
             Mask m;
-            masks(g0, m);
+            masks(m);
             auto one = [&](const In& in, In& fill) {
                 Mask n;
-                masks(g1, n);
-                g1 = grid_row(pl);
-                load(g1, fill);
-                next(pl);
+                masks(n);
+                load(fill);
                 T pn[CPL];
                 T* zr = advance(pn);
                 T a[CPL], q[CPL];
@@ -249,19 +246,17 @@ struct Sweep3 {
             const T c0 = (T)s.cd[0], cr = (T)(s.cd[1] + s.cd[2]), cy = (T)s.cd[1], cz = (T)s.cd[2];
             Mask m0, m1;
             QPart<T, CPL> p0, p1;
-            masks(g0, m0);
-            masks(g1, m1);
+            masks(m0);
+            masks(m1);
             {
                 T P = qpart_cells(c0, cr, k, m0, b0.sg, p0);
                 pscan(P, p0.t);
                 qpart_close<T, CPL>(P, p0);
             }
             auto one = [&](const In& in, const In& nxt, In& fill) {
-                const uint32_t gl = grid_row(pl);
-                load(gl, fill);
-                next(pl);
+                load(fill);
                 Mask n;
-                masks(gl, n);
+                masks(n);
                 T pn[CPL];
                 T* zr = advance(pn);
                 T Pn = qpart_cells(c0, cr, k, m1, nxt.sg, p1);
@@ -299,6 +294,8 @@ struct Sweep3 {
             if (r < nrows) one(b0, b1, b2);
             if (r + 1 < nrows) one(b1, b2, b0);
         }
+        row = row0;              // the wrap solve runs its sweeps from one view
+        mask = mask0;
     }
 };
 
@@ -341,11 +338,12 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(CPL ==
     T* zrows = reinterpret_cast<T*>(lds) + (size_t)w * nz * WAVE * CPL;
     const rsrc_t X = make_rsrc(reinterpret_cast<T*>(g.X) + (size_t)s.sys * g.xs, (uint32_t)g.nsolid * (uint32_t)sizeof(T));
     const int p0 = lane * CPL - (WAVE * CPL - nx);       // row position of this lane's first cell
-    // pairs across the wrap: the first y row's inflow along y
-    const mview_t mrow = (mview_t)(uni(g.qmask[0]) + (size_t)(s.neg[0] * g.ny * nz + (s.neg[1] ? g.ny - 1 : 0)) * row_mask_words3(CPL));
-    auto open = [&](int kp, int c) {
-        return lane_in(mrow[(size_t)(g.ny * (s.neg[2] ? nz - 1 - kp : kp)) * row_mask_words3(CPL) + 8 + (1 + s.neg[1]) * CPL + c]);
-    };
+    // pairs across the wrap: the first y row's inflow along y (its nz rows are
+    // the first swept)
+    const int mstep = s.neg[1] ? -row_mask_words3(CPL) : row_mask_words3(CPL);
+    const mview_t mrow = (mview_t)(uni(g.qmask[0]) + (size_t)((s.neg[0] * 2 + (s.neg[1] != s.neg[2])) * g.ny * nz +
+                                                              (s.neg[1] ? g.ny * nz - 1 : 0)) * row_mask_words3(CPL));
+    auto open = [&](int kp, int c) { return lane_in(mrow[(long)kp * mstep + 8 + (1 + 2 * s.neg[1]) * CPL + c]); };
     const bool has_wrap = g.periodic[1] != 0;
     long long n_it = 0, n_sw = 0;
     int need = 0;
@@ -379,7 +377,8 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(CPL ==
             rr += (double)rv * (double)rv;
         });
         const double scale = sqrt(wave_sum(ss));
-        double rn = sqrt(wave_sum(rr));
+        rr = wave_sum(rr);
+        double rn = sqrt(rr);
         const double thr = fmax(pp.inner_tol * scale, pp.inner_rtol * rn);
         const double thr_final = pp.inner_tol * scale;
         if (rn > thr_final && scale > 0.0) need = 1;
@@ -389,56 +388,102 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(CPL ==
             PLOOP(U[i] += r[i]);
             rn = rho_g * rn;
         } else if (rn > thr && scale > 0.0) {
-            // BiCGSTAB on (I - G) e = r with the best iterate kept (as in 2D)
-            PLOOP({ e[i] = T(0); eb[i] = T(0); rh[i] = r[i]; p[i] = T(0); v[i] = T(0); });
+            // BiCGSTAB on (I - G) e = r with the best iterate kept (as in 2D).
+            // Most systems are done after the first sweep (p = r, e = alpha
+            // r): until then only r is in the slab, A p is taken from the
+            // sweep's last row in LDS, and the other vectors are written
+            // when the second half needs them.
             double best = rn;
             int restarts = 0;
             double rho_old = 1.0, alpha = 1.0, omega = 1.0;
+            bool done = false;
             Sweep3<T, CPL, false, false, ADJ != 0, SIG1 != 0, FULL> h(g, s, qk, lane, zrows, X);
             for (int iter = 0; iter < pp.max_inner; ++iter) {
-                double acc = 0.0;
-                PLOOP(acc += (double)rh[i] * (double)r[i]);
-                double rho = wave_sum(acc);
-                if (fabs(rho) <= 1e-30 * rn * rn || !(omega != 0.0)) {
-                    acc = 0.0;
-                    PLOOP({ rh[i] = r[i]; p[i] = T(0); v[i] = T(0); acc += (double)r[i] * (double)r[i]; });
+                const bool first = iter == 0;
+                double acc = 0.0, rho = rr;
+                if (first) {
+                    PLOOP(z = r[i]);
+                } else {
+                    PLOOP(acc += (double)rh[i] * (double)r[i]);
                     rho = wave_sum(acc);
-                    rho_old = 1.0; alpha = 1.0; omega = 1.0;
+                    if (fabs(rho) <= 1e-30 * rn * rn || !(omega != 0.0)) {
+                        acc = 0.0;
+                        PLOOP({ rh[i] = r[i]; p[i] = T(0); v[i] = T(0); acc += (double)r[i] * (double)r[i]; });
+                        rho = wave_sum(acc);
+                        rho_old = 1.0; alpha = 1.0; omega = 1.0;
+                    }
+                    const double beta = (rho / rho_old) * (alpha / omega);
+                    PLOOP({ z = r[i] + (T)beta * (p[i] - (T)omega * v[i]); p[i] = z; });
                 }
-                const double beta = (rho / rho_old) * (alpha / omega);
-                PLOOP({ z = r[i] + (T)beta * (p[i] - (T)omega * v[i]); p[i] = z; });
                 h.run();
                 ++n_sw;
                 acc = 0.0;
-                PLOOP({
-                    const T vv = p[i] - (open(kp, c) ? z : T(0));
-                    v[i] = vv;
-                    acc += (double)rh[i] * (double)vv;
-                });
+                if (first) {
+                    PLOOP({
+                        const T x = r[i];
+                        acc += (double)x * (double)(x - (open(kp, c) ? z : T(0)));
+                    });
+                } else {
+                    PLOOP({
+                        const T vv = p[i] - (open(kp, c) ? z : T(0));
+                        v[i] = vv;
+                        acc += (double)rh[i] * (double)vv;
+                    });
+                }
                 const double rv = wave_sum(acc);
-                if (!isfinite(rv)) break;
+                if (!isfinite(rv)) {
+                    done = first;
+                    break;
+                }
                 if (!(fabs(rv) > 1e-30 * fabs(rho))) {
                     if (restarts++ >= 4) break;
                     omega = 0.0;
+                    if (first) PLOOP({ e[i] = T(0); eb[i] = T(0); rh[i] = r[i]; p[i] = T(0); v[i] = T(0); });
                     continue;
                 }
                 alpha = rho / rv;
                 acc = 0.0;
-                PLOOP({
-                    const T x = r[i] - (T)alpha * v[i];
-                    sv[i] = x;
-                    z = x;
-                    acc += (double)x * (double)x;
-                });
+                if (first) {
+                    PLOOP({
+                        const T x = r[i];
+                        const T y = x - (T)alpha * (x - (open(kp, c) ? z : T(0)));
+                        acc += (double)y * (double)y;
+                    });
+                } else {
+                    PLOOP({
+                        const T x = r[i] - (T)alpha * v[i];
+                        sv[i] = x;
+                        z = x;
+                        acc += (double)x * (double)x;
+                    });
+                }
                 const double sn = sqrt(wave_sum(acc));
                 ++n_it;
                 if (sn <= thr) {
-                    PLOOP(e[i] += (T)alpha * p[i]);
                     if (sn < best) {
                         best = sn;
-                        PLOOP(eb[i] = e[i]);
+                        if (first) {
+                            PLOOP(U[i] += (T)alpha * r[i]);
+                        } else {
+                            PLOOP(eb[i] = e[i] + (T)alpha * p[i]);
+                        }
                     }
+                    done = first;
                     break;
+                }
+                if (first) {
+                    PLOOP({
+                        const T x = r[i];
+                        const T vv = x - (open(kp, c) ? z : T(0));
+                        e[i] = T(0);
+                        eb[i] = T(0);
+                        rh[i] = x;
+                        p[i] = x;
+                        v[i] = vv;
+                        const T y = x - (T)alpha * vv;
+                        sv[i] = y;
+                        z = y;
+                    });
                 }
                 h.run();
                 ++n_sw;
@@ -469,7 +514,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(CPL ==
                 if (rn <= thr) break;
             }
             rn = best;
-            PLOOP(U[i] += eb[i]);
+            if (!done && n_sw > 1) PLOOP(U[i] += eb[i]);
         }
         if (lane == 0) g.wres[s.sys] = scale > 0.0 ? rn / scale : 0.0;
         // ---- the solution for the corrected inflow (skipped when the
