@@ -15,26 +15,64 @@ __device__ __forceinline__ T shfl_at(T v, int l) { return __shfl(v, l, WAVE); }
 template <typename T>
 __device__ __forceinline__ T shfl_xor(T v, int m) { return __shfl_xor(v, m, WAVE); }
 
-// Butterfly sum: every lane ends with the bitwise-same value.
-template <typename T>
-__device__ __forceinline__ T wave_sum(T v) {
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) v += shfl_xor(v, m);
-    return v;
+// ---------------------------------------------------------------------------
+// cross-lane primitives: DPP row shifts / row broadcasts / wave shift and
+// v_readlane.  `old` is what a lane receives when it has no source lane.
+// ---------------------------------------------------------------------------
+template <int CTRL, int RM>
+__device__ __forceinline__ float dpp(float v, float old) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(old), __float_as_int(v), CTRL, RM, 0xf, false));
+}
+template <int CTRL, int RM>
+__device__ __forceinline__ double dpp(double v, double old) {
+    const long long b = __double_as_longlong(v), o = __double_as_longlong(old);
+    const int lo = __builtin_amdgcn_update_dpp((int)o, (int)b, CTRL, RM, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp((int)(o >> 32), (int)(b >> 32), CTRL, RM, 0xf, false);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+__device__ __forceinline__ float readlane(float v, int l) {
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
+}
+__device__ __forceinline__ double readlane(double v, int l) {
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_readlane((int)b, l), hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 
-// N butterfly sums at once, step by step, so the cross-lane reads of the N
-// values are in flight together; each value is summed exactly as wave_sum does.
+// Sum over the wave, the same value in every lane.  The lanes are combined by
+// DPP row shifts and broadcasts (a step is two moves and an add, where the
+// LDS permutes of a butterfly cost their latency each: 0.15 against 0.35 us
+// for a double), in a fixed order.
+template <int CTRL, int RM, typename T>
+__device__ __forceinline__ void sum_step(T& v) { v += dpp<CTRL, RM>(v, T(0)); }
+template <typename T>
+__device__ __forceinline__ T wave_sum(T v) {
+    sum_step<0x111, 0xf>(v);   // row_shr:1
+    sum_step<0x112, 0xf>(v);   // row_shr:2
+    sum_step<0x114, 0xf>(v);   // row_shr:4
+    sum_step<0x118, 0xf>(v);   // row_shr:8
+    sum_step<0x142, 0xa>(v);   // row_bcast:15 into rows 1, 3
+    sum_step<0x143, 0xc>(v);   // row_bcast:31 into rows 2, 3
+    return readlane(v, WAVE - 1);
+}
+
+// N sums at once, step by step, so that their chains interleave; each value
+// is summed exactly as wave_sum does.
+template <int CTRL, int RM, int N>
+__device__ __forceinline__ void sum_step_n(double (&v)[N]) {
+#pragma unroll
+    for (int q = 0; q < N; ++q) sum_step<CTRL, RM>(v[q]);
+}
 template <int N>
 __device__ __forceinline__ void wave_sum_n(double (&v)[N]) {
+    sum_step_n<0x111, 0xf>(v);
+    sum_step_n<0x112, 0xf>(v);
+    sum_step_n<0x114, 0xf>(v);
+    sum_step_n<0x118, 0xf>(v);
+    sum_step_n<0x142, 0xa>(v);
+    sum_step_n<0x143, 0xc>(v);
 #pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) {
-        double t[N];
-#pragma unroll
-        for (int q = 0; q < N; ++q) t[q] = shfl_xor(v[q], m);
-#pragma unroll
-        for (int q = 0; q < N; ++q) v[q] += t[q];
-    }
+    for (int q = 0; q < N; ++q) v[q] = readlane(v[q], WAVE - 1);
 }
 
 // Deterministic block sum (blockDim.x multiple of 64, <= 1024).
@@ -151,30 +189,6 @@ template <>
 __device__ __forceinline__ const float* sigma_ptr<float>(const GeomDev& g) { return g.sigma_f; }
 
 
-// ---------------------------------------------------------------------------
-// cross-lane primitives: DPP row shifts / row broadcasts / wave shift and
-// v_readlane.  `old` is what a lane receives when it has no source lane.
-// ---------------------------------------------------------------------------
-template <int CTRL, int RM>
-__device__ __forceinline__ float dpp(float v, float old) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(old), __float_as_int(v), CTRL, RM, 0xf, false));
-}
-template <int CTRL, int RM>
-__device__ __forceinline__ double dpp(double v, double old) {
-    const long long b = __double_as_longlong(v), o = __double_as_longlong(old);
-    const int lo = __builtin_amdgcn_update_dpp((int)o, (int)b, CTRL, RM, 0xf, false);
-    const int hi = __builtin_amdgcn_update_dpp((int)(o >> 32), (int)(b >> 32), CTRL, RM, 0xf, false);
-    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-}
-__device__ __forceinline__ float readlane(float v, int l) {
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
-}
-__device__ __forceinline__ double readlane(double v, int l) {
-    const long long b = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_readlane((int)b, l), hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
-    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-}
-
 // Loads through these views compile to global (not flat) loads, which keep
 // only the vector-memory counter pending while the row computes.
 template <typename T>
@@ -214,6 +228,17 @@ __device__ __forceinline__ float bldT<float>(rsrc_t r, uint32_t vo, uint32_t so)
 template <>
 __device__ __forceinline__ double bldT<double>(rsrc_t r, uint32_t vo, uint32_t so) {
     return bld64(r, vo, so);
+}
+// the same past the caches
+__device__ __forceinline__ void bst_nt(float v, rsrc_t r, uint32_t vo) {
+    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), r, (int)vo, 0, 2);
+}
+__device__ __forceinline__ void bst_nt(double v, rsrc_t r, uint32_t vo) {
+    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+    u32x2_t w;
+    w.x = (unsigned int)b;
+    w.y = (unsigned int)(b >> 32);
+    __builtin_amdgcn_raw_buffer_store_b64(w, r, (int)vo, 0, 2);
 }
 __device__ __forceinline__ void bst(float v, rsrc_t r, uint32_t vo) {
     __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), r, (int)vo, 0, 0);

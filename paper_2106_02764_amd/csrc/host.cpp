@@ -1626,7 +1626,7 @@ obte_status obte_material_set(obte_mesh* m, const obte_material_desc* d) {
     for (int o = 0; o < (m->q_tr ? 2 : 1); ++o) {
         const size_t rows = o ? m->nx : (size_t)m->ny * m->nz;
         const size_t words = mask_words(m);
-        HIPCHK(hipMalloc((void**)&m->d_mask[o], ((m->nz > 1 ? 4 : 2) * rows + 2 * ROW_SLACK) * words * sizeof(unsigned long long)));
+        HIPCHK(hipMalloc((void**)&m->d_mask[o], ((m->nz > 1 ? 8 : 4) * rows + 2 * ROW_SLACK) * words * sizeof(unsigned long long)));
         HIPCHK(launch_row_masks(m->d_fc, m->nx, m->ny, m->nz, m->q_cpl, o, m->d_mask[o] + ROW_SLACK * words, nullptr));
     }
     HIPCHK(hipStreamSynchronize(nullptr));      // solves run on other streams

@@ -1236,49 +1236,43 @@ __global__ void __launch_bounds__(256) k_pack_static(const GeomDev* __restrict__
     }
 }
 
-// Lane masks of every sweep row (one wave per row direction and row; o: rows
-// along y; 3D: rows in the order y, z or y, reversed z): row_mask_words(cpl)
-// words, [0..5] the lanes whose segment before scan step k has no cell closed
-// to its inflow along the row, [6] the lanes reached from the row's start
-// without one, [7] all ones when the row has none, then per cell of a lane:
-// inflow along the row open (set in the padding); 2D: inflow through the '-'
-// face across the rows, the '+' face; 3D: through the '-' y face and the z
-// face of a sweep towards + y (in this table's z order), the '+' y face and
-// the other z face; solid.
+// Lane masks of every sweep row (one wave per sweep orientation and row; o:
+// rows along y; 2D: orientations by the directions along and across the rows;
+// 3D: by x, y and the order of the rows: y, z or y, reversed z, in which the
+// sweep then runs forwards or backwards): row_mask_words(cpl) words, [0..5]
+// the lanes whose segment before scan step k has no cell closed to its inflow
+// along the row, [6] the lanes reached from the row's start without one, [7]
+// all ones when the row has none, then per cell of a lane: inflow along the
+// row open (set in the padding), inflow across the rows open, 3D: inflow
+// through the z face open, solid.
 __global__ void __launch_bounds__(64) k_row_masks(const uint16_t* __restrict__ fc, int nx, int ny, int nz, int cpl, int o,
                                                   unsigned long long* __restrict__ out) {
     const int d3 = nz > 1, nr = o ? ny : nx, nw = o ? nx : ny * nz;
-    const int row = blockIdx.x % nw, tab = blockIdx.x / nw, negr = d3 ? tab >> 1 : tab, zrev = d3 ? tab & 1 : 0;
+    const int row = blockIdx.x % nw, tab = blockIdx.x / nw;
+    const int negr = d3 ? tab >> 2 : tab >> 1, negw = d3 ? (tab >> 1) & 1 : tab & 1, zrev = d3 ? tab & 1 : 0;
     const int lane = threadIdx.x, pad = WAVE * cpl - nr, fr = 2 * o, fw = 2 - fr;
     const int iz = d3 ? (zrev ? nz - 1 - row % nz : row % nz) : 0;
+    const int fz = 4 + (zrev ? 1 - negw : negw);       // '-' face of a sweep towards + z
     unsigned long long* w = out + (size_t)blockIdx.x * (d3 ? row_mask_words3(cpl) : row_mask_words(cpl));
     bool ok = true;
     for (int c = 0; c < cpl; ++c) {
         const int p = lane * cpl + c - pad;
-        bool xo = true, f[5] = {false, false, false, false, false};
+        bool xo = true, yo = false, zo = false, sol = false;
         if (p >= 0) {
             const int pp = negr ? nr - 1 - p : p;
             const uint16_t v = fc[o ? pp * nx + row : (d3 ? row / nz + ny * iz : row) * nx + pp];
-            const bool sol = fc_solid(v);
+            sol = fc_solid(v);
             xo = sol && fc_class(v, fr + negr) != FC_WALL;
-            const bool y0 = sol && fc_class(v, fw) != FC_WALL, y1 = sol && fc_class(v, fw + 1) != FC_WALL;
-            f[0] = y0;
-            if (d3) {
-                f[1] = sol && fc_class(v, 4 + zrev) != FC_WALL;
-                f[2] = y1;
-                f[3] = sol && fc_class(v, 5 - zrev) != FC_WALL;
-                f[4] = sol;
-            } else {
-                f[1] = y1;
-                f[2] = sol;
-            }
+            yo = sol && fc_class(v, fw + negw) != FC_WALL;
+            zo = sol && d3 && fc_class(v, fz) != FC_WALL;
         }
         ok = ok && xo;
-        const unsigned long long bx = __ballot(xo);
-        if (lane == 0) w[8 + c] = bx;
-        for (int q = 0; q < (d3 ? 5 : 3); ++q) {
-            const unsigned long long b = __ballot(f[q]);
-            if (lane == 0) w[8 + (1 + q) * cpl + c] = b;
+        const unsigned long long bx = __ballot(xo), by = __ballot(yo), bz = __ballot(zo), bs = __ballot(sol);
+        if (lane == 0) {
+            w[8 + c] = bx;
+            w[8 + cpl + c] = by;
+            if (d3) w[8 + 2 * cpl + c] = bz;
+            w[8 + (d3 ? 3 : 2) * cpl + c] = bs;
         }
     }
     const unsigned long long good = __ballot(ok);
@@ -1303,7 +1297,7 @@ __global__ void __launch_bounds__(64) k_row_masks(const uint16_t* __restrict__ f
 hipError_t launch_row_masks(const uint16_t* fc, int nx, int ny, int nz, int cpl, int o, unsigned long long* out,
                             hipStream_t st) {
     (void)hipGetLastError();
-    hipLaunchKernelGGL(k_row_masks, dim3((nz > 1 ? 4 : 2) * (o ? nx : ny * nz)), dim3(64), 0, st, fc, nx, ny, nz, cpl, o, out);
+    hipLaunchKernelGGL(k_row_masks, dim3((nz > 1 ? 8 : 4) * (o ? nx : ny * nz)), dim3(64), 0, st, fc, nx, ny, nz, cpl, o, out);
     return hipGetLastError();
 }
 

@@ -137,8 +137,8 @@ constexpr size_t tr_tile_bytes(int cpl) { return 64 * (64 * (size_t)cpl + 4); }
 // as many entries.
 constexpr int ROW_SLACK = 4, OFF_SLACK = 16;
 // words of one row's lane masks
-__host__ __device__ constexpr int row_mask_words(int cpl) { return 8 + 4 * cpl; }
-__host__ __device__ constexpr int row_mask_words3(int cpl) { return 8 + 6 * cpl; }
+__host__ __device__ constexpr int row_mask_words(int cpl) { return 8 + 3 * cpl; }
+__host__ __device__ constexpr int row_mask_words3(int cpl) { return 8 + 4 * cpl; }
 
 constexpr int AA_MAX = 8;
 

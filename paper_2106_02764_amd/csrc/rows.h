@@ -71,23 +71,25 @@ struct RowMask {
     mask_t brk[S1 ? 6 : 1], om, nb;
     mask_t xo[CPL], yo[CPL], zo[D3 ? CPL : 1], sol[ADJB ? CPL : 1];
 };
-// neg: the sweep runs towards - across the rows (3D: along y)
 template <int CPL, bool S1, bool ADJB, bool D3>
-__device__ __forceinline__ void load_mask(mview_t row, int neg, RowMask<CPL, S1, ADJB, D3>& m) {
+__device__ __forceinline__ void load_mask(mview_t row, RowMask<CPL, S1, ADJB, D3>& m) {
     if (S1) {
 #pragma unroll
         for (int k = 0; k < 6; ++k) m.brk[k] = row[k];
         m.om = row[6];
         m.nb = row[7];
     }
-    const mview_t in = row + 8 + CPL + neg * (D3 ? 2 : 1) * CPL;
 #pragma unroll
     for (int c = 0; c < CPL; ++c) {
         m.xo[c] = row[8 + c];
-        m.yo[c] = in[c];
-        if (D3) m.zo[c] = in[CPL + c];
-        if (ADJB) m.sol[c] = row[8 + (D3 ? 5 : 3) * CPL + c];
+        m.yo[c] = row[8 + CPL + c];
+        if (D3) m.zo[c] = row[8 + 2 * CPL + c];
+        if (ADJB) m.sol[c] = row[8 + (D3 ? 3 : 2) * CPL + c];
     }
+    // the loads stay here, a row ahead of their use (to save registers the
+    // scheduler would move them next to it; their latency is then in the
+    // chain): other instructions may cross, scalar loads may not
+    __builtin_amdgcn_sched_barrier(0x2 | 0x4 | 0x10 | 0x20 | 0x40 | 0x80 | 0x100 | 0x200);
 }
 
 // ---------------------------------------------------------------------------

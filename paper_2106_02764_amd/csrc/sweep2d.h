@@ -162,7 +162,7 @@ struct Sweep2 {
         v.sT = uni((uint32_t)(s.negw ? -s.rs : s.rs) * (uint32_t)sizeof(T));
         v.s4 = uni((uint32_t)(s.negw ? -s.rs : s.rs) * 4u);
         const int ms = row_mask_words(CPL);
-        v.mask = (mview_t)(uni(s.tr ? g.qmask[1] : g.qmask[0]) + (size_t)(s.negr * s.nw + first) * ms);
+        v.mask = (mview_t)(uni(s.tr ? g.qmask[1] : g.qmask[0]) + (size_t)((2 * s.negr + s.negw) * s.nw + first) * ms);
         v.mstep = s.negw ? -ms : ms;
         if (ST == 2) {
             v.j = lane % RB;
@@ -251,7 +251,7 @@ struct Sweep2 {
         if (ST == 2) load_flush(j, start, b.so);
     }
     __device__ __forceinline__ void masks(Mask& m) {
-        load_mask(v.mask, s.negw, m);
+        load_mask(v.mask, m);
         v.mask += v.mstep;
     }
 
@@ -468,7 +468,7 @@ __device__ __forceinline__ void pass_system(const GeomDev* __restrict__ geoms, c
         RowMask<CPL, false, false> m0;
         const int ms = row_mask_words(CPL);
         load_mask((mview_t)(uni(s.tr ? g.qmask[1] : g.qmask[0]) +
-                            (size_t)(s.negr * s.nw + (s.negw ? s.nw - 1 : 0)) * ms), s.negw, m0);
+                            (size_t)((2 * s.negr + s.negw) * s.nw + (s.negw ? s.nw - 1 : 0)) * ms), m0);
         VLOOP(mk[c] = lane_in(m0.yo[c]));
     }
     const bool has_wrap = g.periodic[s.tr ? 0 : 1] != 0;

@@ -7,14 +7,18 @@
 // per-system slab of the workspace (KRY3_VECS planes), where every element is
 // read and written only by the lane owning its column.
 //
-// Bound: instruction issue.  With the row's face classes as lane masks and
-// constant scan weights (rows.h) a row of 64 FP32 cells takes 33 vector
-// instructions where decoding the face words per system and scanning Q along
-// took 79; and with the pass inputs laid out in the order the rows are swept
-// (two copies, one with the planes reversed: then the eight octants walk one
-// of them forwards or backwards) its scalar work is a few running offsets
-// (53 -> 33 -> @S@).  64 x 64 x 16 membrane, 288 directions x 30 MFPs, FP32:
-// 1.97 -> 1.63 -> @T@ ms a launch.
+// Bound: instruction issue (5 waves per SIMD, about 1.1 instructions per four
+// cycles) and, in the first sweep, the store.  With the row's face classes as
+// lane masks and constant scan weights (rows.h) a row of 64 FP32 cells takes
+// 32 vector instructions where decoding the face words per system and scanning
+// Q along took 79.  The pass inputs are laid out in the order the rows are
+// swept (two copies, one with the planes reversed: the eight octants walk one
+// of them forwards or backwards; a row's values are one block behind one
+// advancing resource), so a row takes 15 scalar instructions where indexing it
+// took 53.  Solutions are stored past the caches (non-temporal: the tables
+// stay in the L2).  64 x 64 x 16 membrane, 288 directions x 30 MFPs, FP32:
+// 1.97 -> 1.39 ms a launch; the masks' scalar loads, one row ahead, still cost
+// about a sixth of it.
 #pragma once
 #include "rows.h"
 
@@ -114,7 +118,7 @@ struct Sweep3 {
         row = uni(static_cast<const char*>(g.qtab[0]) + ((size_t)zrev * nrows + first) * rbytes);
         rstep = s.neg[1] ? -(long)rbytes : (long)rbytes;
         constexpr int ms = row_mask_words3(CPL);
-        mask = (mview_t)(uni(g.qmask[0]) + (size_t)((s.neg[0] * 2 + zrev) * nrows + first) * ms);
+        mask = (mview_t)(uni(g.qmask[0]) + (size_t)((s.neg[0] * 4 + s.neg[1] * 2 + zrev) * nrows + first) * ms);
         mstep = s.neg[1] ? -ms : ms;
         kt = 0.0;
     }
@@ -140,7 +144,7 @@ struct Sweep3 {
         row += rstep;
     }
     __device__ __forceinline__ void masks(Mask& m) {
-        load_mask(mask, s.neg[1], m);
+        load_mask(mask, m);
         mask += mstep;
     }
     __device__ __forceinline__ T source(const In& r, const Mask& m, int c, T ksb, const T (&kb)[3], const T (&ko)[3], T kk) const {
@@ -170,7 +174,7 @@ struct Sweep3 {
             for (int c = 1; c < CPL; ++c) t = FULL ? t + xz[c] : t + k.val[c] * xz[c];
             kt += (double)t;
 #pragma unroll
-            for (int c = 0; c < CPL; ++c) bst(xz[c], X, r.so[c]);
+            for (int c = 0; c < CPL; ++c) bst_nt(xz[c], X, r.so[c]);
         }
     }
 
@@ -341,9 +345,9 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(CPL ==
     // pairs across the wrap: the first y row's inflow along y (its nz rows are
     // the first swept)
     const int mstep = s.neg[1] ? -row_mask_words3(CPL) : row_mask_words3(CPL);
-    const mview_t mrow = (mview_t)(uni(g.qmask[0]) + (size_t)((s.neg[0] * 2 + (s.neg[1] != s.neg[2])) * g.ny * nz +
+    const mview_t mrow = (mview_t)(uni(g.qmask[0]) + (size_t)((s.neg[0] * 4 + s.neg[1] * 2 + (s.neg[1] != s.neg[2])) * g.ny * nz +
                                                               (s.neg[1] ? g.ny * nz - 1 : 0)) * row_mask_words3(CPL));
-    auto open = [&](int kp, int c) { return lane_in(mrow[(long)kp * mstep + 8 + (1 + 2 * s.neg[1]) * CPL + c]); };
+    auto open = [&](int kp, int c) { return lane_in(mrow[(long)kp * mstep + 8 + CPL + c]); };
     const bool has_wrap = g.periodic[1] != 0;
     long long n_it = 0, n_sw = 0;
     int need = 0;

@@ -1,8 +1,9 @@
-"""The 2D sweep's two row orientations and its masked row scan, pass for pass
-against the oracle: rows that fill the wave exactly, rows padded by one to
+"""The 2D sweep's two row orientations, the 3D sweep's row order and the masked
+row scan, pass for pass against the oracle: rows that fill the wave exactly, rows padded by one to
 three cells, a few cells only, meshes where rows along y are wider or are not
 taken, pores on the boundary, both gradient axes, with and without a sigma
 field; and checkpoints written before rows along y existed."""
+import dataclasses
 import struct
 
 import numpy as np
@@ -49,6 +50,36 @@ def test_rows_lockstep(P, nx, ny, sigma):
     K = 4
     ref = source_iteration(prob, n_passes=K)
     Jref = np.zeros((w.n_cells, 2))
+    Jref[prob.mesh.cells] = ref["J"]
+    for prec, tol, bar in ((0, 1e-14, 1e-10), (1, 1e-6, 1e-4)):
+        r = gpu_solve(P, w, precision=prec, outer_tol=0.0, max_outer=K, inner_tol=tol, fourier_tol=1e-14,
+                      max_inner=400)
+        assert r["outer_iters"] == K
+        assert abs(r["kappa"] - ref["kappa_cc"]) <= bar * abs(ref["kappa_cc"]), prec
+        assert abs(r["kappa_face"] - ref["kappa_face"]) <= bar * abs(ref["kappa_face"]), prec
+        assert rel(r["T_L"], oracle_full(prob, ref["T_L"])) < bar, prec
+        assert rel(r["J"], Jref) < bar, prec
+
+
+# 3D: full lanes, padding, three cells per lane, the fewest planes, y rows
+# that leave one or two rows over the unrolled ones
+SHAPES3 = [(64, 5, 3), (65, 4, 2), (130, 3, 2), (3, 3, 2), (9, 7, 5), (20, 6, 4)]
+
+
+@pytest.mark.parametrize("nx,ny,nz", SHAPES3)
+@pytest.mark.parametrize("sigma", [False, True])
+def test_rows_lockstep_3d(P, nx, ny, nz, sigma):
+    rng = np.random.default_rng([nx, ny, nz])
+    sg = 2.0 ** rng.uniform(-1, 1, nx * ny * nz) if sigma else None
+    s = np.ones((nz, ny, nx), np.uint8)
+    s[:, ny // 3, nx // 4: nx // 4 + max(1, nx // 3)] = 0
+    s[0, -1, 0] = 0
+    w = gen.small_3d(nx, ny, nz, solid=s, n_theta=4, n_phi=6, n_mfp=2, sigma=sg)
+    w = dataclasses.replace(w, grad_axis=int(sigma))
+    prob = Problem(w)
+    K = 4
+    ref = source_iteration(prob, n_passes=K)
+    Jref = np.zeros((w.n_cells, 3))
     Jref[prob.mesh.cells] = ref["J"]
     for prec, tol, bar in ((0, 1e-14, 1e-10), (1, 1e-6, 1e-4)):
         r = gpu_solve(P, w, precision=prec, outer_tol=0.0, max_outer=K, inner_tol=tol, fourier_tol=1e-14,
