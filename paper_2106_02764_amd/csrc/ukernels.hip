@@ -10,25 +10,40 @@
 // changing.
 //
 // Transport: one wavefront owns one (m, l) system.  Within a direction the
-// cells are ordered upwind (the host sorts them into levels whose cells
-// depend only on earlier levels, the periodic faces cut), so a sweep is one
-// pass over the levels with the solution in LDS.  The values entering
-// through periodic faces form the system's wrap vector u; BiCGSTAB solves
-// (I - G) e = r for its correction, G being one sweep with u as the only
-// source, as on the structured grids.  All sums are in a fixed order: FP64
-// results are bitwise reproducible.
+// host puts the cells in rows of at most 64 that read only cells of earlier
+// rows (the periodic faces cut), so a sweep is one pass over the rows, the
+// values that later rows read in LDS.  The values entering through periodic
+// faces form the system's wrap vector u; BiCGSTAB solves (I - G) e = r for its
+// correction, G being one sweep with u as the only source, as on the
+// structured grids.  All sums are in a fixed order: FP64 results are bitwise
+// reproducible.
+#include "device.h"
 #include "umesh_internal.h"
 
 namespace {
 
-constexpr int WAVE = 64;
 constexpr int UF_THREADS = 1024;
 
-__device__ __forceinline__ double shfl_xor(double v, int m) { return __shfl_xor(v, m, WAVE); }
-
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) v += shfl_xor(v, m);
+// Butterfly sum over the wave (partners 32, 16, 8, 4, 2, 1 lanes away), every
+// lane the same value.  After a step the values repeat with its distance, so
+// a rotation in a row of 16 lanes brings the same partner as the exchange
+// would: moves within the vector unit, where LDS permutes take their latency
+// six times in a row.
+__device__ __forceinline__ double ubutterfly_sum(double v) {
+    auto swap = [](double a, bool half) {
+        const unsigned lo = (unsigned)__double2loint(a), hi = (unsigned)__double2hiint(a);
+        const auto l = half ? __builtin_amdgcn_permlane32_swap(lo, lo, false, false)
+                            : __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+        const auto h = half ? __builtin_amdgcn_permlane32_swap(hi, hi, false, false)
+                            : __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+        return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
+    };
+    v = swap(v, true);
+    v = swap(v, false);
+    v += dpp<0x128, 0xf>(v, 0.0);      // row_ror:8, 4, 2, 1
+    v += dpp<0x124, 0xf>(v, 0.0);
+    v += dpp<0x122, 0xf>(v, 0.0);
+    v += dpp<0x121, 0xf>(v, 0.0);
     return v;
 }
 
@@ -39,8 +54,8 @@ __device__ __forceinline__ double wave_max(double v) {
 }
 
 // Block-wide sum (every thread gets the same value; waves combined in order).
-__device__ double block_sum(double v, double* red) {
-    v = wave_sum(v);
+__device__ double ublock_sum(double v, double* red) {
+    v = ubutterfly_sum(v);
     const int w = threadIdx.x >> 6, nw = blockDim.x >> 6;
     __syncthreads();
     if ((threadIdx.x & 63) == 0) red[w] = v;
@@ -50,12 +65,12 @@ __device__ double block_sum(double v, double* red) {
     return s;
 }
 
-// N block-wide sums in one exchange (each value summed as block_sum does;
+// N block-wide sums in one exchange (each value summed as ublock_sum does;
 // red: at least 16 N doubles)
 template <int N>
 __device__ void block_sum_n(double (&v)[N], double* red) {
 #pragma unroll
-    for (int n = 0; n < N; ++n) v[n] = wave_sum(v[n]);
+    for (int n = 0; n < N; ++n) v[n] = ubutterfly_sum(v[n]);
     const int w = threadIdx.x >> 6, nw = blockDim.x >> 6;
     __syncthreads();
     if ((threadIdx.x & 63) == 0)
@@ -117,7 +132,7 @@ __host__ __device__ __forceinline__ int uf_blocks(int ns) { return (ns + UFB - 1
 // fixed-order sum (or max) of the B partials of a slot, in every thread
 __device__ __forceinline__ double uf_sum(const UFourierDev& f, int slot, int B, double* red) {
     const double v = (int)threadIdx.x < B ? f.fpart[slot * UF_MAXB + threadIdx.x] : 0.0;
-    return block_sum(v, red);
+    return ublock_sum(v, red);
 }
 __device__ __forceinline__ double uf_max(const UFourierDev& f, int slot, int B, double* red) {
     const double v = (int)threadIdx.x < B ? f.fpart[slot * UF_MAXB + threadIdx.x] : 0.0;
@@ -178,8 +193,8 @@ __global__ void __launch_bounds__(UFB) k_uf_init(const UFourierDev* __restrict__
         bb = s * s;
         rr = ri * ri;
     }
-    bb = block_sum(bb, red);
-    rr = block_sum(rr, red);
+    bb = ublock_sum(bb, red);
+    rr = ublock_sum(rr, red);
     if (threadIdx.x == 0) {
         f.fpart[UP_BB * UF_MAXB + blockIdx.x] = bb;
         f.fpart[UP_RR0 * UF_MAXB + blockIdx.x] = rr;
@@ -208,8 +223,8 @@ __global__ void __launch_bounds__(UFB) k_uf_w0(const UFourierDev* __restrict__ f
         gm = f.r[i] * ui;
         dl = w * ui;
     }
-    gm = block_sum(gm, red);
-    dl = block_sum(dl, red);
+    gm = ublock_sum(gm, red);
+    dl = ublock_sum(dl, red);
     if (threadIdx.x == 0) {
         f.fpart[UP_G0 * UF_MAXB + blockIdx.x] = gm;
         f.fpart[UP_D0 * UF_MAXB + blockIdx.x] = dl;
@@ -302,7 +317,7 @@ __global__ void __launch_bounds__(UFB) k_uf_sum(const UFourierDev* __restrict__ 
     __shared__ double red[UFB / 64];
     const UFourierDev& f = *fp;
     const int i = blockIdx.x * UFB + threadIdx.x;
-    const double v = block_sum(i < f.ns ? f.T[i] : 0.0, red);
+    const double v = ublock_sum(i < f.ns ? f.T[i] : 0.0, red);
     if (threadIdx.x == 0) f.fpart[UP_ST * UF_MAXB + blockIdx.x] = v;
 }
 
@@ -358,7 +373,7 @@ __global__ void __launch_bounds__(UF_THREADS) k_uf_kappa(const UFourierDev* __re
         // a = n.K n / (n.d); the secondary part g.K n - (n.K n)(g.d)/(n.d)
         tot += f.cut_A[c] * (a * (f.T[jn] + f.dT - f.T[ip]) + (gx * kx + gy * ky) - a * gd);
     }
-    tot = block_sum(tot, red);
+    tot = ublock_sum(tot, red);
     if (threadIdx.x == 0) {
         f.out[0] = f.Lg / (f.dT * f.Aperp) * tot;
         f.out[1] = f.fsc[3];
@@ -371,113 +386,195 @@ __global__ void __launch_bounds__(UF_THREADS) k_uf_kappa(const UFourierDev* __re
 // transport: one pass for every system
 // ---------------------------------------------------------------------------
 struct USys {
-    int sys, l, lb, nlev, nw;
+    int sys, l, nrow, nw;
     double lam;
-    const int* up;
-    const double* del;
 };
 
-// One sweep of the system: x (LDS) from the sources (src: sigma T_L and the
-// wall values; else none) and the wrap inflow staged in LDS.  The workgroup
-// is one wavefront, whose LDS accesses are executed in program order, so
-// level k + 1 reads what level k wrote without a barrier; the table entries
-// of a lane's cell in the next level (independent of the solution, and all
-// indexed by the sweep position: the pass's sources are packed in sweep
-// order by k_upack) are loaded two levels ahead of their solve.
-struct UEnt {
-    int i;
-    double d, sg, b;              // outflow sum, sigma, sigma T_L + the wall inflow
-    int code[UFACES];             // cell / wrap-slot inflows (walls folded into b)
-    double c[UFACES];
-};
-
-__device__ __forceinline__ void ufetch(const UGeomDev& g, const USys& s, bool src, int p, UEnt& e) {
-    const size_t pl = (size_t)s.l * g.ns + p;
-    e.i = g.ord[pl];
-    e.d = g.dout[pl];
-    e.sg = g.psg[pl];
-    const double b0 = g.pb0[pl], bw = g.pbw[pl];
-#pragma unroll
-    for (int q = 0; q < UFACES; ++q) {
-        const int code = g.inc[pl * UFACES + q];
-        e.code[q] = code <= UWALL0 ? UNONE : code;
-        e.c[q] = g.inv[pl * UFACES + q];
+// A lane's cell of a row, as loaded.
+template <int NIN>
+struct UCell {
+    double sg, d, c[NIN], b0, bw;
+    uint32_t s0, s1, s2;          // URec2's offsets, or URec3's in pairs
+    __device__ __forceinline__ uint32_t in(int q) const {
+        return NIN == 2 ? (q ? s1 : s0) : (q == 0 ? s0 & 0xffffu : (q == 1 ? s0 >> 16 : s1 & 0xffffu));
     }
-    e.b = src ? b0 + s.lam * bw : 0.0;
+    __device__ __forceinline__ uint32_t out() const { return NIN == 2 ? s2 : s1 >> 16; }
+};
+
+// A direction's sweep tables as buffer resources: pointers that come out of
+// memory are generic, and a flat load would count as an LDS access, whose
+// waits then hold up the chain.  All tables have 16 bytes a position, so that
+// a row costs one lane offset and one scalar offset.
+struct UTab {
+    rsrc_t rec, c01, pd, pb, rows;
+};
+
+__device__ __forceinline__ double udouble(unsigned lo, unsigned hi) { return __hiloint2double((int)hi, (int)lo); }
+
+// Lanes past the row's end take its last cell, whose value they then write as
+// well: no load sits in a branch, so the compiler counts the loads in flight
+// exactly, and nothing is masked.
+template <int NIN, bool SRC>
+__device__ __forceinline__ void ufetch(const UTab& t, int base, int last, UCell<NIN>& e) {
+    const int o = min((int)threadIdx.x * 16, last);
+    const auto a = __builtin_amdgcn_raw_buffer_load_b128(t.rec, o, base, 0);
+    const auto p = __builtin_amdgcn_raw_buffer_load_b128(t.pd, o, base, 0);
+    const auto c = __builtin_amdgcn_raw_buffer_load_b128(t.c01, o, base, 0);
+    if constexpr (NIN == 2) {
+        e.s0 = a[0];
+        e.s1 = a[1];
+        e.s2 = a[2];
+    } else {
+        e.c[2] = udouble(a[0], a[1]);
+        e.s0 = a[2];
+        e.s1 = a[3];
+    }
+    e.sg = udouble(p[0], p[1]);
+    e.d = udouble(p[2], p[3]);
+    e.c[0] = udouble(c[0], c[1]);
+    e.c[1] = udouble(c[2], c[3]);
+    if constexpr (SRC) {
+        const auto b = __builtin_amdgcn_raw_buffer_load_b128(t.pb, o, base, 0);
+        e.b0 = udouble(b[0], b[1]);
+        e.bw = udouble(b[2], b[3]);
+    }
+}
+
+// The kappa sums of a pass (fixed order: each thread a contiguous chunk, then
+// the block in order).
+__device__ void ukappa(const UGeomDev& g) {
+    __shared__ double red[4];
+    double a = 0.0, b = 0.0, w = 0.0;
+    const int kb = (g.ns + g.nwalls + UITEMS - 1) / UITEMS * USTRANDS;
+    for (int i = threadIdx.x; i < kb; i += blockDim.x) a += g.kpart[i];
+    const int per = (g.n_sys + blockDim.x - 1) / blockDim.x;
+    const int i0 = threadIdx.x * per, i1 = min(g.n_sys, i0 + per);
+    for (int i = i0; i < i1; ++i) {
+        b += g.kfsys[i];
+        w = fmax(w, g.wres[i]);
+    }
+    a = ublock_sum(a, red);
+    b = ublock_sum(b, red);
+    w = block_max(w, red);
+    if (threadIdx.x == 0) {
+        g.kap[0] = g.Lg / (g.dT * g.Vbox) * a;
+        g.kap[1] = b;
+        g.kap[2] = w;
+    }
 }
 
 // The pass's sources in every direction's sweep order: sigma, sigma T_L and
-// the inflow wall sum of the cell at each position (one thread per position).
-__global__ void __launch_bounds__(256) k_upack(const UGeomDev* __restrict__ gp) {
+// the inflow wall sum of the cell at each position (one thread per position);
+// with_kappa: the last block takes the kappa sums of the pass before.
+__global__ void __launch_bounds__(256) k_upack(const UGeomDev* __restrict__ gp, int with_kappa) {
     const UGeomDev& g = *gp;
-    const size_t n = (size_t)g.n_dir * g.ns;
-    for (size_t pl = (size_t)blockIdx.x * blockDim.x + threadIdx.x; pl < n; pl += (size_t)gridDim.x * blockDim.x) {
-        const int i = g.ord[pl];
+    const int n = g.n_dir * (g.ns + 1), nb = (int)gridDim.x - with_kappa;
+    if ((int)blockIdx.x == nb) {
+        ukappa(g);
+        return;
+    }
+    for (int o = blockIdx.x * blockDim.x + threadIdx.x; o < n; o += nb * blockDim.x) {
+        const int i = g.ord[o];
         double wall = 0.0;
-#pragma unroll
-        for (int q = 0; q < UFACES; ++q) {
-            const int code = g.inc[pl * UFACES + q];
-            const bool w = code <= UWALL0;
-            wall += w ? g.inv[pl * UFACES + q] * g.T_w[UWALL0 - code] : 0.0;
+        {
+#pragma clang fp contract(off)
+            for (int k = g.wall_ptr[o]; k < g.wall_ptr[o + 1]; ++k) wall = wall + g.wall_c[k] * g.T_w[g.wall_id[k]];
         }
-        const double sg = g.sigma[i];
-        g.psg[pl] = sg;
-        g.pb0[pl] = sg * g.T_L[i];
-        g.pbw[pl] = wall;
+        const double sg = i < 0 ? 1.0 : g.sigma[i], T = i < 0 ? 0.0 : g.T_L[i];
+        g.pd[o] = make_double2(sg, g.dout[o]);
+        g.pb[o] = make_double2(sg * T, wall);
     }
 }
 
-// The wrap inflow follows the solution in LDS (uin = x + ns), so an inflow
-// code indexes both: x[code] is the upwind cell's value for code < ns and the
-// wrap slot's for code >= ns; unused faces read x[0] and drop it (no branch).
-__device__ __forceinline__ void usolve(const UGeomDev& g, const USys& s, const UEnt& e, double* x, const double* uin) {
-    (void)uin;
-    double acc = 0.0;
-#pragma unroll
-    for (int q = 0; q < UFACES; ++q) {
-        const int code = e.code[q];
-        const double v = x[code >= 0 ? code : 0];       // read always, selected
-        acc += code >= 0 ? e.c[q] * v : 0.0;
-    }
-    x[e.i] = (e.b + s.lam * acc) / (e.sg + s.lam * e.d);
+// 1 / d to the last place, for normal numbers.
+__device__ __forceinline__ double urecip(double d) {
+    double r = __builtin_amdgcn_rcp(d);
+    r = fma(fma(-d, r, 1.0), r, r);
+    return fma(fma(-d, r, 1.0), r, r);
 }
 
-__device__ void usweep(const UGeomDev& g, const USys& s, bool src, double* x, const double* uin) {
-    const int lane = threadIdx.x;
-    // level k spans positions [lp[k], lp[k + 1]); past the last level the
-    // bounds clamp to its end (empty ranges).  At level k the entries of level
-    // k + 2 are fetched (two levels of loads in flight) and the bound that
-    // ends level k + 3 is loaded a level before it is needed.
-    const int* lp = g.lptr + s.lb;
-    const int L = s.nlev;
-    auto bound = [&](int k) { return lp[k < L ? k : L]; };
-    int a0 = bound(0), a1 = bound(1), e1 = bound(2), e2 = bound(3);
-    // every lane fetches (beyond its level: the level's last entry, or the
-    // first position), so no load sits in a branch: the compiler then counts
-    // the loads in flight exactly and waits only for the level it solves
-    auto pos = [&](int lo, int hi) { return lo + lane < hi ? lo + lane : (hi > 0 ? hi - 1 : 0); };
-    UEnt cur, nxt, nx2;
-    ufetch(g, s, src, pos(a0, a1), cur);
-    ufetch(g, s, src, pos(a1, e1), nxt);
-    for (int k = 0; k < L; ++k) {
-        const int e3 = bound(k + 4);
-        ufetch(g, s, src, pos(e1, e2), nx2);
-        if (a0 + lane < a1) usolve(g, s, cur, x, uin);
-        for (int p = a0 + lane + WAVE; p < a1; p += WAVE) {
-            UEnt e;
-            ufetch(g, s, src, p, e);
-            usolve(g, s, e, x, uin);
-        }
-        // keeps the compiler from moving this level's LDS accesses past the
-        // next level's
-        __builtin_amdgcn_wave_barrier();
-        cur = nxt;
-        nxt = nx2;
-        a0 = a1;
-        a1 = e1;
-        e1 = e2;
-        e2 = e3;
+// a store at a lane offset and a scalar offset
+__device__ __forceinline__ void ust(double v, rsrc_t r, uint32_t vo, uint32_t so) {
+    u32x2_t w;
+    w.x = (unsigned)__double2loint(v);
+    w.y = (unsigned)__double2hiint(v);
+    __builtin_amdgcn_raw_buffer_store_b64(w, r, (int)vo, (int)so, 0);
+}
+
+// One sweep of the system from the wrap inflow staged in LDS and, SRC, the
+// sources; SRC also stores the solution, by position (whole lines, for
+// k_ureduce to put in order).  The workgroup is one
+// wavefront, whose LDS accesses are executed in program order, so a row reads
+// what the rows before it wrote without a barrier.
+//
+// What bounds it is the chain from row to row: LDS read, the inflow sum, the
+// quotient, LDS write.  So UROWS rows of table entries are in flight; the
+// reciprocal 1 / (sigma + Lambda d) is taken before the row's inflow arrives,
+// and the quotient from it in one product and a residual correction (the
+// division's own result); a row is some 30 instructions; and LDS holds the
+// live values alone, a few hundred slots, so that every system of a pass is
+// resident at once.  5609 triangles in 165 rows: 22 us a sweep with 1440
+// systems at once (130 ns a row); a pass of them with all cells in LDS (three
+// systems a CU), levels for rows, entries two levels ahead and flat loads took
+// 947 us, now 243 us.
+template <int NIN, bool SRC, bool STORE>
+__device__ __forceinline__ void usweep(const UTab& t, const USys& s, double* x, rsrc_t X) {
+    const int lane = threadIdx.x, l8 = (lane & (UROWS - 1)) * 8;
+    auto rows = [&](int r) { return __builtin_amdgcn_raw_buffer_load_b64(t.rows, l8, r * 8, 0); };
+    auto at = [&](uint32_t o) -> double& { return *(double*)((char*)x + o); };
+    auto den_of = [&](const UCell<NIN>& c) { return fma(s.lam, c.d, c.sg); };
+    UCell<NIN> e[UROWS];
+    auto rc = rows(0), rn = rows(UROWS);     // this iteration's rows and the next's
+#pragma unroll
+    for (int k = 0; k < UROWS - 1; ++k) {
+        ufetch<NIN, SRC>(t, __builtin_amdgcn_readlane(rc[0], k), __builtin_amdgcn_readlane(rc[1], k), e[k]);
+        __builtin_amdgcn_sched_barrier(0);   // in the order they are waited for
     }
+    double den = den_of(e[0]), inv = urecip(den);
+    __builtin_amdgcn_sched_barrier(0);
+    for (int r = 0; r < s.nrow; r += UROWS) {
+        const auto rn2 = rows(r + 2 * UROWS);
+#pragma unroll
+        for (int k = 0; k < UROWS; ++k) {
+            // the row's inflow is read; while it is on its way the entries of
+            // the row UROWS - 1 ahead are asked for, in the place of the row
+            // before, and the next row's reciprocal is taken
+            const UCell<NIN>& c = e[k];
+            double v[NIN];
+#pragma unroll
+            for (int q = 0; q < NIN; ++q) v[q] = at(c.in(q));
+            __builtin_amdgcn_sched_barrier(0);
+            const auto& rf = k == 0 ? rc : rn;
+            const int kf = (k + UROWS - 1) % UROWS;
+            ufetch<NIN, SRC>(t, __builtin_amdgcn_readlane(rf[0], kf), __builtin_amdgcn_readlane(rf[1], kf), e[kf]);
+            const double b = SRC ? fma(s.lam, c.bw, c.b0) : 0.0;
+            const double den1 = den_of(e[(k + 1) % UROWS]), inv1 = urecip(den1);
+            // (kept apart: the scheduler would move every reciprocal of an
+            // iteration to its start, and wait there for the rows asked for last)
+            __builtin_amdgcn_sched_barrier(0);
+            double acc = c.c[0] * v[0];
+            {
+                // products and sum apart: the products start with their reads
+#pragma clang fp contract(off)
+#pragma unroll
+                for (int q = 1; q < NIN; ++q) acc = acc + c.c[q] * v[q];
+            }
+            const double num = SRC ? fma(s.lam, acc, b) : s.lam * acc;
+            const double q0 = num * inv;
+            const double xv = fma(fma(-den, q0, num), inv, q0);
+            at(c.out()) = xv;
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (STORE) {
+                const int base = __builtin_amdgcn_readlane(rc[0], k), last = __builtin_amdgcn_readlane(rc[1], k);
+                ust(xv, X, (uint32_t)min(lane * 16, last) / 2u, (uint32_t)base / 2u);
+            }
+            den = den1;
+            inv = inv1;
+        }
+        rc = rn;
+        rn = rn2;
+    }
+    __builtin_amdgcn_wave_barrier();
 }
 
 template <int WPL>
@@ -491,14 +588,11 @@ __device__ __forceinline__ void ustage(const USys& s, const double (&v)[WPL], do
 }
 
 // G v: the values a homogeneous sweep with inflow v carries back across the
-// periodic faces
+// periodic faces (up: their slots)
 template <int WPL>
-__device__ __forceinline__ void ugather(const USys& s, const double* x, double (&out)[WPL]) {
+__device__ __forceinline__ void ugather(const double* x, const int (&up)[WPL], double (&out)[WPL]) {
 #pragma unroll
-    for (int k = 0; k < WPL; ++k) {
-        const int q = k * WAVE + threadIdx.x;
-        out[k] = q < s.nw ? x[s.up[q]] : 0.0;
-    }
+    for (int k = 0; k < WPL; ++k) out[k] = *(const double*)((const char*)x + up[k]);
 }
 
 template <int WPL>
@@ -506,10 +600,10 @@ __device__ __forceinline__ double udot(const double (&a)[WPL], const double (&b)
     double v = 0.0;
 #pragma unroll
     for (int k = 0; k < WPL; ++k) v += a[k] * b[k];
-    return wave_sum(v);
+    return ubutterfly_sum(v);
 }
 
-template <int WPL>
+template <int WPL, int NIN>
 __global__ void __launch_bounds__(WAVE) k_upass(const UGeomDev* __restrict__ gp, double inner_tol, double inner_rtol,
                                                 int max_inner) {
     extern __shared__ double lds[];
@@ -524,38 +618,63 @@ __global__ void __launch_bounds__(WAVE) k_upass(const UGeomDev* __restrict__ gp,
     const int m = g.n_mfp - 1 - (int)blockIdx.x / g.n_dir;
     s.sys = m * g.n_dir + s.l;
     s.lam = g.mfp[m];
-    s.lb = g.lbase[s.l];
-    s.nlev = g.nlev[s.l];
+    s.nrow = g.nrow[s.l];
     s.nw = g.nwrap[s.l];
-    s.up = g.wup + (size_t)s.l * g.wmax;
-    s.del = g.wdel + (size_t)s.l * g.wmax;
     double* x = lds;
-    double* uin = lds + g.ns;
-    double* U = g.U + (size_t)s.sys * g.wmax;
+    double* uin = lds + USLOT_WRAP;
+    if (lane == 0) x[USLOT_ZERO] = 0.0;
+    const uint32_t np = (uint32_t)g.ns + 1u;
+    const rsrc_t X = make_rsrc(g.X + (size_t)s.sys * np, np * 8u);
+    const size_t p0 = (size_t)s.l * np;
+    const UTab t = {make_rsrc((const URec2*)g.rec + p0, np * 16u), make_rsrc(g.c01 + p0, np * 16u),
+                    make_rsrc(g.pd + p0, np * 16u), make_rsrc(g.pb + p0, np * 16u),
+                    make_rsrc(g.rows + g.rbase[s.l], (uint32_t)(s.nrow + UROW_SLACK) * 8u)};
+    const size_t w0 = (size_t)s.l * g.wmax;
+    const auto U = gmut(g.U) + (size_t)s.sys * g.wmax;
+    const auto wslot = gview(g.wslot) + w0;
+    const auto wdel = gview(g.wdel) + w0;
+    int up[WPL];
     double u[WPL], ez[WPL], r[WPL];
 #pragma unroll
     for (int k = 0; k < WPL; ++k) {
         const int q = k * WAVE + lane;
         u[k] = q < s.nw ? U[q] : 0.0;
+        up[k] = q < s.nw ? wslot[q] : 8 * USLOT_ZERO;
     }
-    // ---- the sweep with the sources and the wrap inflow of the last pass
-    ustage(s, u, uin);
-    usweep(g, s, true, x, uin);
-    ugather(s, x, ez);
-#pragma unroll
-    for (int k = 0; k < WPL; ++k) {
-        const int q = k * WAVE + lane;
-        if (q < s.nw) ez[k] += s.del[q];
-        r[k] = ez[k] - u[k];
-    }
-    const double scale = sqrt(udot(ez, ez));
-    double rn = sqrt(udot(r, r));
+    double scale = 0.0, rn = 0.0;
     long long its = 0;
-    // this pass's target: inner_tol relative to the inflow, or (forcing
-    // term) a cut by inner_rtol of the residual the pass started from; the
-    // rest carries into the next pass through U
-    const double thr = fmax(inner_tol * scale, inner_rtol * rn);
-    if (s.nw > 0 && scale > 0.0 && rn > thr) {
+    // the sweep with the sources and the wrap inflow of the last pass, and a
+    // second time with the corrected inflow (one loop: one copy of the code)
+    // (a system that corrected its inflow in the last pass will again, most
+    // often: its first sweep then stores nothing)
+    bool store = !gview(g.corrected)[s.sys], corrected = false, fixed = false;
+    for (;;) {
+        ustage(s, u, uin);
+        if (store) {
+            usweep<NIN, true, true>(t, s, x, X);
+        } else {
+            usweep<NIN, true, false>(t, s, x, X);
+        }
+        if (corrected) break;
+        ugather(x, up, ez);
+#pragma unroll
+        for (int k = 0; k < WPL; ++k) {
+            const int q = k * WAVE + lane;
+            if (q < s.nw) ez[k] += wdel[q];
+            r[k] = ez[k] - u[k];
+        }
+        scale = sqrt(udot(ez, ez));
+        rn = sqrt(udot(r, r));
+        // this pass's target: inner_tol relative to the inflow, or (forcing
+        // term) a cut by inner_rtol of the residual the pass started from; the
+        // rest carries into the next pass through U
+        const double thr = fmax(inner_tol * scale, inner_rtol * rn);
+        if (!(s.nw > 0 && scale > 0.0 && rn > thr)) {
+            if (store) break;
+            store = true;                   // the same sweep again, stored
+            corrected = true;
+            continue;
+        }
         // ---- BiCGSTAB on (I - G) e = r, the best iterate kept
         double e[WPL], eb[WPL], rh[WPL], p[WPL], v[WPL], sv[WPL], tt[WPL], gx[WPL];
 #pragma unroll
@@ -576,8 +695,8 @@ __global__ void __launch_bounds__(WAVE) k_upass(const UGeomDev* __restrict__ gp,
 #pragma unroll
             for (int k = 0; k < WPL; ++k) p[k] = r[k] + beta * (p[k] - omega * v[k]);
             ustage(s, p, uin);
-            usweep(g, s, false, x, uin);
-            ugather(s, x, gx);
+            usweep<NIN, false, false>(t, s, x, X);
+            ugather(x, up, gx);
 #pragma unroll
             for (int k = 0; k < WPL; ++k) v[k] = p[k] - gx[k];
             const double rv = udot(rh, v);
@@ -603,8 +722,8 @@ __global__ void __launch_bounds__(WAVE) k_upass(const UGeomDev* __restrict__ gp,
                 break;
             }
             ustage(s, sv, uin);
-            usweep(g, s, false, x, uin);
-            ugather(s, x, gx);
+            usweep<NIN, false, false>(t, s, x, X);
+            ugather(x, up, gx);
 #pragma unroll
             for (int k = 0; k < WPL; ++k) tt[k] = sv[k] - gx[k];
             const double t2 = udot(tt, tt);
@@ -625,110 +744,139 @@ __global__ void __launch_bounds__(WAVE) k_upass(const UGeomDev* __restrict__ gp,
             if (rn <= thr) break;
         }
         rn = best;
-        // ---- the corrected inflow, and the final sweep with it
+        // ---- the corrected inflow
 #pragma unroll
         for (int k = 0; k < WPL; ++k) {
             u[k] += eb[k];
             const int q = k * WAVE + lane;
             if (q < s.nw) U[q] = u[k];
         }
-        ustage(s, u, uin);
-        usweep(g, s, true, x, uin);
+        fixed = store = corrected = true;
     }
-    // ---- the stored solution and this system's kappa shares
-    double kc = 0.0;
-    double* X = g.X + (size_t)s.sys * g.ns;
-    for (int i = lane; i < g.ns; i += WAVE) {
-        const double xv = x[i];
-        X[i] = xv;
-        kc += g.V[i] * xv;
-    }
-    kc = wave_sum(kc);
+    // ---- this system's kappa_face share: the flow across the cut, each of
+    // whose faces is a wrap slot with its upwind cell's value
     const double Sx = g.S[2 * s.sys], Sy = g.S[2 * s.sys + 1];
-    double kf = 0.0;
-    for (int c = lane; c < g.ncut; c += WAVE) {
-        const double sn = Sx * g.cut_An[2 * c] + Sy * g.cut_An[2 * c + 1];     // A_f S . n
-        const double up = sn > 0.0 ? x[g.cut_i[c]] : x[g.cut_j[c]] + g.dT;
-        kf -= sn * up;                 // flow from the + side cell out across the cut
+    double kf = 0.0, xu[WPL];
+    ugather(x, up, xu);
+#pragma unroll
+    for (int k = 0; k < WPL; ++k) {
+        const int q = k * WAVE + lane;
+        if (q < s.nw) {
+            const auto c = gview(g.wcut) + 3 * (w0 + q);
+            kf -= (Sx * c[0] + Sy * c[1]) * (xu[k] + c[2]);
+        }
     }
-    kf = wave_sum(kf);
+    kf = ubutterfly_sum(kf);
     if (lane == 0) {
-        const double Sg = g.S[2 * s.sys + g.grad_axis];
-        g.ksys[s.sys] = g.Lg / (g.dT * g.Vbox) * Sg * kc;
         g.kfsys[s.sys] = g.Lg / (g.dT * g.Aperp) * kf;
         g.iters[s.sys] += its;
+        g.corrected[s.sys] = fixed;
         g.wres[s.sys] = scale > 0.0 ? rn / scale : 0.0;
     }
 }
 
 // T_L = sum D x per cell, T_w = sum of the outgoing weights times x at the
-// wall's cell.  A block owns 64 cells (or 64 wall faces); its UQ waves sum
-// fixed chunks of the systems, combined in order.
-constexpr int UQ = 16;
-
-__global__ void __launch_bounds__(64 * UQ) k_ureduce(const UGeomDev* __restrict__ gp) {
-    __shared__ double part[UQ][64];
+// wall's cell, and the cells' shares of kappa_cc.  The systems are taken in UQ
+// chunks, each chunk's every fourth system by one strand of workgroups (what a
+// chunk has past a multiple of eight goes to the first), one after the other:
+// the system's solution goes through LDS from sweep order to the cells, the
+// next two on their way meanwhile.  5609 cells, 1440 systems (65 MB): 40 us
+// with two workgroups a strand, each reading the whole system; 51 us with one
+// and one system on its way; 107 us with a block per 64 cells on an X by cell,
+// whose scattered stores the sweeps had to make.
+__global__ void __launch_bounds__(URED_THREADS) k_ureduce(const UGeomDev* __restrict__ gp) {
+    extern __shared__ double lds[];
     const UGeomDev& g = *gp;
-    const int q = threadIdx.x >> 6, cl = threadIdx.x & 63;
-    const int cblocks = (g.ns + 63) / 64;
-    const bool walls = (int)blockIdx.x >= cblocks;
-    const int t = (walls ? (int)blockIdx.x - cblocks : (int)blockIdx.x) * 64 + cl;
-    const int n = walls ? g.nwalls : g.ns;
-    const bool in = t < n;
-    const int cell = in ? (walls ? g.wcell[t] : t) : 0;
+    const int tid = threadIdx.x, ns = g.ns, nw = g.nwalls, items = ns + nw;
+    const int strand = (int)blockIdx.x % USTRANDS, q = strand >> 2, j = strand & 3;
+    const int it0 = (int)blockIdx.x / USTRANDS * UITEMS + tid;
     const int per = (g.n_sys + UQ - 1) / UQ;
-    const int i0 = q * per, i1 = min(g.n_sys, i0 + per);
-    // eight systems' values in flight per lane, four running sums
-    auto wgt = [&](int k) { return walls ? (in ? g.wout[(size_t)t * g.n_sys + k] : 0.0) : g.Dw[k]; };
-    double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
-    int i = i0;
-    for (; i + 7 < i1; i += 8) {
-        double xv[8], wv[8];
+    const int i0 = q * per, i1 = min(g.n_sys, i0 + per), n8 = max(i1 - i0, 0) & ~7;
+    const int n = n8 / 4 + (j == 0 ? max(i1 - i0, 0) - n8 : 0);
+    auto sys = [&](int t) { return i0 + (t < n8 / 4 ? 4 * t + j : n8 + t - n8 / 4); };
+    const auto gX = gview(g.X);
+    const auto gI = gview(g.ipos);
+    const auto gW = gview(g.wout);
+    constexpr int ROWS = 8;                       // ns <= 8192
+    // two systems on their way
+    struct Next {
+        double x[ROWS], w[UITEMS_PER];
+        unsigned ip[UITEMS_PER];
+    } nx[2];
+    double a[UITEMS_PER], v[UITEMS_PER], z = 0.0;
+    auto load = [&](int k, Next& e) {
 #pragma unroll
-        for (int u = 0; u < 8; ++u) xv[u] = g.X[(size_t)(i + u) * g.ns + cell];
+        for (int u = 0; u < ROWS; ++u)
+            if (tid + u * URED_THREADS < ns) e.x[u] = gX[(size_t)k * (ns + 1) + tid + u * URED_THREADS];
+        const auto I = gI + (size_t)(k % g.n_dir) * items;
 #pragma unroll
-        for (int u = 0; u < 8; ++u) wv[u] = wgt(i + u);
-        a0 += wv[0] * xv[0];
-        a1 += wv[1] * xv[1];
-        a2 += wv[2] * xv[2];
-        a3 += wv[3] * xv[3];
-        a0 += wv[4] * xv[4];
-        a1 += wv[5] * xv[5];
-        a2 += wv[6] * xv[6];
-        a3 += wv[7] * xv[7];
+        for (int u = 0; u < UITEMS_PER; ++u) {
+            const int it = it0 + u * URED_THREADS;
+            e.ip[u] = I[min(it, items - 1)];
+            e.w[u] = it >= ns && it < items ? gW[(size_t)k * nw + (it - ns)] : 0.0;
+        }
+    };
+    auto take = [&](int t, Next& e) {
+        const double D = g.Dw[sys(t)], S = g.S[2 * sys(t) + g.grad_axis];
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < ROWS; ++u)
+            if (tid + u * URED_THREADS < ns) lds[tid + u * URED_THREADS] = e.x[u];
+        double w[UITEMS_PER];
+        unsigned ip[UITEMS_PER];
+#pragma unroll
+        for (int u = 0; u < UITEMS_PER; ++u) {
+            w[u] = it0 + u * URED_THREADS < ns ? D : e.w[u];
+            ip[u] = e.ip[u];
+        }
+        if (t + 2 < n) load(sys(t + 2), e);
+        __syncthreads();
+        double vx = 0.0;
+#pragma unroll
+        for (int u = 0; u < UITEMS_PER; ++u) {
+            const double xv = lds[ip[u]];
+            a[u] = fma(w[u], xv, a[u]);
+            vx = fma(v[u], xv, vx);
+        }
+        z = fma(S, vx, z);
+    };
+#pragma unroll
+    for (int u = 0; u < UITEMS_PER; ++u) {
+        const int it = it0 + u * URED_THREADS;
+        a[u] = 0.0;
+        v[u] = it < ns ? g.V[it] : 0.0;
     }
-    for (; i < i1; ++i) a0 += wgt(i) * g.X[(size_t)i * g.ns + cell];
-    part[q][cl] = (a0 + a1) + (a2 + a3);
+    if (n > 0) load(sys(0), nx[0]);
+    if (n > 1) load(sys(1), nx[1]);
+    for (int t = 0; t < n; t += 2) {
+        take(t, nx[0]);
+        if (t + 1 < n) take(t + 1, nx[1]);
+    }
+#pragma unroll
+    for (int u = 0; u < UITEMS_PER; ++u) {
+        const int it = it0 + u * URED_THREADS;
+        if (it < items) g.part[(size_t)strand * items + it] = a[u];
+    }
     __syncthreads();
-    if (q == 0 && in) {
-        double acc = 0.0;
-#pragma unroll
-        for (int u = 0; u < UQ; ++u) acc += part[u][cl];
-        if (walls) g.T_w[t] = acc;
-        else g.T_L[t] = acc;
-    }
+    z = ublock_sum(z, lds);
+    if (tid == 0) g.kpart[blockIdx.x] = z;
 }
 
-__global__ void __launch_bounds__(256) k_ukappa(const UGeomDev* __restrict__ gp) {
-    __shared__ double red[4];
+// The strands' sums combined in order, one thread per cell or wall face.
+__global__ void __launch_bounds__(256) k_ucombine(const UGeomDev* __restrict__ gp) {
     const UGeomDev& g = *gp;
-    double a = 0.0, b = 0.0, w = 0.0;
-    // fixed order: each thread a contiguous chunk, then the block in order
-    const int per = (g.n_sys + blockDim.x - 1) / blockDim.x;
-    const int i0 = threadIdx.x * per, i1 = min(g.n_sys, i0 + per);
-    for (int i = i0; i < i1; ++i) {
-        a += g.ksys[i];
-        b += g.kfsys[i];
-        w = fmax(w, g.wres[i]);
+    const int items = g.ns + g.nwalls, it = blockIdx.x * 256 + threadIdx.x;
+    if (it >= items) return;
+    const auto p = gview(g.part) + it;
+    double s = 0.0;
+#pragma unroll 4
+    for (int q = 0; q < UQ; ++q) {
+        const double a0 = p[(size_t)(4 * q) * items], a1 = p[(size_t)(4 * q + 1) * items];
+        const double a2 = p[(size_t)(4 * q + 2) * items], a3 = p[(size_t)(4 * q + 3) * items];
+        s += (a0 + a1) + (a2 + a3);
     }
-    a = block_sum(a, red);
-    b = block_sum(b, red);
-    w = block_max(w, red);
-    if (threadIdx.x == 0) {
-        g.kap[0] = a;
-        g.kap[1] = b;
-        g.kap[2] = w;
-    }
+    if (it < g.ns) g.T_L[it] = s;
+    else g.T_w[it - g.ns] = s;
 }
 
 }  // namespace
@@ -771,26 +919,37 @@ hipError_t ulaunch_fourier_kappa(const UFourierDev* f_dev, int ns, hipStream_t s
     return hipGetLastError();
 }
 
-hipError_t ulaunch_pass(const UGeomDev* g_dev, int n_sys, int n_pos, int wpl, size_t lds_bytes, double inner_tol,
-                        double inner_rtol, int max_inner, hipStream_t st) {
+hipError_t ulaunch_pack(const UGeomDev* g_dev, int n_pos, bool with_kappa, hipStream_t st) {
     (void)hipGetLastError();
     int blocks = (n_pos + 255) / 256;
     blocks = blocks < 1 ? 1 : (blocks > 2048 ? 2048 : blocks);
-    hipLaunchKernelGGL(k_upack, dim3(blocks), dim3(256), 0, st, g_dev);
+    hipLaunchKernelGGL(k_upack, dim3(blocks + with_kappa), dim3(256), 0, st, g_dev, (int)with_kappa);
+    return hipGetLastError();
+}
+
+hipError_t ulaunch_pass(const UGeomDev* g_dev, int n_sys, int nin, int wpl, int slots, double inner_tol,
+                        double inner_rtol, int max_inner, hipStream_t st) {
+    (void)hipGetLastError();
+    auto go = [&](auto* k) {
+        hipLaunchKernelGGL(k, dim3(n_sys), dim3(WAVE), (size_t)slots * sizeof(double), st, g_dev, inner_tol,
+                           inner_rtol, max_inner);
+        return hipGetLastError();
+    };
+    const bool tri = nin <= 2;
     switch (wpl) {
-    case 1: hipLaunchKernelGGL(k_upass<1>, dim3(n_sys), dim3(WAVE), lds_bytes, st, g_dev, inner_tol, inner_rtol, max_inner); break;
-    case 2: hipLaunchKernelGGL(k_upass<2>, dim3(n_sys), dim3(WAVE), lds_bytes, st, g_dev, inner_tol, inner_rtol, max_inner); break;
-    case 4: hipLaunchKernelGGL(k_upass<4>, dim3(n_sys), dim3(WAVE), lds_bytes, st, g_dev, inner_tol, inner_rtol, max_inner); break;
-    case 8: hipLaunchKernelGGL(k_upass<8>, dim3(n_sys), dim3(WAVE), lds_bytes, st, g_dev, inner_tol, inner_rtol, max_inner); break;
+    case 1: return tri ? go(k_upass<1, 2>) : go(k_upass<1, 3>);
+    case 2: return tri ? go(k_upass<2, 2>) : go(k_upass<2, 3>);
+    case 4: return tri ? go(k_upass<4, 2>) : go(k_upass<4, 3>);
+    case 8: return tri ? go(k_upass<8, 2>) : go(k_upass<8, 3>);
     default: return hipErrorInvalidValue;
     }
-    return hipGetLastError();
 }
 
 hipError_t ulaunch_reduce(const UGeomDev* g_dev, int ns, int nwalls, hipStream_t st) {
     (void)hipGetLastError();
-    const int blocks = (ns + 63) / 64 + (nwalls + 63) / 64;
-    hipLaunchKernelGGL(k_ureduce, dim3(blocks), dim3(64 * UQ), 0, st, g_dev);
-    hipLaunchKernelGGL(k_ukappa, dim3(1), dim3(256), 0, st, g_dev);
+    const int items = ns + nwalls;
+    const size_t lds = sizeof(double) * (size_t)(ns < 64 ? 64 : ns);
+    hipLaunchKernelGGL(k_ureduce, dim3(USTRANDS * ((items + UITEMS - 1) / UITEMS)), dim3(URED_THREADS), lds, st, g_dev);
+    hipLaunchKernelGGL(k_ucombine, dim3((items + 255) / 256), dim3(256), 0, st, g_dev);
     return hipGetLastError();
 }

@@ -13,6 +13,7 @@
 
 #include <algorithm>
 #include <array>
+#include <climits>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -62,10 +63,10 @@ struct obte_umesh {
     // material
     bool has_material = false;
     int n_mfp = 0, n_dir = 0, n_sys = 0;
-    std::vector<double> mfp, dirs, Dw, S, wout;
+    std::vector<double> mfp, dirs, Dw, S;
     double kax[2] = {0, 0};
     std::vector<int> nlev;
-    int wmax = 0;
+    int wmax = 0, slots = 0;                   // wrap slots of a direction, LDS slots of a system
     // device
     std::vector<void*> dev;
     UGeomDev gh{};
@@ -343,33 +344,46 @@ obte_status obte_umesh_material_set(obte_umesh* m, const double* mfp, int n_mfp,
             }
         }
     // outgoing weights of each wall face: ReLu(S . n) / sum ReLu(S . n)
-    m->wout.assign((size_t)nw * m->n_sys, 0.0);
+    std::vector<double> wout((size_t)nw * m->n_sys, 0.0);
     for (int w = 0; w < nw; ++w) {
+        auto out = [&](int sys) {
+            return std::max(0.0, m->S[2 * sys] * m->wn[2 * w] + m->S[2 * sys + 1] * m->wn[2 * w + 1]);
+        };
         double tot = 0.0;
-        for (int sys = 0; sys < m->n_sys; ++sys)
-            tot += std::max(0.0, m->S[2 * sys] * m->wn[2 * w] + m->S[2 * sys + 1] * m->wn[2 * w + 1]);
-        for (int sys = 0; sys < m->n_sys; ++sys) {
-            const double r = std::max(0.0, m->S[2 * sys] * m->wn[2 * w] + m->S[2 * sys + 1] * m->wn[2 * w + 1]);
-            m->wout[(size_t)w * m->n_sys + sys] = tot > 0.0 ? r / tot : 0.0;
-        }
+        for (int sys = 0; sys < m->n_sys; ++sys) tot += out(sys);
+        for (int sys = 0; sys < m->n_sys; ++sys) wout[(size_t)sys * nw + w] = tot > 0.0 ? out(sys) / tot : 0.0;
     }
-    // ---- per-direction upwind order (periodic faces cut) and wrap slots
-    std::vector<int> ord((size_t)n_dir * ns), lbase(n_dir), lptr, nwrap(n_dir, 0);
-    std::vector<int> inc((size_t)n_dir * ns * UFACES, UNONE);
-    std::vector<double> dout((size_t)n_dir * ns, 0.0), inv((size_t)n_dir * ns * UFACES, 0.0);
-    std::vector<std::vector<int>> wup_l(n_dir);
-    std::vector<std::vector<double>> wdel_l(n_dir);
+    // ---- per direction: the upwind graph (periodic faces cut), the rows of
+    // its sweep and the LDS slots of the values that later rows read
+    const size_t npos = (size_t)n_dir * (ns + 1);
+    std::vector<int> ord(npos, -1), rbase(n_dir), nrow(n_dir), nwrap(n_dir, 0), wall_ptr{0}, wall_id;
+    std::vector<URow> rows;
+    struct Pos { double c[UIN]; int in[UIN], out; };
+    std::vector<Pos> rec(npos);
+    std::vector<double> dout(npos, 1.0), wall_c;
+    std::vector<uint16_t> ipos((size_t)n_dir * (ns + nw));
+    std::vector<std::vector<int>> wslot_l(n_dir);
+    std::vector<std::vector<double>> wdel_l(n_dir), wcut_l(n_dir);
+    wall_ptr.reserve(npos + 1);
     m->nlev.assign(n_dir, 0);
+    int nin_max = 2, slots_max = USLOT_WRAP;
+    struct Face { int code; double c; };                  // >= 0: upwind cell; < 0: wrap slot -1 - code
+    std::vector<double> dcell(ns);
+    std::vector<std::array<Face, UIN>> in(ns);
+    std::vector<int> nin(ns), indeg(ns), down((size_t)ns * UFACES), ndown(ns), height(ns), level(ns), last(ns), slot(ns),
+        queue, wallw, walln(ns + 1), byh, hptr, free_slots;
+    std::vector<double> wallc;
     for (int l = 0; l < n_dir; ++l) {
         const double s0 = dirs[2 * l], s1 = dirs[2 * l + 1];
-        std::vector<double> dcell(ns, 0.0);
-        std::vector<std::array<int, UFACES>> icode(ns);
-        std::vector<std::array<double, UFACES>> icoef(ns);
-        std::vector<int> indeg(ns, 0), nin(ns, 0);
-        std::vector<std::vector<int>> down(ns);
+        std::vector<int> wup;
+        std::fill(dcell.begin(), dcell.end(), 0.0);
+        std::fill(nin.begin(), nin.end(), 0);
+        std::fill(indeg.begin(), indeg.end(), 0);
+        std::fill(ndown.begin(), ndown.end(), 0);
+        wallw.clear();
+        wallc.clear();
         for (int i = 0; i < ns; ++i) {
-            icode[i].fill(UNONE);
-            icoef[i].fill(0.0);
+            walln[i] = (int)wallw.size();
             for (int code : m->cfaces[i]) {
                 double nx, ny, A;
                 int j = -1, w = -1, f = -1;
@@ -392,59 +406,153 @@ obte_status obte_umesh_material_set(obte_umesh* m, const double* mfp, int n_mfp,
                 if (sn > 0.0) {
                     dcell[i] += sn * A / m->V[i];
                 } else if (sn < 0.0) {
-                    const int q = nin[i]++;
-                    icoef[i][q] = -sn * A / m->V[i];
+                    const double c = -sn * A / m->V[i];
                     if (w >= 0) {
-                        icode[i][q] = UWALL0 - w;
-                    } else if (m->fper[f]) {
-                        const int slot = nwrap[l]++;
-                        wup_l[l].push_back(j);
+                        wallw.push_back(w);
+                        wallc.push_back(c);
+                        continue;
+                    }
+                    // the face vectors of a cell add to zero, so one with four
+                    // inflows has only faces along the direction: 0 to rounding
+                    if (nin[i] == UIN) continue;
+                    Face& fc = in[i][nin[i]++];
+                    fc.c = c;
+                    if (m->fper[f]) {
+                        fc.code = -1 - (int)wup.size();
+                        wup.push_back(j);
                         wdel_l[l].push_back((second ? -m->fdel[f] : m->fdel[f]) * m->dT);
-                        icode[i][q] = ns + slot;
+                        // the face as kappa_face takes it: oriented from its + side
+                        const double sg = m->fdel[f] > 0.0 ? 1.0 : (m->fdel[f] < 0.0 ? -1.0 : 0.0);
+                        const bool up_plus = second == (sg > 0.0);
+                        wcut_l[l].push_back(m->fA[f] * (sg * m->fn[2 * f]));
+                        wcut_l[l].push_back(m->fA[f] * (sg * m->fn[2 * f + 1]));
+                        wcut_l[l].push_back(sg != 0.0 && !up_plus ? m->dT : 0.0);
                     } else {
-                        icode[i][q] = j;
+                        fc.code = j;
                         ++indeg[i];
-                        down[j].push_back(i);
+                        down[(size_t)j * UFACES + ndown[j]++] = i;
                     }
                 }
             }
+            nin_max = std::max(nin_max, nin[i]);
         }
-        // levels: a cell follows every upwind neighbour it reads
-        std::vector<int> level(ns, 0), queue;
-        queue.reserve(ns);
+        walln[ns] = (int)wallw.size();
+        // levels (a cell follows every upwind neighbour it reads) and heights
+        // (the longest chain of cells that wait for it)
+        std::fill(level.begin(), level.end(), 0);
+        queue.clear();
         for (int i = 0; i < ns; ++i)
             if (indeg[i] == 0) queue.push_back(i);
+        std::vector<int> wait(indeg);
         for (size_t h = 0; h < queue.size(); ++h) {
             const int u = queue[h];
-            for (int v : down[u]) {
+            for (int k = 0; k < ndown[u]; ++k) {
+                const int v = down[(size_t)u * UFACES + k];
                 level[v] = std::max(level[v], level[u] + 1);
-                if (--indeg[v] == 0) queue.push_back(v);
+                if (--wait[v] == 0) queue.push_back(v);
             }
         }
         if ((int)queue.size() != ns)
             return ufail(OBTE_ERR_ARG, "the upwind graph of direction %d has a cycle (non-convex cells?)", l);
-        std::vector<int> byl(ns);
-        for (int i = 0; i < ns; ++i) byl[i] = i;
-        std::stable_sort(byl.begin(), byl.end(), [&](int a, int b) { return level[a] < level[b]; });
-        const int nl = ns ? level[byl[ns - 1]] + 1 : 0;
-        m->nlev[l] = nl;
-        lbase[l] = (int)lptr.size();
-        int p = 0;
-        for (int k = 0; k < nl; ++k) {
-            lptr.push_back(p);
-            while (p < ns && level[byl[p]] == k) ++p;
+        int nl = 0;
+        for (int h = ns - 1; h >= 0; --h) {
+            const int u = queue[h];
+            height[u] = 0;
+            for (int k = 0; k < ndown[u]; ++k) height[u] = std::max(height[u], height[down[(size_t)u * UFACES + k]] + 1);
+            nl = std::max(nl, level[u] + 1);
         }
-        lptr.push_back(ns);
-        for (int p2 = 0; p2 < ns; ++p2) {
-            const int i = byl[p2];
-            const size_t pl = (size_t)l * ns + p2;
-            ord[pl] = i;
-            dout[pl] = dcell[i];
-            for (int q = 0; q < UFACES; ++q) {
-                inc[pl * UFACES + q] = icode[i][q];
-                inv[pl * UFACES + q] = icoef[i][q];
+        m->nlev[l] = nl;
+        // rows: of the cells whose upwind neighbours are in earlier rows, the
+        // 64 with the greatest heights (so a level wider than a wavefront
+        // gives its less urgent cells to later, narrower rows)
+        const size_t p0 = (size_t)l * (ns + 1);
+        rbase[l] = (int)rows.size();
+        std::vector<std::vector<int>> ready(nl);           // by height
+        int top = 0, left = ns, p = 0, nslots = 0, r = 0;
+        for (int i = 0; i < ns; ++i)
+            if (indeg[i] == 0) {
+                ready[height[i]].push_back(i);
+                top = std::max(top, height[i]);
+            }
+        wait = indeg;
+        std::vector<int> row_of(ns, 0), row_end;
+        for (; left > 0; ++r) {
+            const int b = p;
+            while (p - b < 64 && top >= 0) {
+                if (ready[top].empty()) {
+                    --top;
+                    continue;
+                }
+                const int i = ready[top].back();
+                ready[top].pop_back();
+                row_of[i] = r;
+                ord[p0 + p++] = i;
+            }
+            std::sort(ord.begin() + p0 + b, ord.begin() + p0 + p);
+            left -= p - b;
+            top = std::max(top, 0);
+            for (int q = b; q < p; ++q) {
+                const int u = ord[p0 + q];
+                for (int k = 0; k < ndown[u]; ++k) {
+                    const int v = down[(size_t)u * UFACES + k];
+                    if (--wait[v] == 0) {
+                        ready[height[v]].push_back(v);
+                        top = std::max(top, height[v]);
+                    }
+                }
+            }
+            rows.push_back({16 * b, 16 * (p - b - 1)});
+            row_end.push_back(p);
+        }
+        nrow[l] = (r + UROWS - 1) / UROWS * UROWS;
+        for (int q = r; q < nrow[l] + UROW_SLACK; ++q) rows.push_back({16 * ns, 0});
+        // slots: a value is kept until the last row that reads it (which may
+        // give the slot to a cell of its own: a row reads before it writes),
+        // a wrap slot's upwind cell to the end
+        std::fill(last.begin(), last.end(), -1);
+        for (int i = 0; i < ns; ++i)
+            for (int k = 0; k < ndown[i]; ++k) last[i] = std::max(last[i], row_of[down[(size_t)i * UFACES + k]]);
+        for (int i : wup) last[i] = INT_MAX;
+        const int nwl = (int)wup.size(), first = USLOT_WRAP + nwl;
+        nwrap[l] = nwl;
+        free_slots.clear();
+        std::vector<std::vector<int>> ends(r);
+        for (int i = 0; i < ns; ++i)
+            if (last[i] >= 0 && last[i] < r) ends[last[i]].push_back(i);
+        for (int q = 0, k = 0; k < r; ++k) {
+            for (int i : ends[k]) free_slots.push_back(slot[i]);
+            for (; q < row_end[k]; ++q) {
+                const int i = ord[p0 + q];
+                if (last[i] < 0) {
+                    slot[i] = USLOT_TRASH;
+                } else if (!free_slots.empty()) {
+                    slot[i] = free_slots.back();
+                    free_slots.pop_back();
+                } else {
+                    slot[i] = first + nslots++;
+                }
+                Pos& e = rec[p0 + q];
+                dout[p0 + q] = dcell[i];
+                for (int t = 0; t < UIN; ++t) {
+                    const Face fc = t < nin[i] ? in[i][t] : Face{0, 0.0};
+                    e.in[t] = t >= nin[i] ? USLOT_ZERO : (fc.code >= 0 ? slot[fc.code] : USLOT_WRAP - 1 - fc.code);
+                    e.c[t] = fc.c;
+                }
+                e.out = slot[i];
+                for (int t = walln[i]; t < walln[i + 1]; ++t) {
+                    wall_id.push_back(wallw[t]);
+                    wall_c.push_back(wallc[t]);
+                }
+                wall_ptr.push_back((int)wall_id.size());
             }
         }
+        rec[p0 + ns] = {{0.0, 0.0, 0.0}, {USLOT_ZERO, USLOT_ZERO, USLOT_ZERO}, USLOT_TRASH};
+        wall_ptr.push_back((int)wall_id.size());
+        for (int i : wup) wslot_l[l].push_back(8 * slot[i]);
+        uint16_t* pos = ipos.data() + (size_t)l * (ns + nw);
+        for (int q = 0; q < ns; ++q) pos[ord[p0 + q]] = (uint16_t)q;
+        for (int w = 0; w < nw; ++w) pos[ns + w] = pos[m->wcell[w]];
+        slots_max = std::max(slots_max, first + nslots);
     }
     int wmax = 0;
     for (int l = 0; l < n_dir; ++l) wmax = std::max(wmax, nwrap[l]);
@@ -452,13 +560,31 @@ obte_status obte_umesh_material_set(obte_umesh* m, const double* mfp, int n_mfp,
     if ((size_t)(ns + wmax) * 8 > 65536)
         return ufail(OBTE_ERR_ARG, "%d solid cells and %d periodic faces exceed one workgroup's LDS", ns, wmax);
     m->wmax = std::max(wmax, 1);
-    std::vector<int> wup((size_t)n_dir * m->wmax, 0);
-    std::vector<double> wdel((size_t)n_dir * m->wmax, 0.0);
-    for (int l = 0; l < n_dir; ++l)
-        for (int q = 0; q < nwrap[l]; ++q) {
-            wup[(size_t)l * m->wmax + q] = wup_l[l][q];
-            wdel[(size_t)l * m->wmax + q] = wdel_l[l][q];
-        }
+    // a value that is kept has a reader (three inflows a cell at most) among
+    // the cells to come, so at most 3/4 of the cells have slots at a time
+    m->slots = slots_max;
+    if (slots_max > 8192) return ufail(OBTE_ERR_STATE, "%d values in flight in a sweep", slots_max);
+    std::vector<URec2> rec2(nin_max > 2 ? 0 : npos);
+    std::vector<URec3> rec3(nin_max > 2 ? npos : 0);
+    std::vector<double> c01(2 * npos);
+    for (size_t q = 0; q < npos; ++q) {
+        const Pos& e = rec[q];
+        c01[2 * q] = e.c[0];
+        c01[2 * q + 1] = e.c[1];
+        if (nin_max > 2)
+            rec3[q] = {e.c[2], {(uint16_t)(8 * e.in[0]), (uint16_t)(8 * e.in[1]), (uint16_t)(8 * e.in[2])},
+                       (uint16_t)(8 * e.out)};
+        else
+            rec2[q] = {{8u * e.in[0], 8u * e.in[1]}, 8u * e.out, 0u};
+    }
+    std::vector<int> wslot((size_t)n_dir * m->wmax, 8 * USLOT_ZERO);
+    std::vector<double> wdel((size_t)n_dir * m->wmax, 0.0), wcut(3 * (size_t)n_dir * m->wmax, 0.0);
+    for (int l = 0; l < n_dir; ++l) {
+        const size_t q0 = (size_t)l * m->wmax;
+        std::copy(wslot_l[l].begin(), wslot_l[l].end(), wslot.begin() + q0);
+        std::copy(wdel_l[l].begin(), wdel_l[l].end(), wdel.begin() + q0);
+        std::copy(wcut_l[l].begin(), wcut_l[l].end(), wcut.begin() + 3 * q0);
+    }
     // ---- heat conduction tables (Appendix B, volume-scaled): per cell its
     // neighbour entries with the primary coefficient a = A n.K n / (n.d),
     // the jump of the neighbour's image and the least-squares weights
@@ -530,8 +656,8 @@ obte_status obte_umesh_material_set(obte_umesh* m, const double* mfp, int n_mfp,
     }
     // cut faces (across the periodic plane of the gradient axis), oriented
     // from the cell on the + side
-    std::vector<int> cut_f, cut_s, cut_i, cut_j;
-    std::vector<double> cut_K, cut_d, cut_A, cut_An;
+    std::vector<int> cut_f, cut_s;
+    std::vector<double> cut_K, cut_d, cut_A;
     for (int f = 0; f < nf; ++f) {
         if (m->fdel[f] == 0.0) continue;
         const double sg = m->fdel[f] > 0.0 ? 1.0 : -1.0;
@@ -539,16 +665,12 @@ obte_status obte_umesh_material_set(obte_umesh* m, const double* mfp, int n_mfp,
         const double dx = sg * m->fd[2 * f], dy = sg * m->fd[2 * f + 1];
         cut_f.push_back(f);
         cut_s.push_back(sg > 0 ? 1 : -1);
-        cut_i.push_back(sg > 0 ? m->fi[f] : m->fj[f]);
-        cut_j.push_back(sg > 0 ? m->fj[f] : m->fi[f]);
         cut_K.push_back((nx * nx * Kx + ny * ny * Ky) / (nx * dx + ny * dy));
         cut_K.push_back(Kx * nx);
         cut_K.push_back(Ky * ny);
         cut_d.push_back(dx);
         cut_d.push_back(dy);
         cut_A.push_back(m->fA[f]);
-        cut_An.push_back(m->fA[f] * nx);
-        cut_An.push_back(m->fA[f] * ny);
     }
     // ---- device tables and buffers
     obte_status s = OBTE_OK;
@@ -560,7 +682,7 @@ obte_status obte_umesh_material_set(obte_umesh* m, const double* mfp, int n_mfp,
     g.n_mfp = n_mfp;
     g.grad_axis = ga;
     g.wmax = m->wmax;
-    g.ncut = (int)cut_f.size();
+    g.nin = nin_max;
     g.dT = m->dT;
     g.Lg = m->L[ga];
     g.Vbox = m->L[0] * m->L[1];
@@ -574,37 +696,43 @@ obte_status obte_umesh_material_set(obte_umesh* m, const double* mfp, int n_mfp,
     UP((double**)&g.mfp, m->mfp);
     UP((double**)&g.Dw, m->Dw);
     UP((double**)&g.S, m->S);
-    UP((double**)&g.wout, m->wout);
-    UP((int**)&g.wcell, m->wcell);
+    UP((double**)&g.wout, wout);
+    UP(&m->wcell_d, m->wcell);
+    UP((uint16_t**)&g.ipos, ipos);
     UP((int**)&g.ord, ord);
-    UP((int**)&g.lbase, lbase);
-    UP((int**)&g.nlev, m->nlev);
-    UP((int**)&g.lptr, lptr);
+    UP((int**)&g.rbase, rbase);
+    UP((int**)&g.nrow, nrow);
+    UP((URow**)&g.rows, rows);
+    if (nin_max > 2) {
+        UP((URec3**)&g.rec, rec3);
+    } else {
+        UP((URec2**)&g.rec, rec2);
+    }
+    UP((double**)&g.c01, c01);
     UP((double**)&g.dout, dout);
-    UP((int**)&g.inc, inc);
-    UP((double**)&g.inv, inv);
     UP((int**)&g.nwrap, nwrap);
-    UP((int**)&g.wup, wup);
+    UP((int**)&g.wslot, wslot);
     UP((double**)&g.wdel, wdel);
-    UP((int**)&g.cut_i, cut_i);
-    UP((int**)&g.cut_j, cut_j);
-    UP((double**)&g.cut_An, cut_An);
+    UP((double**)&g.wcut, wcut);
+    UP((int**)&g.wall_ptr, wall_ptr);
+    UP((int**)&g.wall_id, wall_id);
+    UP((double**)&g.wall_c, wall_c);
     UP(&m->sigma1, ones);
     UP(&m->scell_d, m->scell);
-    m->wcell_d = (int*)g.wcell;
     AL((double**)&g.sigma, ns);
     AL(&g.T_L, ns);
     AL(&g.T_w, nw);
     AL(&g.U, (size_t)m->n_sys * m->wmax);
-    AL(&g.X, (size_t)m->n_sys * ns);
-    AL(&g.ksys, m->n_sys);
+    AL(&g.X, (size_t)m->n_sys * (ns + 1));
+    AL(&g.part, (size_t)USTRANDS * (ns + nw));
+    AL(&g.kpart, (size_t)USTRANDS * ((ns + nw + UITEMS - 1) / UITEMS));
     AL(&g.kfsys, m->n_sys);
     AL(&g.iters, m->n_sys);
+    AL(&g.corrected, m->n_sys);
     AL(&g.kap, 4);
     AL(&g.wres, m->n_sys);
-    AL(&g.psg, (size_t)n_dir * ns);
-    AL(&g.pb0, (size_t)n_dir * ns);
-    AL(&g.pbw, (size_t)n_dir * ns);
+    AL((double**)&g.pd, 2 * npos);
+    AL((double**)&g.pb, 2 * npos);
     UFourierDev fdv{};
     fdv.ns = ns;
     fdv.nfaces = nf;
@@ -741,17 +869,19 @@ obte_status obte_umesh_solve(obte_umesh* m, const obte_solve_opts* o, const doub
     }
     UHIP(hipMemsetAsync(g.U, 0, sizeof(double) * (size_t)m->n_sys * m->wmax, st));
     UHIP(hipMemsetAsync(g.iters, 0, sizeof(long long) * m->n_sys, st));
+    UHIP(hipMemsetAsync(g.corrected, 0, sizeof(int) * m->n_sys, st));
     int wpl = 1;
     while (wpl * 64 < m->wmax) wpl *= 2;
-    const size_t lds = sizeof(double) * ((size_t)ns + m->wmax);
     std::vector<double> hist;
     double kap[4] = {0, 0, 0, 0};
     const double wrap_tol = o->wrap_tol > 0.0 ? o->wrap_tol : std::max(o->inner_tol, 0.2 * o->outer_tol);
     bool converged = false;
     int passes = 0;
+    UHIP(ulaunch_pack(m->gd, m->n_dir * (ns + 1), false, st));
     for (passes = 1; passes <= o->max_outer; ++passes) {
-        UHIP(ulaunch_pass(m->gd, m->n_sys, m->n_dir * ns, wpl, lds, o->inner_tol, o->inner_rtol, o->max_inner, st));
+        UHIP(ulaunch_pass(m->gd, m->n_sys, g.nin, wpl, m->slots, o->inner_tol, o->inner_rtol, o->max_inner, st));
         UHIP(ulaunch_reduce(m->gd, ns, nw, st));
+        UHIP(ulaunch_pack(m->gd, m->n_dir * (ns + 1), true, st));
         UHIP(hipMemcpyAsync(kap, g.kap, sizeof kap, hipMemcpyDeviceToHost, st));
         UHIP(hipStreamSynchronize(st));
         if (!std::isfinite(kap[0])) return ufail(OBTE_ERR_NUMERIC, "non-finite kappa in pass %d", passes);

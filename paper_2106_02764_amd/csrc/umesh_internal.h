@@ -6,58 +6,91 @@
 
 // At most four faces per cell (triangles and quadrilaterals).
 constexpr int UFACES = 4;
-// Code of an inflow slot in the sweep tables: >= n_solid: a periodic face
-// (wrap slot code - n_solid); >= 0: the upwind solid cell; UWALL0 - code: a
-// wall face; UNONE: unused.
-constexpr int UNONE = -1;
-constexpr int UWALL0 = -2;
+// Inflow faces of a cell that read a solution value (walls are part of the
+// source): two in a triangle, three in a quadrilateral.
+constexpr int UIN = 3;
+// Rows of a sweep in flight (row counts are multiples of it), and the row
+// descriptors that may be read past a direction's last row.
+constexpr int UROWS = 8;
+constexpr int UROW_SLACK = 2 * UROWS;
+// LDS slots of a system's sweep: one that holds 0 (read by unused inflows),
+// one that is only written, the wrap inflow, then the values of the cells
+// that a later row still reads.
+constexpr int USLOT_ZERO = 0, USLOT_TRASH = 1, USLOT_WRAP = 2;
 // Wrap slots per wave lane the pass kernel keeps in registers.
 constexpr int UWPL_MAX = 8;
+
+// What a sweep reads of a cell besides its first two inflow coefficients and
+// sigma: the LDS byte offsets of its inflows' values and of its own, and the
+// third inflow's coefficient.
+struct alignas(16) URec2 {
+    uint32_t in[2], out, pad;
+};
+struct alignas(16) URec3 {
+    double c2;
+    uint16_t in[3], out;
+};
+static_assert(sizeof(URec2) == 16 && sizeof(URec3) == 16, "one 16-byte load");
+// A row: the byte offsets (16 a cell) of its first position, and of its last
+// cell from there.
+struct alignas(8) URow {
+    int base, last;
+};
+
+// The sums over the systems: their systems in UQ chunks of four strands each
+// (one workgroup a strand), UITEMS cells and wall faces a workgroup.
+constexpr int UQ = 16, USTRANDS = 4 * UQ, URED_THREADS = 1024, UITEMS_PER = 3, UITEMS = URED_THREADS * UITEMS_PER;
 
 struct UGeomDev {
     int ns, nwalls, n_sys, n_dir, n_mfp, grad_axis;
     int wmax;                 // wrap slots of the direction with the most
-    int ncut;                 // interior faces across the periodic plane of the gradient axis
+    int nin;                  // 2 or 3: inflows of the cell with the most
     double dT, Lg, Vbox, Aperp;
     // ---- static tables
     const double* V;          // ns: cell areas
     const double* mfp;        // n_mfp
     const double* Dw;         // n_sys: T_L weights
     const double* S;          // 2 * n_sys: flux weights
-    const double* wout;       // nwalls * n_sys: outgoing weights of each wall face
-    const int* wcell;         // nwalls: solid cell of each wall face
-    // sweep tables per direction l: cells in upwind (topological) order,
-    // grouped in levels whose cells depend only on earlier levels
-    const int* ord;           // n_dir * ns
-    const int* lbase;         // n_dir: start of direction l's level pointers in lptr
-    const int* nlev;          // n_dir
-    const int* lptr;          // level boundaries (positions in ord), n_lev + 1 per direction
-    const double* dout;       // n_dir * ns (by position): sum of the outflow |s.n| A / V
-    const int* inc;           // n_dir * ns * UFACES (by position): inflow codes
-    const double* inv;        // n_dir * ns * UFACES: inflow |s.n| A / V
+    const double* wout;       // n_sys * nwalls: outgoing weights of each wall face
+    const uint16_t* ipos;     // n_dir * (ns + nwalls): sweep position of each cell and of each wall face's cell
+    // sweep tables per direction l: the cells in rows of at most 64 that read
+    // only cells of earlier rows
+    // (n_pos = n_dir * (ns + 1): each direction's last position is a cell of
+    // no effect, which rows past the direction's end sweep)
+    const int* ord;           // n_pos: cell at each sweep position, -1 at the last
+    const int* rbase;         // n_dir: start of direction l's rows
+    const int* nrow;          // n_dir: rows (a multiple of UROWS)
+    const URow* rows;
+    const void* rec;          // n_pos: URec2 (nin 2) or URec3
+    const double2* c01;       // n_pos: |s.n| A / V of the first two inflows
+    const double* dout;       // n_pos: sum of the outflow |s.n| A / V
     const int* nwrap;         // n_dir: wrap slots of direction l
-    const int* wup;           // n_dir * wmax: upwind solid cell of each wrap slot
+    const int* wslot;         // n_dir * wmax: LDS byte offset of each wrap slot's upwind cell
     const double* wdel;       // n_dir * wmax: jump of the value crossing (delta dT)
-    const int* cut_i;         // ncut: cell on the + side of the cut
-    const int* cut_j;         // ncut: its neighbour across the cut
-    const double* cut_An;     // 2 * ncut: A_f n_f (n_f from cut_i to cut_j)
+    const double* wcut;       // 3 * n_dir * wmax: A_f n_f of a face across the periodic plane of the
+                              // gradient axis (n_f from its + side; 0 elsewhere), and the jump there
+    const int* wall_ptr;      // n_pos + 1: the inflow walls of each position
+    const int* wall_id;       // their wall faces
+    const double* wall_c;     // their |s.n| A / V
     // ---- solve state (library-owned buffers)
     const double* sigma;      // ns
     double* T_L;              // ns
     double* T_w;              // nwalls
     double* U;                // n_sys * wmax: wrap inflow values
-    double* X;                // n_sys * ns: each system's solution of the pass
-    double* ksys;             // n_sys: kappa_cc share
+    double* X;                // n_sys * (ns + 1): each system's solution of the pass, by sweep position
+    double* part;             // USTRANDS * (ns + nwalls): the strands' sums
+    double* kpart;            // USTRANDS per UITEMS items: their share of kappa_cc
     double* kfsys;            // n_sys: kappa_face share
     long long* iters;         // n_sys: accumulated BiCGSTAB iterations
     double* kap;              // 4: kappa_cc, kappa_face of the pass, max relative wrap residual
+    int* corrected;           // n_sys: whether the last pass corrected the system's wrap inflow
     double* wres;             // n_sys: relative wrap residual after the pass
     // ---- per pass, in every direction's sweep order (k_upack): sigma of the
-    // cell at each position, sigma T_L, and the sum over its inflow wall faces
-    // of |s.n| A / V T_w (the wall part of the source before the factor Lambda)
-    double* psg;              // n_dir * ns
-    double* pb0;              // n_dir * ns
-    double* pbw;              // n_dir * ns
+    // cell at each position and its outflow sum; sigma T_L and the sum over its
+    // inflow wall faces of |s.n| A / V T_w (the wall part of the source before
+    // the factor Lambda)
+    double2* pd;              // n_pos
+    double2* pb;              // n_pos
 };
 
 struct UFourierDev {
@@ -115,8 +148,11 @@ hipError_t ulaunch_fourier_cg(const UFourierDev* f_dev, int ns, int iters, doubl
                               hipStream_t st);
 hipError_t ulaunch_fourier_end(const UFourierDev* f_dev, int ns, double tol, hipStream_t st);
 hipError_t ulaunch_fourier_kappa(const UFourierDev* f_dev, int ns, hipStream_t st);
-// the pass's sources packed in sweep order (n_pos = n_dir * n_solid
-// positions), then every system's pass
-hipError_t ulaunch_pass(const UGeomDev* g_dev, int n_sys, int n_pos, int wpl, size_t lds_bytes, double inner_tol,
+// The sources of the next pass packed in sweep order (n_pos =
+// n_dir * (n_solid + 1) positions) and, with_kappa, the sums of the pass before.
+hipError_t ulaunch_pack(const UGeomDev* g_dev, int n_pos, bool with_kappa, hipStream_t st);
+// every system's pass; slots: LDS slots of a system
+hipError_t ulaunch_pass(const UGeomDev* g_dev, int n_sys, int nin, int wpl, int slots, double inner_tol,
                         double inner_rtol, int max_inner, hipStream_t st);
+// T_L, T_w and the parts of kappa from the systems' solutions
 hipError_t ulaunch_reduce(const UGeomDev* g_dev, int ns, int nwalls, hipStream_t st);
