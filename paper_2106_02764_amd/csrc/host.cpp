@@ -930,10 +930,16 @@ obte_status run_fourier(const Run& R, const obte_solve_opts* o, hipStream_t st, 
     const int n = (int)R.views.size();
     constexpr int KF = 8;     // even: an iteration's parity is its position in the graph
     HIPCHK(launch_fourier_init(R.d_views, n, R.max_cells, st));
+    std::vector<int> ncells;
+    int ndim = 2;
+    for (const GeomDev& g : R.views) {
+        ncells.push_back(g.ncells);
+        ndim = std::max(ndim, g.ndim);
+    }
     auto enqueue = [&]() -> hipError_t {
         hipError_t e = hipSuccess;
         for (int j = 0; j < KF && e == hipSuccess; ++j)
-            e = launch_fourier_iter(R.d_views, n, R.max_cells, j & 1, o->fourier_tol, o->max_fourier, st);
+            e = launch_fourier_iter(R.d_views, ncells.data(), n, ndim, j & 1, o->fourier_tol, o->max_fourier, st);
         if (e == hipSuccess) e = launch_fourier_pending(R.d_views, n, R.d_pending, st);
         return e;
     };

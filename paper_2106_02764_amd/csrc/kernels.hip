@@ -29,6 +29,7 @@
 // a fixed order and a third reduces kappa, so FP64 results are bitwise
 // reproducible (no floating-point atomics).
 #include "device.h"
+#include <climits>
 
 namespace {
 
@@ -542,7 +543,8 @@ __device__ __forceinline__ double fourier_rhs(const GeomDev& g, uint16_t w, cons
     return b;
 }
 
-constexpr int FB_MAX = 256, FB_THREADS = 256;
+// (FGRID_MAX: geometries of one iteration launch, a multiple of 8)
+constexpr int FB_MAX = 256, FB_THREADS = 256, FGRID_MAX = 64;
 
 // This geometry's CG storage (in the fx region) and block b's cell range.
 // r, s = A r and q = A p are double buffered by iteration parity; gp / dp hold
@@ -714,44 +716,81 @@ __global__ void __launch_bounds__(FB_THREADS) k_fourier_s0(const GeomDev* __rest
 // neighbours, which every block forms itself from the unchanged buffers qq.
 // The stop test (every block computes the same sums) is the one of the plain
 // CG: |r_k| <= tol |b|, or max_iter iterations.
-__global__ void __launch_bounds__(FB_THREADS) k_fourier_cg(const GeomDev* __restrict__ geoms, int qq,
-                                                         double tol, int max_iter) {
-    __shared__ double red[40];
-    const GeomDev& g = geoms[blockIdx.y];
-    const FView v = fourier_view(g, blockIdx.x);
-    if ((int)blockIdx.x >= v.B || v.sc[1] != 0.0) return;
+//
+// A block's chain is what it costs: the geometry, the partials and their sum,
+// the cells, the new partials.  So a thread's first cell is loaded before the
+// sums of the partials (its loads need none of the scalars; they are all of
+// its work up to FB_MAX * FB_THREADS cells), a wall face reads the cell itself
+// (its difference is 0) so that no load sits in a branch, and of a batch only
+// the blocks that have cells are launched.  An iteration of the 128 x 128 cell:
+// 6.1 -> 5.2 us; of 24 geometries (517 000 cells, a grid of 6144 blocks for
+// 2017 with cells): 20 -> 16 us, where the 80 bytes a cell would take 8 us.
+struct FGrid {
+    int n, first[FGRID_MAX + 1];  // blocks per XCD before each geometry (INT_MAX past the last)
+};
+
+template <int NF>
+struct FCell {
+    uint16_t w;
+    double r, s, q, p, x, rj[NF], sj[NF], qj[NF];
+};
+
+template <int NF>
+__device__ __forceinline__ void fourier_cells(const GeomDev& g, const FView& v, int qq, double tol, int max_iter,
+                                              double* red, int blk) {
+    const gptr_t<double> r = gview(v.r(qq)), s = gview(v.s(qq)), q = gview(v.q(qq));
+    const gmut_t<double> p = gmut(v.p), x = gmut(v.x);
+    const gmut_t<double> rn = gmut(v.r(qq ^ 1)), sn = gmut(v.s(qq ^ 1)), qn = gmut(v.q(qq ^ 1));
+    const auto fc = gview(g.fc);
+    auto load = [&](int c, FCell<NF>& e) {
+        e.w = fc[c];
+        const int row = c / g.nx;
+        const CellPos cp = NF == 4 ? CellPos{c - row * g.nx, row, 0} : cell_pos(g, c);
+        e.r = r[c];
+        e.s = s[c];
+        e.q = q[c];
+        e.p = p[c];
+        e.x = x[c];
+#pragma unroll
+        for (int f = 0; f < NF; ++f) {
+            const int j = fc_class(e.w, f) == FC_WALL ? c : nbr_cell(g, c, cp, f);
+            e.rj[f] = r[j];
+            e.sj[f] = s[j];
+            e.qj[f] = q[j];
+        }
+    };
+    FCell<NF> e;
+    int c = v.c0 + (int)threadIdx.x;
+    load(min(c, v.n - 1), e);
+    const auto sc = gview(v.sc);
+    const double bn = sc[0], done = sc[1], g1 = sc[8 + (qq ^ 1)], a1 = sc[10 + (qq ^ 1)];
+    const int it = (int)sc[6 + qq];
+    if (done != 0.0) return;
     double gam, del;
     sum_partials2(v.gp(qq), v.dp(qq), v.B, red, gam, del);
-    const int it = (int)v.sc[6 + qq];
-    if (!(sqrt(gam) > tol * v.sc[0]) || it >= max_iter) {
-        if (blockIdx.x == 0 && threadIdx.x == 0) v.sc[1] = 1.0;
+    if (!(sqrt(gam) > tol * bn) || it >= max_iter) {
+        if (blk == 0 && threadIdx.x == 0) v.sc[1] = 1.0;
         return;
     }
     double alpha = gam / del, beta = 0.0;
     if (it > 0) {
-        beta = gam / v.sc[8 + (qq ^ 1)];
-        alpha = gam / (del - beta * gam / v.sc[10 + (qq ^ 1)]);
+        beta = gam / g1;
+        alpha = gam / (del - beta * gam / a1);
     }
     double k0, k1, k2;
     fourier_k(g, k0, k1, k2);
-    const int nf = g.nf;
-    const double *r = v.r(qq), *s = v.s(qq), *qo = v.q(qq);
-    double *rn = v.r(qq ^ 1), *sn = v.s(qq ^ 1), *qn = v.q(qq ^ 1);
     double gs = 0.0, ds = 0.0;
-    for (int c = v.c0 + threadIdx.x; c < v.c1; c += blockDim.x) {
-        const uint16_t w = g.fc[c];
-        const CellPos cp = cell_pos(g, c);
+    for (; c < v.c1;) {
         double rc = 0.0, sa = 0.0, qc = 0.0;
-        if (fc_solid(w)) {
-            const double pc = r[c] + beta * v.p[c];
-            v.p[c] = pc;
-            qc = s[c] + beta * qo[c];
-            v.x[c] += alpha * pc;
-            rc = r[c] - alpha * qc;
-            for (int f = 0; f < nf; ++f) {
-                if (fc_class(w, f) == FC_WALL) continue;
-                const int j = nbr_cell(g, c, cp, f);
-                const double rj = r[j] - alpha * (s[j] + beta * qo[j]);
+        if (fc_solid(e.w)) {
+            const double pc = e.r + beta * e.p;
+            qc = e.s + beta * e.q;
+            p[c] = pc;
+            x[c] = e.x + alpha * pc;
+            rc = e.r - alpha * qc;
+#pragma unroll
+            for (int f = 0; f < NF; ++f) {
+                const double rj = e.rj[f] - alpha * (e.sj[f] + beta * e.qj[f]);
                 sa += axis_pick(k0, k1, k2, f >> 1) * (rc - rj);
             }
         }
@@ -760,18 +799,48 @@ __global__ void __launch_bounds__(FB_THREADS) k_fourier_cg(const GeomDev* __rest
         qn[c] = qc;
         gs += rc * rc;
         ds += rc * sa;
+        c += blockDim.x;
+        if (c < v.c1) load(c, e);
     }
     block_sum2(gs, ds, red);
     if (threadIdx.x == 0) {
-        v.gp(qq ^ 1)[blockIdx.x] = gs;
-        v.dp(qq ^ 1)[blockIdx.x] = ds;
-        if (blockIdx.x == 0) {
+        v.gp(qq ^ 1)[blk] = gs;
+        v.dp(qq ^ 1)[blk] = ds;
+        if (blk == 0) {
             v.sc[8 + qq] = gam;
             v.sc[10 + qq] = alpha;
             v.sc[6 + (qq ^ 1)] = (double)(it + 1);
             v.sc[4] = (double)(it + 1);
         }
     }
+}
+
+// NF: faces of a cell (a batch is all 2D or all 3D).  2D runs
+// with all waves of 517 000 cells resident (64 registers, 8 waves a SIMD).
+template <int NF>
+__global__ void __launch_bounds__(FB_THREADS, NF == 4 ? 8 : 4) k_fourier_cg(const GeomDev* __restrict__ geoms, FGrid fg, int qq,
+                                                         double tol, int max_iter) {
+    __shared__ double red[40];
+    // workgroups go to the eight XCDs in turn: an XCD takes consecutive blocks
+    // of each geometry, so the rows that neighbouring blocks share are in its
+    // L2 (with the blocks dealt out one by one each row was fetched three times)
+    const int b = (int)blockIdx.x / 8, xcd = (int)blockIdx.x % 8;
+    int k = 0;
+    if (fg.n > 1) {
+#pragma unroll
+        for (int i = 8; i < FGRID_MAX; i += 8) k += b >= fg.first[i] ? 8 : 0;
+        int d = 0;
+#pragma unroll
+        for (int i = 1; i < 8; ++i) d += b >= fg.first[k + i] ? 1 : 0;
+        k += d;
+    }
+    const GeomDev& g = geoms[k];
+    const int blk = xcd * (fg.first[k + 1] - fg.first[k]) + b - fg.first[k];
+    const FView v = fourier_view(g, blk);
+    if (blk >= v.B) return;
+    // in a batch, most blocks are soon those of geometries that have ended
+    if (fg.n > 1 && v.sc[1] != 0.0) return;
+    fourier_cells<NF>(g, v, qq, tol, max_iter, red, blk);
 }
 
 // geometries still iterating -> *pending (one block)
@@ -1091,11 +1160,20 @@ hipError_t launch_fourier_init(const GeomDev* geoms_dev, int n_geoms, int max_ce
     return hipGetLastError();
 }
 
-hipError_t launch_fourier_iter(const GeomDev* geoms_dev, int n_geoms, int max_cells, int parity, double tol,
+hipError_t launch_fourier_iter(const GeomDev* geoms_dev, const int* ncells, int n_geoms, int ndim, int parity, double tol,
                                int max_iter, hipStream_t st) {
     (void)hipGetLastError();
-    const dim3 grid(fourier_blocks(max_cells), n_geoms);
-    hipLaunchKernelGGL(k_fourier_cg, grid, dim3(FB_THREADS), 0, st, geoms_dev, parity, tol, max_iter);
+    for (int g0 = 0; g0 < n_geoms; g0 += FGRID_MAX) {
+        FGrid fg;
+        fg.n = n_geoms - g0 < FGRID_MAX ? n_geoms - g0 : FGRID_MAX;
+        int per = 0;
+        for (int k = 0; k <= FGRID_MAX; ++k) {
+            fg.first[k] = k <= fg.n ? per : INT_MAX;
+            if (k < fg.n) per += (fourier_blocks(ncells[g0 + k]) + 7) / 8;
+        }
+        hipLaunchKernelGGL(ndim > 2 ? k_fourier_cg<6> : k_fourier_cg<4>, dim3(8 * per), dim3(FB_THREADS), 0, st,
+                           geoms_dev + g0, fg, parity, tol, max_iter);
+    }
     return hipGetLastError();
 }
 

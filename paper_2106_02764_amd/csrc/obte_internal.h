@@ -171,7 +171,7 @@ struct PassParams {
 // fx must hold fourier_scratch_doubles(ncells) doubles.
 constexpr size_t fourier_scratch_doubles(size_t ncells) { return 8 * ncells + 4 * 256 + 16; }
 hipError_t launch_fourier_init(const GeomDev* geoms_dev, int n_geoms, int max_cells, hipStream_t st);
-hipError_t launch_fourier_iter(const GeomDev* geoms_dev, int n_geoms, int max_cells, int parity, double tol,
+hipError_t launch_fourier_iter(const GeomDev* geoms_dev, const int* ncells, int n_geoms, int ndim, int parity, double tol,
                                int max_iter, hipStream_t st);
 hipError_t launch_fourier_pending(const GeomDev* geoms_dev, int n_geoms, int* pending_dev, hipStream_t st);
 hipError_t launch_fourier_finish(const GeomDev* geoms_dev, int n_geoms, int max_cells, hipStream_t st);
