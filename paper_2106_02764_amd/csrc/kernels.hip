@@ -1491,15 +1491,35 @@ hipError_t launch_reduce_pass(int precision, const GeomDev* geoms_dev, int n_geo
 // The stored wrap inflows stay as they are: re-centred, the next inputs are
 // close to this pass's, whose inflows they hold.  ax[n_aa] carries the shift
 // from the first kernel to the second.
-__global__ void __launch_bounds__(256) k_gauge_mean(const GeomDev* __restrict__ geoms) {
-    __shared__ double red[32];
+//
+// One block of 1024 threads with eight cells of each in flight: it is its
+// loads' latency that counts (96 x 96 cells: 20.5 -> 5 us from 256 threads
+// with one).
+__global__ void __launch_bounds__(1024) k_gauge_mean(const GeomDev* __restrict__ geoms) {
+    __shared__ double red[40];
     const GeomDev& g = geoms[blockIdx.x];
     if (!g.gauge || g.ctrl[CTRL_DONE]) return;
+    const auto T = gview(g.T_L);
+    const auto fc = gview(g.fc);
+    const int nc = g.ncells, bd = blockDim.x;
     double s = 0.0, ns = 0.0;
-    for (int c = threadIdx.x; c < g.ncells; c += blockDim.x)
-        if (fc_solid(g.fc[c])) { s += g.T_L[c]; ns += 1.0; }
-    s = block_sum(s, red);
-    ns = block_sum(ns, red);
+    for (int c0 = threadIdx.x; c0 < nc; c0 += 8 * bd) {
+        double t[8];
+        uint16_t w[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int c = min(c0 + u * bd, nc - 1);
+            t[u] = T[c];
+            w[u] = fc[c];
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (c0 + u * bd < nc && fc_solid(w[u])) {
+                s += t[u];
+                ns += 1.0;
+            }
+    }
+    block_sum2(s, ns, red);
     if (threadIdx.x == 0) g.ax[g.n_aa] = ns > 0.0 ? s / ns : 0.0;
 }
 
@@ -1532,7 +1552,7 @@ __global__ void __launch_bounds__(256) k_gauge_apply(const GeomDev* __restrict__
 
 hipError_t launch_gauge(const GeomDev* geoms_dev, int n_geoms, int max_aa, hipStream_t st) {
     (void)hipGetLastError();
-    hipLaunchKernelGGL(k_gauge_mean, dim3(n_geoms), dim3(256), 0, st, geoms_dev);
+    hipLaunchKernelGGL(k_gauge_mean, dim3(n_geoms), dim3(1024), 0, st, geoms_dev);
     hipLaunchKernelGGL(k_gauge_apply, dim3((max_aa + 255) / 256, n_geoms), dim3(256), 0, st, geoms_dev);
     return hipGetLastError();
 }

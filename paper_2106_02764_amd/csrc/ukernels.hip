@@ -247,52 +247,71 @@ __global__ void __launch_bounds__(UFB) k_uf_cg(const UFourierDev* __restrict__ f
                                                int max_cg) {
     __shared__ double red[4 * 16];
     const UFourierDev& f = *fp;
-    if (f.fsc[0] != 0.0) return;
     const int B = uf_blocks(f.ns);
+    const auto r = gview(q ? f.r1 : f.r), w = gview(q ? f.w1 : f.w0);
+    const auto so = gview(q ? f.s1 : f.s0);   // s of the previous iteration (parity q ^ 1 wrote it here)
+    const auto rn = gmut(q ? f.r : f.r1), wn = gmut(q ? f.w0 : f.w1), sn = gmut(q ? f.s0 : f.s1);
+    const auto dg = gview(f.dg), sc = gview(f.fsc), pt = gview(f.fpart);
+    const auto p = gmut(f.p), T = gmut(f.T);
+    const int i = blockIdx.x * UFB + threadIdx.x, ic = min(i, f.ns - 1);
+    // everything that the iteration reads is asked for before the sums of the
+    // partials, which the scalars wait for (a 5609-cell mesh: 6.8 -> 5.5 us)
+    const double done = sc[0], g1 = sc[6 + (q ^ 1)], a1 = sc[8 + (q ^ 1)];
+    const int it = (int)sc[10 + q];
+    const double ri0 = r[ic], wi0 = w[ic], si0 = so[ic], dgi = dg[ic], pi0 = p[ic], Ti0 = T[ic];
+    const auto nj = gview(f.nb4_j) + (size_t)ic * UFACES;
+    const auto ak = gview(f.nb4_a) + (size_t)ic * UFACES;
+    int jk[UFACES];
+#pragma unroll
+    for (int k = 0; k < UFACES; ++k) jk[k] = nj[k];
+    double na[UFACES], nr[UFACES], nw[UFACES], ns[UFACES], nd[UFACES];
+#pragma unroll
+    for (int k = 0; k < UFACES; ++k) {
+        const int j = jk[k] < 0 ? ic : jk[k];
+        na[k] = ak[k];
+        nr[k] = r[j];
+        nw[k] = w[j];
+        ns[k] = so[j];
+        nd[k] = dg[j];
+    }
     // the four sums of the partials in one exchange (block order, as uf_sum)
     double sm[4] = {0.0, 0.0, 0.0, 0.0};
     if ((int)threadIdx.x < B) {
-        sm[0] = f.fpart[(UP_RR0 + q) * UF_MAXB + threadIdx.x];
-        sm[1] = f.fpart[UP_BB * UF_MAXB + threadIdx.x];
-        sm[2] = f.fpart[(UP_G0 + q) * UF_MAXB + threadIdx.x];
-        sm[3] = f.fpart[(UP_D0 + q) * UF_MAXB + threadIdx.x];
+        sm[0] = pt[(UP_RR0 + q) * UF_MAXB + threadIdx.x];
+        sm[1] = pt[UP_BB * UF_MAXB + threadIdx.x];
+        sm[2] = pt[(UP_G0 + q) * UF_MAXB + threadIdx.x];
+        sm[3] = pt[(UP_D0 + q) * UF_MAXB + threadIdx.x];
     }
+    if (done != 0.0) return;
     block_sum_n(sm, red);
     const double rr = sm[0], bb = sm[1], gam = sm[2], del = sm[3];
-    const int it = (int)f.fsc[10 + q];
     double alpha = gam / del, beta = 0.0;
     if (it > 0) {
-        beta = gam / f.fsc[6 + (q ^ 1)];
-        alpha = gam / (del - beta * gam / f.fsc[8 + (q ^ 1)]);
+        beta = gam / g1;
+        alpha = gam / (del - beta * gam / a1);
     }
     if (!(rr > cg_tol * cg_tol * bb) || it >= max_cg || !(alpha > 0.0) || !isfinite(alpha)) {
         if (blockIdx.x == 0 && threadIdx.x == 0) f.fsc[0] = 1.0;
         return;
     }
-    const double* r = q ? f.r1 : f.r;
-    const double* w = q ? f.w1 : f.w0;
-    const double* so = q ? f.s1 : f.s0;       // s of the previous iteration (parity q ^ 1 wrote it here)
-    double* rn = q ? f.r : f.r1;
-    double* wn = q ? f.w0 : f.w1;
-    double* sn = q ? f.s0 : f.s1;
-    const int i = blockIdx.x * UFB + threadIdx.x;
     double gm = 0.0, dl = 0.0, r2 = 0.0;
     if (i < f.ns) {
-        const double pc = r[i] / f.dg[i] + beta * f.p[i];
-        const double sc = w[i] + beta * so[i];
-        f.p[i] = pc;
-        f.T[i] += alpha * pc;
-        const double ri = r[i] - alpha * sc;
-        const double ui = ri / f.dg[i];
+        const double pc = ri0 / dgi + beta * pi0;
+        const double si = wi0 + beta * si0;
+        p[i] = pc;
+        T[i] = Ti0 + alpha * pc;
+        const double ri = ri0 - alpha * si;
+        const double ui = ri / dgi;
         double wv = 0.0;
-        for (int k = f.nb_ptr[i]; k < f.nb_ptr[i + 1]; ++k) {
-            const int j = f.nb_j[k];
-            const double rj = r[j] - alpha * (w[j] + beta * so[j]);
-            wv += f.nb_a[k] * (ui - rj / f.dg[j]);
+#pragma unroll
+        for (int k = 0; k < UFACES; ++k) {
+            const double rj = nr[k] - alpha * (nw[k] + beta * ns[k]);
+            const double t = wv + na[k] * (ui - rj / nd[k]);
+            wv = jk[k] < 0 ? wv : t;
         }
         rn[i] = ri;
         wn[i] = wv;
-        sn[i] = sc;
+        sn[i] = si;
         gm = ri * ui;
         dl = wv * ui;
         r2 = ri * ri;

@@ -744,6 +744,15 @@ obte_status obte_umesh_material_set(obte_umesh* m, const double* mfp, int n_mfp,
     UP((int**)&fdv.nb_ptr, nb_ptr);
     UP((int**)&fdv.nb_j, nb_j);
     UP((double**)&fdv.nb_a, nb_a);
+    std::vector<int> nb4_j((size_t)ns * UFACES, -1);
+    std::vector<double> nb4_a((size_t)ns * UFACES, 0.0);
+    for (int i = 0; i < ns; ++i)
+        for (int k = nb_ptr[i]; k < nb_ptr[i + 1]; ++k) {
+            nb4_j[(size_t)i * UFACES + k - nb_ptr[i]] = nb_j[k];
+            nb4_a[(size_t)i * UFACES + k - nb_ptr[i]] = nb_a[k];
+        }
+    UP((int**)&fdv.nb4_j, nb4_j);
+    UP((double**)&fdv.nb4_a, nb4_a);
     UP((double**)&fdv.nb_del, nb_del);
     UP((double**)&fdv.nb_w, nb_w);
     UP((int**)&fdv.nb_f, nb_f);
@@ -802,7 +811,9 @@ obte_status obte_umesh_fourier(obte_umesh* m, double tol, int max_outer, double 
     // conjugate gradients end in at most n steps in exact arithmetic; twice
     // that caps a solve whose tolerance sits below the rounding floor
     const int max_cg = 2 * m->ns + 50;
-    constexpr int CG_CHUNK = 16;        // CG iterations queued per read of the stop flag (even)
+    // CG iterations queued per read of the stop flag (even): a read costs some
+    // 20 us, an iteration past the stop 3 us
+    constexpr int CG_CHUNK = 32;
     double* h = m->h_fsc;               // pinned: the loop scalars read back
     for (int outer = 1; outer <= max_outer; ++outer) {
         UHIP(ulaunch_fourier_start(m->fdv, m->ns, m->nf, st));

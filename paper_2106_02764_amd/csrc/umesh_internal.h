@@ -99,6 +99,8 @@ struct UFourierDev {
     const int* nb_ptr;        // ns + 1: neighbour lists (both sides of every interior face)
     const int* nb_j;          // neighbour cell
     const double* nb_a;       // primary coefficient A_f n.K n / (n.d)
+    const int* nb4_j;         // UFACES * ns: the neighbours again, -1 past a cell's last
+    const double* nb4_a;      // their coefficients
     const double* nb_del;     // jump of the neighbour's image seen from the cell
     const double* nb_w;       // 2 per entry: least-squares weight column of the entry
     const int* nb_f;          // face index * 2 + (1 if the cell is the face's second cell)
