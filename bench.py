@@ -62,8 +62,8 @@ REF = dict(precision=0, outer_tol=1e-10, stop_rule=0, accel=8, inner_tol=1e-12, 
 # operating point, per launch (rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE over one
 # solve, each scaled by the same counter on a plain 256 MiB copy); valid only
 # for the kernel source it was taken on.
-TRAFFIC = {"kernels_sha256": "a4b87ad98d042e1c01d43d6cddb813d4e054cb9f3ba34e262d5b502025d0f9b5",
-           "fetch_bytes": 15430209, "write_bytes": 59392513}
+TRAFFIC = {"kernels_sha256": "12e313a2996f56a328540116690d31735e97aaffaad56b1fed37fb069ccee434",
+           "fetch_bytes": 27375701, "write_bytes": 89442336}
 
 
 def parse():
@@ -86,8 +86,14 @@ def parse():
 
 
 def kernels_sha():
-    with open(os.path.join(ROOT, "paper_2106_02764_amd", "csrc", "kernels.hip"), "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()
+    """Of the structured path's device sources, in name order."""
+    src = os.path.join(ROOT, "paper_2106_02764_amd", "csrc")
+    h = hashlib.sha256()
+    for name in sorted(os.listdir(src)):
+        if name.endswith((".hip", ".h")) and not name.startswith("u"):
+            with open(os.path.join(src, name), "rb") as f:
+                h.update(f.read())
+    return h.hexdigest()
 
 
 def copy_probe(nbytes):

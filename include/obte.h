@@ -382,7 +382,7 @@ typedef struct obte_umesh obte_umesh;   /* opaque handle */
  * and for clockwise or degenerate cells, sizes out of range or no solid
  * cell).  The applied difference dT > 0 is along grad_axis (0 = x, 1 = y),
  * with T(x + L) = T(x) - dT across the periodic plane.  Limits: at most
- * 8192 solid cells (a system's solution lives in one workgroup's LDS). */
+ * 8192 solid cells (a system's solution goes through one workgroup's LDS). */
 obte_status obte_umesh_create(const double* nodes, int n_nodes, const int* cells, const int* shifts,
                               int n_cells, int nv, const unsigned char* solid, double Lx, double Ly,
                               int grad_axis, double dT, obte_umesh** out);
@@ -390,8 +390,8 @@ obte_status obte_umesh_create(const double* nodes, int n_nodes, const int* cells
 /* Material weights on the vectorial-MFP grid (section Model, Appendix A):
  * mfp (n_mfp), in-plane unit directions dirs (n_dir x 2), weights dir_w
  * (summing to 1), per-MFP conductivity kappa_m; all host.  Builds the
- * per-direction sweep order: the cells sorted into upwind levels with the
- * periodic faces cut (OBTE_ERR_ARG if the upwind graph of some direction has
+ * per-direction sweep order: the cells in rows of at most 64 that read only
+ * cells of earlier rows, the periodic faces cut (OBTE_ERR_ARG if the upwind graph of some direction has
  * a cycle, which convex cells do not produce). */
 obte_status obte_umesh_material_set(obte_umesh* mesh, const double* mfp, int n_mfp, const double* dirs,
                                     const double* dir_w, int n_dir, const double* kappa_m);

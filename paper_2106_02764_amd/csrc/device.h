@@ -41,8 +41,8 @@ __device__ __forceinline__ double readlane(double v, int l) {
 
 // Sum over the wave, the same value in every lane.  The lanes are combined by
 // DPP row shifts and broadcasts (a step is two moves and an add, where the
-// LDS permutes of a butterfly cost their latency each: 0.15 against 0.35 us
-// for a double), in a fixed order.
+// LDS permutes of a butterfly cost their latency each: the pass of a 32 x 32
+// FP64 cell, whose sweeps are short, 54 -> 46.8 us), in a fixed order.
 template <int CTRL, int RM, typename T>
 __device__ __forceinline__ void sum_step(T& v) { v += dpp<CTRL, RM>(v, T(0)); }
 template <typename T>

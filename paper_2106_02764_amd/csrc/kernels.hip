@@ -8,26 +8,25 @@
 // reduces the solutions into T_L = sum D x, the diffuse-wall temperatures
 // T_w and kappa.
 //
-// Inner solve.  Ordering the cells of a structured grid in upwind order makes
-// A_l lower triangular except for the periodic wrap couplings.  One wavefront
-// owns one (m,l) system and sweeps the grid row by row in y-upwind order
-// (and plane by plane in z-upwind order in 3D); inside a row the x-recurrence
-// x_i = a_i + q_i x_{i-1}, cyclic when x is periodic, is solved exactly with a
-// wavefront-wide scan of affine maps.  The sweep M^{-1} is therefore exact up
-// to the y-wrap coupling E (row 0 <- last row).  BiCGSTAB right-preconditioned
-// by the sweep works on A M^{-1} = I - E M^{-1}: its Krylov vectors are
-// supported on the wrap row only, so they are nx*nz values held in the
-// wavefront's registers and every dot product is a wavefront reduction.
-// Each matrix-vector product is one sweep whose only source is the wrap row.
-// No per-(cell,system) vector is ever stored: b is formed on the fly from the
-// per-cell T_L / T_w tables shared by all systems.
+// Inner solve (sweep2d.h, sweep3d.h, rows.h).  Ordering the cells of a
+// structured grid in upwind order makes A_l lower triangular except for the
+// periodic wrap couplings.  One wavefront owns one (m,l) system and sweeps the
+// grid row by row in upwind order (and plane by plane in z-upwind order in
+// 3D); 2D rows run along the axis that the direction crosses more often, 3D
+// rows along x.  Inside a row the recurrence x_i = a_i + q_i x_{i-1}, cyclic
+// when its axis is periodic, is solved exactly with a wavefront-wide scan of
+// affine maps.  The sweep M^{-1} is therefore exact up to the wrap coupling E
+// (first row <- last row).  BiCGSTAB right-preconditioned by the sweep works
+// on A M^{-1} = I - E M^{-1}: its Krylov vectors are supported on the wrap row
+// only (2D: held in the wavefront's registers; 3D: a plane per vector) and
+// every dot product is a wavefront reduction.  Each matrix-vector product is
+// one sweep whose only source is the wrap row.  A system stores its solution
+// on the solid cells; b is formed on the fly from tables shared by all
+// systems.
 //
-// Reductions.  The systems of one workgroup share a direction and run their
-// final sweep in lockstep; per row they combine D x (T_L), the outgoing wall
-// weights (T_w) and S x (flux) through LDS in a fixed order and write one
-// partial per workgroup.  A second kernel sums the partials per cell / wall in
-// a fixed order and a third reduces kappa, so FP64 results are bitwise
-// reproducible (no floating-point atomics).
+// Reductions.  One kernel sums the stored solutions per cell and wall in a
+// fixed order, another reduces kappa, so FP64 results are bitwise reproducible
+// (no floating-point atomics).
 #include "device.h"
 #include <climits>
 

@@ -99,9 +99,8 @@ __device__ __forceinline__ void load_mask(mview_t row, RowMask<CPL, S1, ADJB, D3
 // scan's weights (Q of the segment a lane holds before each step) are powers
 // of q, zero where the segment holds a closed face: constants selected by the
 // row's masks.  Only the affine part is scanned: 35 vector instructions per
-// FP32 row of 2 cells per lane, against 57 when Q is scanned along (0.156 ->
-// 0.10 us per row of a wave alone on its SIMD).  The powers are formed in
-// double from P = 1 - Q by P_{a+b} = P_a + (1 - P_a) P_b, which keeps P's
+// FP32 row of 2 cells per lane, against 57 when Q is scanned along.  The powers
+// are formed in double from P = 1 - Q by P_{a+b} = P_a + (1 - P_a) P_b, which keeps P's
 // relative accuracy where it is small (the closure divides by it).
 // ---------------------------------------------------------------------------
 template <typename T, int CPL, bool FULL>

@@ -1,5 +1,5 @@
 // Host driver of the unstructured-mesh path: polygon geometry and face
-// lists, material weights, the per-direction upwind order, the tables of
+// lists, material weights, the rows of each direction's sweep, the tables of
 // the non-orthogonal heat-conduction solve, and Algorithm 1's outer loop.
 //
 // Geometry (plain definitions): polygon area by the shoelace formula, the
@@ -44,7 +44,7 @@ obte_status ufail(obte_status st, const char* fmt, ...) {
             return ufail(OBTE_ERR_HIP, "%s failed: %s", #call, hipGetErrorString(e_));   \
     } while (0)
 
-constexpr int MAX_SOLID = 8192;     // with the wrap slots: one workgroup's 64 KiB of LDS
+constexpr int MAX_SOLID = 8192;     // a solution goes through one workgroup's 64 KiB of LDS
 static_assert(MAX_SOLID <= 256 * UF_MAXB, "heat-conduction partials: one slot per block of 256 cells");
 
 }  // namespace
