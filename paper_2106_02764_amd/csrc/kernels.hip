@@ -994,41 +994,82 @@ __global__ void __launch_bounds__(256) k_sigma_min(const GeomDev* __restrict__ g
 }
 
 // Flux map of one geometry from the stored solutions of the replayed last
-// sweep: J_i = sum_ml S_ml x_iml (one thread per cell, systems in order).
+// sweep: J_i = sum_ml S_ml x_iml.
+// (the flux and the gradient: a block takes 64 cells, its FQ waves fixed chunks
+// of the systems with eight loads of each in flight, combined in order; with a
+// thread per cell for all systems a quarter of the CUs had a block, and one
+// load each: 128 x 128 cells, 1440 systems, FP64: flux 389 -> 46 us, gradient
+// 628 -> 64 us)
+constexpr int FQ = 16;
+
 template <typename T>
-__global__ void __launch_bounds__(256) k_flux(const GeomDev* __restrict__ gp, double* J_out) {
+__global__ void __launch_bounds__(64 * FQ) k_flux(const GeomDev* __restrict__ gp, double* J_out) {
+    __shared__ double part[3][FQ][64];
     const GeomDev& g = *gp;
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= g.ncells) return;
-    const int i = g.sidx[c];
-    const gptr_t<T> X = gview(reinterpret_cast<const T*>(g.X));
+    const int q = threadIdx.x >> 6, cl = threadIdx.x & 63, nd = g.ndim;
+    const int c = blockIdx.x * 64 + cl;
+    const bool in = c < g.ncells;
+    const int i = in ? g.sidx[c] : -1;
+    const gptr_t<T> X = gview(reinterpret_cast<const T*>(g.X)) + max(i, 0);
+    const gptr_t<double> S = gview(g.S);
+    const size_t xs = g.xs;
+    const int per = (g.n_sys + FQ - 1) / FQ, s0 = q * per, s1 = min(g.n_sys, s0 + per);
     double j[3] = {0.0, 0.0, 0.0};
-    if (i >= 0)
-        for (int sys = 0; sys < g.n_sys; ++sys) {
-            const double x = (double)X[(size_t)sys * g.xs + i];
+    for (int k = s0; k < s1; k += 8) {
+        double x[8];
 #pragma unroll
-            for (int a = 0; a < 3; ++a) j[a] += g.S[sys * 3 + a] * x;
-        }
-    for (int a = 0; a < g.ndim; ++a) J_out[(size_t)c * g.ndim + a] = j[a];
+        for (int u = 0; u < 8; ++u) x[u] = (double)X[(size_t)min(k + u, s1 - 1) * xs];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (k + u < s1)
+#pragma unroll
+                for (int a = 0; a < 3; ++a) j[a] += S[(k + u) * 3 + a] * x[u];
+    }
+#pragma unroll
+    for (int a = 0; a < 3; ++a) part[a][q][cl] = j[a];
+    __syncthreads();
+    if (q >= nd || !in) return;            // wave a sums axis a
+    double t = 0.0;
+#pragma unroll
+    for (int u = 0; u < FQ; ++u) t += part[q][u][cl];
+    J_out[(size_t)c * nd + q] = i >= 0 ? t : 0.0;
 }
 
 // Adjoint gradient of one geometry: -sum_ml lambda_iml (T_iml - T_L,i) from
 // the stored adjoint solutions and the stored forward state.
 template <typename T>
-__global__ void __launch_bounds__(256) k_grad(const GeomDev* __restrict__ gp, double* grad_out) {
+__global__ void __launch_bounds__(64 * FQ) k_grad(const GeomDev* __restrict__ gp, double* grad_out) {
+    __shared__ double part[FQ][64];
     const GeomDev& g = *gp;
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= g.ncells) return;
-    const int i = g.sidx[c];
-    const gptr_t<T> X = gview(reinterpret_cast<const T*>(g.X));
-    const double tl = g.T_L[c];
+    const int q = threadIdx.x >> 6, cl = threadIdx.x & 63;
+    const int c = blockIdx.x * 64 + cl;
+    const bool in = c < g.ncells;
+    const int i = in ? g.sidx[c] : -1;
+    const gptr_t<T> X = gview(reinterpret_cast<const T*>(g.X)) + max(i, 0);
+    const gptr_t<double> F = gview(g.Tstore) + max(i, 0);
+    const double tl = g.T_L[in ? c : 0];
+    const size_t xs = g.xs;
+    const int per = (g.n_sys + FQ - 1) / FQ, s0 = q * per, s1 = min(g.n_sys, s0 + per);
     double acc = 0.0;
-    if (i >= 0)
-        for (int sys = 0; sys < g.n_sys; ++sys) {
-            const size_t e = (size_t)sys * g.xs + i;
-            acc += (double)X[e] * (g.Tstore[e] - tl);
+    for (int k = s0; k < s1; k += 8) {
+        double x[8], f[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const size_t e = (size_t)min(k + u, s1 - 1) * xs;
+            x[u] = (double)X[e];
+            f[u] = F[e];
         }
-    grad_out[c] = i >= 0 ? -acc : 0.0;
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (k + u < s1) acc += x[u] * (f[u] - tl);
+    }
+    part[q][cl] = acc;
+    __syncthreads();
+    if (q != 0 || !in) return;
+    double t = 0.0;
+#pragma unroll
+    for (int u = 0; u < FQ; ++u) t += part[u][cl];
+    grad_out[c] = i >= 0 ? -t : 0.0;
 }
 
 // Energy balance of the last pass (paper, section Model: T_L is fixed by
@@ -1633,15 +1674,15 @@ hipError_t launch_prep_sigma(const GeomDev* g_dev, int ncells, const double* sig
 hipError_t launch_output(const GeomDev* geom_dev, int precision, int ncells, double* T_L_out, double* J_out,
                          double* grad_out, hipStream_t st) {
     (void)hipGetLastError();
-    const dim3 grid((ncells + 255) / 256);
+    const dim3 grid((ncells + 63) / 64), block(64 * FQ);
     if (T_L_out) hipLaunchKernelGGL(k_output, dim3(1), dim3(1024), 0, st, geom_dev, T_L_out);
     if (J_out) {
-        if (precision == 1) hipLaunchKernelGGL(k_flux<float>, grid, dim3(256), 0, st, geom_dev, J_out);
-        else hipLaunchKernelGGL(k_flux<double>, grid, dim3(256), 0, st, geom_dev, J_out);
+        if (precision == 1) hipLaunchKernelGGL(k_flux<float>, grid, block, 0, st, geom_dev, J_out);
+        else hipLaunchKernelGGL(k_flux<double>, grid, block, 0, st, geom_dev, J_out);
     }
     if (grad_out) {
-        if (precision == 1) hipLaunchKernelGGL(k_grad<float>, grid, dim3(256), 0, st, geom_dev, grad_out);
-        else hipLaunchKernelGGL(k_grad<double>, grid, dim3(256), 0, st, geom_dev, grad_out);
+        if (precision == 1) hipLaunchKernelGGL(k_grad<float>, grid, block, 0, st, geom_dev, grad_out);
+        else hipLaunchKernelGGL(k_grad<double>, grid, block, 0, st, geom_dev, grad_out);
     }
     return hipGetLastError();
 }
