@@ -29,22 +29,31 @@ constexpr int UF_THREADS = 1024;
 // a rotation in a row of 16 lanes brings the same partner as the exchange
 // would: moves within the vector unit, where LDS permutes take their latency
 // six times in a row.
-__device__ __forceinline__ double ubutterfly_sum(double v) {
-    auto swap = [](double a, bool half) {
-        const unsigned lo = (unsigned)__double2loint(a), hi = (unsigned)__double2hiint(a);
-        const auto l = half ? __builtin_amdgcn_permlane32_swap(lo, lo, false, false)
-                            : __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
-        const auto h = half ? __builtin_amdgcn_permlane32_swap(hi, hi, false, false)
-                            : __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
-        return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
-    };
-    v = swap(v, true);
-    v = swap(v, false);
+struct UPair {
+    double x, y;          // of the even and of the odd half (or row pair), in both
+};
+template <bool HALF>
+__device__ __forceinline__ UPair uswap(double a) {
+    const unsigned lo = (unsigned)__double2loint(a), hi = (unsigned)__double2hiint(a);
+    const auto l = HALF ? __builtin_amdgcn_permlane32_swap(lo, lo, false, false)
+                        : __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+    const auto h = HALF ? __builtin_amdgcn_permlane32_swap(hi, hi, false, false)
+                        : __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+    return {__hiloint2double((int)h[0], (int)l[0]), __hiloint2double((int)h[1], (int)l[1])};
+}
+// the steps after the first
+__device__ __forceinline__ double ubutterfly_half(double v) {
+    const UPair q = uswap<false>(v);
+    v = q.x + q.y;
     v += dpp<0x128, 0xf>(v, 0.0);      // row_ror:8, 4, 2, 1
     v += dpp<0x124, 0xf>(v, 0.0);
     v += dpp<0x122, 0xf>(v, 0.0);
     v += dpp<0x121, 0xf>(v, 0.0);
     return v;
+}
+__device__ __forceinline__ double ubutterfly_sum(double v) {
+    const UPair h = uswap<true>(v);
+    return ubutterfly_half(h.x + h.y);
 }
 
 __device__ __forceinline__ double wave_max(double v) {
@@ -622,6 +631,23 @@ __device__ __forceinline__ double udot(const double (&a)[WPL], const double (&b)
     return ubutterfly_sum(v);
 }
 
+// |a|^2.  With one value a lane its square goes into the first step's sum
+// unrounded (an FMA, so each half of the wave has its own last bit): the wrap
+// solves amplify it, so it is written out here and not left to the compiler's
+// contraction, and decisions are taken for the whole wave (uyes).
+template <int WPL>
+__device__ __forceinline__ double unorm2(const double (&a)[WPL]) {
+    if constexpr (WPL == 1) {
+        const UPair h = uswap<true>(a[0] * a[0]);
+        return ubutterfly_half(fma(a[0], a[0], threadIdx.x < 32 ? h.y : h.x));
+    } else {
+        return udot(a, a);
+    }
+}
+
+// the first lane's answer
+__device__ __forceinline__ bool uyes(bool b) { return __builtin_amdgcn_readfirstlane((int)b) != 0; }
+
 template <int WPL, int NIN>
 __global__ void __launch_bounds__(WAVE) k_upass(const UGeomDev* __restrict__ gp, double inner_tol, double inner_rtol,
                                                 int max_inner) {
@@ -682,13 +708,13 @@ __global__ void __launch_bounds__(WAVE) k_upass(const UGeomDev* __restrict__ gp,
             if (q < s.nw) ez[k] += wdel[q];
             r[k] = ez[k] - u[k];
         }
-        scale = sqrt(udot(ez, ez));
-        rn = sqrt(udot(r, r));
+        scale = sqrt(unorm2(ez));
+        rn = sqrt(unorm2(r));
         // this pass's target: inner_tol relative to the inflow, or (forcing
         // term) a cut by inner_rtol of the residual the pass started from; the
         // rest carries into the next pass through U
         const double thr = fmax(inner_tol * scale, inner_rtol * rn);
-        if (!(s.nw > 0 && scale > 0.0 && rn > thr)) {
+        if (!uyes(s.nw > 0 && scale > 0.0 && rn > thr)) {
             if (store) break;
             store = true;                   // the same sweep again, stored
             corrected = true;
@@ -704,10 +730,10 @@ __global__ void __launch_bounds__(WAVE) k_upass(const UGeomDev* __restrict__ gp,
         int restarts = 0;
         for (int it = 0; it < max_inner; ++it) {
             double rho = udot(rh, r);
-            if (fabs(rho) <= 1e-30 * rn * rn || !(omega != 0.0)) {
+            if (uyes(fabs(rho) <= 1e-30 * rn * rn || !(omega != 0.0))) {
 #pragma unroll
                 for (int k = 0; k < WPL; ++k) { rh[k] = r[k]; p[k] = 0.0; v[k] = 0.0; }
-                rho = udot(r, r);
+                rho = unorm2(r);
                 rho_old = 1.0; alpha = 1.0; omega = 1.0;
             }
             const double beta = (rho / rho_old) * (alpha / omega);
@@ -719,8 +745,8 @@ __global__ void __launch_bounds__(WAVE) k_upass(const UGeomDev* __restrict__ gp,
 #pragma unroll
             for (int k = 0; k < WPL; ++k) v[k] = p[k] - gx[k];
             const double rv = udot(rh, v);
-            if (!isfinite(rv)) break;
-            if (!(fabs(rv) > 1e-30 * fabs(rho))) {
+            if (!uyes(isfinite(rv))) break;
+            if (!uyes(fabs(rv) > 1e-30 * fabs(rho))) {
                 if (restarts++ >= 4) break;
                 omega = 0.0;
                 continue;
@@ -728,12 +754,12 @@ __global__ void __launch_bounds__(WAVE) k_upass(const UGeomDev* __restrict__ gp,
             alpha = rho / rv;
 #pragma unroll
             for (int k = 0; k < WPL; ++k) sv[k] = r[k] - alpha * v[k];
-            const double sn = sqrt(udot(sv, sv));
+            const double sn = sqrt(unorm2(sv));
             ++its;
-            if (sn <= thr) {
+            if (uyes(sn <= thr)) {
 #pragma unroll
                 for (int k = 0; k < WPL; ++k) e[k] += alpha * p[k];
-                if (sn < best) {
+                if (uyes(sn < best)) {
                     best = sn;
 #pragma unroll
                     for (int k = 0; k < WPL; ++k) eb[k] = e[k];
@@ -745,22 +771,23 @@ __global__ void __launch_bounds__(WAVE) k_upass(const UGeomDev* __restrict__ gp,
             ugather(x, up, gx);
 #pragma unroll
             for (int k = 0; k < WPL; ++k) tt[k] = sv[k] - gx[k];
-            const double t2 = udot(tt, tt);
-            omega = t2 > 0.0 ? udot(tt, sv) / t2 : 0.0;
+            const double t2 = unorm2(tt);
+            const double ts = udot(tt, sv);
+            omega = t2 > 0.0 ? ts / t2 : 0.0;
 #pragma unroll
             for (int k = 0; k < WPL; ++k) {
                 e[k] += alpha * p[k] + omega * sv[k];
                 r[k] = sv[k] - omega * tt[k];
             }
-            rn = sqrt(udot(r, r));
+            rn = sqrt(unorm2(r));
             rho_old = rho;
-            if (!isfinite(rn)) break;
-            if (rn < best) {
+            if (!uyes(isfinite(rn))) break;
+            if (uyes(rn < best)) {
                 best = rn;
 #pragma unroll
                 for (int k = 0; k < WPL; ++k) eb[k] = e[k];
             }
-            if (rn <= thr) break;
+            if (uyes(rn <= thr)) break;
         }
         rn = best;
         // ---- the corrected inflow
