@@ -30,6 +30,19 @@ __device__ __forceinline__ double dpp(double v, double old) {
     const int hi = __builtin_amdgcn_update_dpp((int)(o >> 32), (int)(b >> 32), CTRL, RM, 0xf, false);
     return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
+// the same over all lanes, 0 to a lane without a source (no register is set to
+// 0 before)
+template <int CTRL>
+__device__ __forceinline__ float dpp0(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp0(double v) {
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xf, 0xf, true);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
 __device__ __forceinline__ float readlane(float v, int l) {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
 }
@@ -39,12 +52,37 @@ __device__ __forceinline__ double readlane(double v, int l) {
     return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 
+// The masks of a row's scan (sigma = 1), from the lanes g whose cells' inflow
+// along the row is open: brk[k], the lanes whose segment before scan step k has
+// no closed inflow (right in the lanes that the step writes); om, the lanes
+// reached from the row's start without one; nb, all ones when the row has none.
+// A run of 2^k lanes by doubling; a run from a segment's start is the ones
+// below the carry of + 1.
+struct ScanMask {
+    unsigned long long brk[6], om, nb;
+};
+__device__ __forceinline__ uint32_t run_up(uint32_t g) { return g & ~(g + 1u); }
+__device__ __forceinline__ void scan_mask(unsigned long long g, ScanMask& m) {
+    m.brk[0] = g;
+    m.brk[1] = g & (g << 1);
+    m.brk[2] = m.brk[1] & (m.brk[1] << 2);
+    m.brk[3] = m.brk[2] & (m.brk[2] << 4);
+    const uint32_t lo = (uint32_t)g, hi = (uint32_t)(g >> 32);
+    m.brk[4] = ((unsigned long long)run_up(hi | 0xffffu) << 32) | run_up(lo | 0xffffu);   // read in rows 1, 3
+    m.brk[5] = (unsigned long long)run_up(hi) << 32;                                      // read in rows 2, 3
+    m.om = g & ~(g + 1);
+    m.nb = (unsigned long long)((long long)m.om >> 63);
+}
+
 // Sum over the wave, the same value in every lane.  The lanes are combined by
 // DPP row shifts and broadcasts (a step is two moves and an add, where the
 // LDS permutes of a butterfly cost their latency each: the pass of a 32 x 32
 // FP64 cell, whose sweeps are short, 54 -> 46.8 us), in a fixed order.
 template <int CTRL, int RM, typename T>
-__device__ __forceinline__ void sum_step(T& v) { v += dpp<CTRL, RM>(v, T(0)); }
+__device__ __forceinline__ void sum_step(T& v) {
+    if constexpr (RM == 0xf) v += dpp0<CTRL>(v);
+    else v += dpp<CTRL, RM>(v, T(0));
+}
 template <typename T>
 __device__ __forceinline__ T wave_sum(T v) {
     sum_step<0x111, 0xf>(v);   // row_shr:1

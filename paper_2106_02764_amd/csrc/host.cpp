@@ -363,7 +363,7 @@ size_t table_lead(const obte_mesh* m) { return ROW_SLACK * std::max(row_records(
 size_t row3_bytes(const obte_mesh* m, size_t tsz) { return ((size_t)m->nx * (8 * tsz + 4) + 15) / 16 * 16; }
 
 // words of one row's lane masks
-size_t mask_words(const obte_mesh* m) { return m->nz > 1 ? row_mask_words3(m->q_cpl) : row_mask_words(m->q_cpl); }
+size_t mask_words(const obte_mesh* m) { return row_mask_words(m->q_cpl, m->nz > 1); }
 
 // Stride of one system's wrap inflow (tr: rows along y are in use).
 size_t wrap_stride(const obte_mesh* m, bool tr) {

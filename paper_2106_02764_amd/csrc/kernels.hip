@@ -1357,65 +1357,61 @@ __global__ void __launch_bounds__(256) k_pack_static(const GeomDev* __restrict__
 // Lane masks of every sweep row (one wave per sweep orientation and row; o:
 // rows along y; 2D: orientations by the directions along and across the rows;
 // 3D: by x, y and the order of the rows: y, z or y, reversed z, in which the
-// sweep then runs forwards or backwards): row_mask_words(cpl) words, [0..5]
-// the lanes whose segment before scan step k has no cell closed to its inflow
-// along the row, [6] the lanes reached from the row's start without one, [7]
-// all ones when the row has none, then per cell of a lane: inflow along the
+// sweep then runs forwards or backwards), per cell of a lane: inflow along the
 // row open (set in the padding), inflow across the rows open, 3D: inflow
-// through the z face open, solid.
-__global__ void __launch_bounds__(64) k_row_masks(const uint16_t* __restrict__ fc, int nx, int ny, int nz, int cpl, int o,
-                                                  unsigned long long* __restrict__ out) {
-    const int d3 = nz > 1, nr = o ? ny : nx, nw = o ? nx : ny * nz;
-    const int row = blockIdx.x % nw, tab = blockIdx.x / nw;
-    const int negr = d3 ? tab >> 2 : tab >> 1, negw = d3 ? (tab >> 1) & 1 : tab & 1, zrev = d3 ? tab & 1 : 0;
-    const int lane = threadIdx.x, pad = WAVE * cpl - nr, fr = 2 * o, fw = 2 - fr;
-    const int iz = d3 ? (zrev ? nz - 1 - row % nz : row % nz) : 0;
-    const int fz = 4 + (zrev ? 1 - negw : negw);       // '-' face of a sweep towards + z
-    unsigned long long* w = out + (size_t)blockIdx.x * (d3 ? row_mask_words3(cpl) : row_mask_words(cpl));
-    bool ok = true;
-    for (int c = 0; c < cpl; ++c) {
-        const int p = lane * cpl + c - pad;
-        bool xo = true, yo = false, zo = false, sol = false;
-        if (p >= 0) {
-            const int pp = negr ? nr - 1 - p : p;
-            const uint16_t v = fc[o ? pp * nx + row : (d3 ? row / nz + ny * iz : row) * nx + pp];
-            sol = fc_solid(v);
-            xo = sol && fc_class(v, fr + negr) != FC_WALL;
-            yo = sol && fc_class(v, fw + negw) != FC_WALL;
-            zo = sol && d3 && fc_class(v, fz) != FC_WALL;
+// through the z face open; solid; and (row_mask_scan) the scan's masks.
+__global__ void __launch_bounds__(256) k_row_masks(const uint16_t* __restrict__ fc, int nx, int ny, int nz, int cpl, int o,
+                                                   unsigned long long* __restrict__ out) {
+    const bool d3 = nz > 1;
+    const int nr = o ? ny : nx, nw = o ? nx : ny * nz, words = row_mask_words(cpl, d3);
+    const int lane = threadIdx.x & 63, pad = WAVE * cpl - nr, fr = 2 * o, fw = 2 - fr;
+    const size_t n = (size_t)(d3 ? 8 : 4) * nw;
+    for (size_t r = (size_t)blockIdx.x * 4 + (threadIdx.x >> 6); r < n; r += (size_t)gridDim.x * 4) {
+        const int tab = (int)(r / nw), row = (int)(r - (size_t)tab * nw);
+        const int negr = d3 ? tab >> 2 : tab >> 1, negw = d3 ? (tab >> 1) & 1 : tab & 1, zrev = d3 ? tab & 1 : 0;
+        const int iz = d3 ? (zrev ? nz - 1 - row % nz : row % nz) : 0;
+        const int fz = 4 + (zrev ? 1 - negw : negw);       // '-' face of a sweep towards + z
+        unsigned long long* w = out + r * words;
+        unsigned long long good = ~0ull;
+        for (int c = 0; c < cpl; ++c) {
+            const int p = lane * cpl + c - pad;
+            bool xo = true, yo = false, zo = false, sol = false;
+            if (p >= 0) {
+                const int pp = negr ? nr - 1 - p : p;
+                const uint16_t v = fc[o ? pp * nx + row : (d3 ? row / nz + ny * iz : row) * nx + pp];
+                sol = fc_solid(v);
+                xo = sol && fc_class(v, fr + negr) != FC_WALL;
+                yo = sol && fc_class(v, fw + negw) != FC_WALL;
+                zo = sol && d3 && fc_class(v, fz) != FC_WALL;
+            }
+            const unsigned long long bx = __ballot(xo), by = __ballot(yo), bz = __ballot(zo), bs = __ballot(sol);
+            good &= bx;
+            if (lane == 0) {
+                w[c] = bx;
+                w[cpl + c] = by;
+                if (d3) w[2 * cpl + c] = bz;
+                w[(d3 ? 3 : 2) * cpl + c] = bs;
+            }
         }
-        ok = ok && xo;
-        const unsigned long long bx = __ballot(xo), by = __ballot(yo), bz = __ballot(zo), bs = __ballot(sol);
-        if (lane == 0) {
-            w[8 + c] = bx;
-            w[8 + cpl + c] = by;
-            if (d3) w[8 + 2 * cpl + c] = bz;
-            w[8 + (d3 ? 3 : 2) * cpl + c] = bs;
+        if (row_mask_scan(cpl, d3)) {
+            ScanMask m;
+            scan_mask(good, m);
+            if (lane == 0) {
+                for (int k = 0; k < 6; ++k) w[4 * cpl + k] = m.brk[k];
+                w[4 * cpl + 6] = m.om;
+                w[4 * cpl + 7] = m.nb;
+            }
         }
     }
-    const unsigned long long good = __ballot(ok);
-    // lanes lo..lane all open
-    auto run = [&](int lo) {
-        const int len = lane - lo + 1;
-        const unsigned long long m = (len >= 64 ? ~0ull : (1ull << len) - 1ull) << lo;
-        return (good & m) == m;
-    };
-    bool f[7];
-    for (int k = 0; k < 4; ++k) f[k] = (lane & 15) >= (1 << k) && run(lane - (1 << k) + 1);
-    f[4] = (lane & 16) && run(lane & ~15);
-    f[5] = (lane & 32) && run(32);
-    f[6] = run(0);
-    for (int k = 0; k < 7; ++k) {
-        const unsigned long long b = __ballot(f[k]);
-        if (lane == 0) w[k] = b;
-    }
-    if (lane == 0) w[7] = good == ~0ull ? ~0ull : 0ull;
 }
 
 hipError_t launch_row_masks(const uint16_t* fc, int nx, int ny, int nz, int cpl, int o, unsigned long long* out,
                             hipStream_t st) {
     (void)hipGetLastError();
-    hipLaunchKernelGGL(k_row_masks, dim3((nz > 1 ? 8 : 4) * (o ? nx : ny * nz)), dim3(64), 0, st, fc, nx, ny, nz, cpl, o, out);
+    // four rows a block, at most 2^16 blocks (grid-stride)
+    const size_t n = (size_t)(nz > 1 ? 8 : 4) * (o ? nx : (size_t)ny * nz), blocks = (n + 3) / 4;
+    hipLaunchKernelGGL(k_row_masks, dim3((unsigned)(blocks < 65536 ? blocks : 65536)), dim3(256), 0, st, fc, nx, ny, nz, cpl, o,
+                       out);
     return hipGetLastError();
 }
 

@@ -136,9 +136,12 @@ constexpr size_t tr_tile_bytes(int cpl) { return 64 * (64 * (size_t)cpl + 4); }
 // this many rows of slack before and behind them, the store offsets by cell
 // as many entries.
 constexpr int ROW_SLACK = 4, OFF_SLACK = 16;
-// words of one row's lane masks
-__host__ __device__ constexpr int row_mask_words(int cpl) { return 8 + 3 * cpl; }
-__host__ __device__ constexpr int row_mask_words3(int cpl) { return 8 + 4 * cpl; }
+// words of one row's lane masks: per face and cell of a lane, and (row_mask_scan)
+// the scan's
+__host__ __device__ constexpr bool row_mask_scan(int cpl, bool d3) { return d3 && cpl >= 3; }
+__host__ __device__ constexpr int row_mask_words(int cpl, bool d3) {
+    return (d3 ? 4 : 3) * cpl + (row_mask_scan(cpl, d3) ? 8 : 0);
+}
 
 constexpr int AA_MAX = 8;
 

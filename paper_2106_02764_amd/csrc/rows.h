@@ -61,35 +61,66 @@ __device__ __forceinline__ double selw(mask_t m, double v) {
     return __longlong_as_double(((long long)hi << 32) | (unsigned int)(int)b);
 }
 
-// The masks of one row that its sweep needs.  With sigma = 1: brk[k], the
-// lanes whose segment before scan step k has no closed x inflow; om, the
-// lanes reached from the row's start without one; nb, all ones when the row
-// has none.  xo / yo / zo: cells whose inflow along the row / across the rows
-// / through the planes (3D) is open; sol (adjoint): solid cells.
-template <int CPL, bool S1, bool ADJB, bool D3 = false>
-struct RowMask {
-    mask_t brk[S1 ? 6 : 1], om, nb;
+// What a sweep reads of a row's masks (k_row_masks).  xo / yo / zo: cells whose
+// inflow along the row / across the rows / through the planes (3D) is open; sol
+// (adjoint): solid cells; SCAN: the scan's masks.
+//
+// With sigma = 1 the scan's eight masks are formed from the open lanes in some
+// 20 scalar instructions.  Loading them was cheaper to issue, but a row's line
+// then came from the L2 (64 x 256 cells: 22 KB an orientation, and two CUs
+// share 16 KB of scalar cache), and as the loads sat next to their use its
+// latency was in the chain of every row.  With the few words left, asked for at
+// the start of a row: 64 x 256, 48 x 30 systems, FP32: 97 -> 66 us a launch;
+// 150 x 109 with a sigma field, 36 x 22 systems, FP32: 149 -> 99 us.
+// Rows of 3 and 4 cells per lane in 3D FP32 keep the scan's masks loaded: two
+// waves a SIMD do not hide the scalar instructions (256 x 16 x 6, 72 x 12
+// systems: 3.47 against 3.65 ms for 6 passes; in FP64, with twice the vector
+// instructions, 4.16 against 4.18).
+template <int CPL, bool ADJB, bool D3 = false, bool SCAN = false>
+struct RowBits {
     mask_t xo[CPL], yo[CPL], zo[D3 ? CPL : 1], sol[ADJB ? CPL : 1];
+    mask_t sc[SCAN ? 8 : 1];
 };
-template <int CPL, bool S1, bool ADJB, bool D3>
-__device__ __forceinline__ void load_mask(mview_t row, RowMask<CPL, S1, ADJB, D3>& m) {
-    if (S1) {
-#pragma unroll
-        for (int k = 0; k < 6; ++k) m.brk[k] = row[k];
-        m.om = row[6];
-        m.nb = row[7];
-    }
+template <int CPL, bool ADJB, bool D3, bool SCAN>
+__device__ __forceinline__ void load_bits(mview_t row, RowBits<CPL, ADJB, D3, SCAN>& m) {
 #pragma unroll
     for (int c = 0; c < CPL; ++c) {
-        m.xo[c] = row[8 + c];
-        m.yo[c] = row[8 + CPL + c];
-        if (D3) m.zo[c] = row[8 + 2 * CPL + c];
-        if (ADJB) m.sol[c] = row[8 + (D3 ? 3 : 2) * CPL + c];
+        m.xo[c] = row[c];
+        m.yo[c] = row[CPL + c];
+        if (D3) m.zo[c] = row[2 * CPL + c];
+        if (ADJB) m.sol[c] = row[(D3 ? 3 : 2) * CPL + c];
     }
-    // the loads stay here, a row ahead of their use (to save registers the
-    // scheduler would move them next to it; their latency is then in the
-    // chain): other instructions may cross, scalar loads may not
-    __builtin_amdgcn_sched_barrier(0x2 | 0x4 | 0x10 | 0x20 | 0x40 | 0x80 | 0x100 | 0x200);
+    if (SCAN)
+#pragma unroll
+        for (int k = 0; k < 8; ++k) m.sc[k] = row[4 * CPL + k];
+    // the loads stay here, ahead of their use (to save registers the scheduler
+    // would move them next to it, and their latency would be in the chain).
+    // 3D: vector instructions may cross, its other waves fill the wait
+    if constexpr (D3)
+        __builtin_amdgcn_sched_barrier(0x2 | 0x4 | 0x10 | 0x20 | 0x40 | 0x80 | 0x100 | 0x200);
+    else
+        __builtin_amdgcn_sched_barrier(0);
+}
+// The wait for a row's bits (2D): before the next row's are asked for, as
+// scalar loads come back in any order and a wait is for all of them.
+template <int CPL, bool ADJB>
+__device__ __forceinline__ void need_bits(const RowBits<CPL, ADJB>& m) {
+    asm volatile("" ::"s"(m.xo[0]));
+    __builtin_amdgcn_sched_barrier(0);
+}
+template <int CPL, bool ADJB, bool D3, bool SCAN>
+__device__ __forceinline__ void scan_mask(const RowBits<CPL, ADJB, D3, SCAN>& b, ScanMask& m) {
+    if constexpr (SCAN) {
+#pragma unroll
+        for (int k = 0; k < 6; ++k) m.brk[k] = b.sc[k];
+        m.om = b.sc[6];
+        m.nb = b.sc[7];
+    } else {
+        mask_t g = b.xo[0];
+#pragma unroll
+        for (int c = 1; c < CPL; ++c) g &= b.xo[c];
+        scan_mask(g, m);
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -151,23 +182,26 @@ __device__ __forceinline__ void make_qconst(double c0, double c1, int nr, int la
 
 // sigma = 1: scan of the affine parts A with the weights selected by the
 // masks; returns Q from the row's start (for the closure).
-template <int CPL, bool FULL, bool ADJB, bool D3>
-__device__ __forceinline__ double ascan(double& A, const QConst<double, CPL, FULL>& k, const RowMask<CPL, true, ADJB, D3>& m) {
-    A = A + selw(m.brk[0], k.tk[0]) * dpp<0x111, 0xf>(A, 0.0);   // row_shr:1
-    A = A + selw(m.brk[1], k.tk[1]) * dpp<0x112, 0xf>(A, 0.0);   // row_shr:2
-    A = A + selw(m.brk[2], k.tk[2]) * dpp<0x114, 0xf>(A, 0.0);   // row_shr:4
-    A = A + selw(m.brk[3], k.tk[3]) * dpp<0x118, 0xf>(A, 0.0);   // row_shr:8
+template <int CPL, bool FULL>
+__device__ __forceinline__ double ascan(double& A, const QConst<double, CPL, FULL>& k, const ScanMask& m) {
+    A = A + selw(m.brk[0], k.tk[0]) * dpp0<0x111>(A);   // row_shr:1
+    A = A + selw(m.brk[1], k.tk[1]) * dpp0<0x112>(A);   // row_shr:2
+    A = A + selw(m.brk[2], k.tk[2]) * dpp0<0x114>(A);   // row_shr:4
+    A = A + selw(m.brk[3], k.tk[3]) * dpp0<0x118>(A);   // row_shr:8
     A = A + selw(m.brk[4], k.tk[4]) * dpp<0x142, 0xa>(A, 0.0);   // row_bcast:15 into rows 1, 3
     A = A + selw(m.brk[5], k.tk[5]) * dpp<0x143, 0xc>(A, 0.0);   // row_bcast:31 into rows 2, 3
     return selw(m.om, k.om);
 }
 // FP32: the DPP read folded into v_fmac (the compiler does not fold its own
 // moves); a DPP read needs two wait states after the write of its register,
-// filled with the next weights' selects where there are any.
-template <int CPL, bool FULL, bool ADJB, bool D3>
-__device__ __forceinline__ float ascan(float& A, const QConst<float, CPL, FULL>& k, const RowMask<CPL, true, ADJB, D3>& m) {
+// filled with the next weights' selects where there are any.  So does a select
+// after a vector instruction that wrote its mask (one that the compiler reloads
+// by v_readlane, which it may put right before the block: hence the first s_nop).
+template <int CPL, bool FULL>
+__device__ __forceinline__ float ascan(float& A, const QConst<float, CPL, FULL>& k, const ScanMask& m) {
     float t0, t1, om;
-    asm("v_cndmask_b32_e64 %1, 0, %4, %11\n\t"
+    asm("s_nop 1\n\t"
+        "v_cndmask_b32_e64 %1, 0, %4, %11\n\t"
         "v_cndmask_b32_e64 %2, 0, %5, %12\n\t"
         "v_fmac_f32_dpp %0, %0, %1 row_shr:1 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
         "v_cndmask_b32_e64 %1, 0, %6, %13\n\t"
@@ -204,7 +238,7 @@ struct QPart {
     T rPt;
 };
 template <typename T, int CPL, bool FULL, bool ADJB, bool D3>
-__device__ __forceinline__ T qpart_cells(T c0, T c1, const QConst<T, CPL, FULL>& k, const RowMask<CPL, false, ADJB, D3>& m,
+__device__ __forceinline__ T qpart_cells(T c0, T c1, const QConst<T, CPL, FULL>& k, const RowBits<CPL, ADJB, D3>& m,
                                          const T (&sg)[CPL], QPart<T, CPL>& o) {
     const T cdiag = c0 + c1;
     T Pl;
@@ -234,10 +268,10 @@ __device__ __forceinline__ void qpart_close(T P, QPart<T, CPL>& o) {
 // The P half of the scan alone (the first row of a sweep), recording t_k.
 template <typename T>
 __device__ __forceinline__ void pscan(T& P, T (&t)[6]) {
-    t[0] = T(1) - P; P = P + t[0] * dpp<0x111, 0xf>(P, T(0));   // row_shr:1
-    t[1] = T(1) - P; P = P + t[1] * dpp<0x112, 0xf>(P, T(0));   // row_shr:2
-    t[2] = T(1) - P; P = P + t[2] * dpp<0x114, 0xf>(P, T(0));   // row_shr:4
-    t[3] = T(1) - P; P = P + t[3] * dpp<0x118, 0xf>(P, T(0));   // row_shr:8
+    t[0] = T(1) - P; P = P + t[0] * dpp0<0x111>(P);   // row_shr:1
+    t[1] = T(1) - P; P = P + t[1] * dpp0<0x112>(P);   // row_shr:2
+    t[2] = T(1) - P; P = P + t[2] * dpp0<0x114>(P);   // row_shr:4
+    t[3] = T(1) - P; P = P + t[3] * dpp0<0x118>(P);   // row_shr:8
     t[4] = T(1) - P; P = P + t[4] * dpp<0x142, 0xa>(P, T(0));   // row_bcast:15 into rows 1, 3
     t[5] = T(1) - P; P = P + t[5] * dpp<0x143, 0xc>(P, T(0));   // row_bcast:31 into rows 2, 3
 }
@@ -245,10 +279,10 @@ __device__ __forceinline__ void pscan(T& P, T (&t)[6]) {
 // recording tn (the two chains interleave).
 template <typename T>
 __device__ __forceinline__ void scan_pair(T& A, const T (&t)[6], T& P, T (&tn)[6]) {
-    tn[0] = T(1) - P; A = A + t[0] * dpp<0x111, 0xf>(A, T(0)); P = P + tn[0] * dpp<0x111, 0xf>(P, T(0));
-    tn[1] = T(1) - P; A = A + t[1] * dpp<0x112, 0xf>(A, T(0)); P = P + tn[1] * dpp<0x112, 0xf>(P, T(0));
-    tn[2] = T(1) - P; A = A + t[2] * dpp<0x114, 0xf>(A, T(0)); P = P + tn[2] * dpp<0x114, 0xf>(P, T(0));
-    tn[3] = T(1) - P; A = A + t[3] * dpp<0x118, 0xf>(A, T(0)); P = P + tn[3] * dpp<0x118, 0xf>(P, T(0));
+    tn[0] = T(1) - P; A = A + t[0] * dpp0<0x111>(A); P = P + tn[0] * dpp0<0x111>(P);
+    tn[1] = T(1) - P; A = A + t[1] * dpp0<0x112>(A); P = P + tn[1] * dpp0<0x112>(P);
+    tn[2] = T(1) - P; A = A + t[2] * dpp0<0x114>(A); P = P + tn[2] * dpp0<0x114>(P);
+    tn[3] = T(1) - P; A = A + t[3] * dpp0<0x118>(A); P = P + tn[3] * dpp0<0x118>(P);
     tn[4] = T(1) - P; A = A + t[4] * dpp<0x142, 0xa>(A, T(0)); P = P + tn[4] * dpp<0x142, 0xa>(P, T(0));
     tn[5] = T(1) - P; A = A + t[5] * dpp<0x143, 0xc>(A, T(0)); P = P + tn[5] * dpp<0x143, 0xc>(P, T(0));
 }

@@ -126,7 +126,7 @@ template <typename T, int CPL, int ST, bool WITH_B, bool ADJ, bool S1, bool FULL
 struct Sweep2 {
     static constexpr int RB = tr_rb<T>(), PB = WAVE / RB, LS = tr_ls<CPL>();
     static constexpr bool ADJB = ADJ && WITH_B;
-    using Mask = RowMask<CPL, S1, ADJB>;
+    using Bits = RowBits<CPL, ADJB>;
     const GeomDev& g;
     const Sys2<T>& s;
     const QConst<T, CPL, FULL>& k;
@@ -162,7 +162,7 @@ struct Sweep2 {
         v.o4 = uni((uint32_t)((first + ROW_SLACK) * s.rs) * 4u);
         v.sT = uni((uint32_t)(s.negw ? -s.rs : s.rs) * (uint32_t)sizeof(T));
         v.s4 = uni((uint32_t)(s.negw ? -s.rs : s.rs) * 4u);
-        const int ms = row_mask_words(CPL);
+        constexpr int ms = row_mask_words(CPL, false);
         v.mask = (mview_t)(uni(s.tr ? g.qmask[1] : g.qmask[0]) + (size_t)((2 * s.negr + s.negw) * s.nw + first) * ms);
         v.mstep = s.negw ? -ms : ms;
         if (ST == 2) {
@@ -184,20 +184,13 @@ struct Sweep2 {
         return p * s.nx + (s.negw ? s.nw - RB - j0 : j0) + OFF_SLACK;
     }
     // store offsets of the flush steps of row jj (of the previous batch);
-    // start: jj may be the first row of a batch
+    // start: jj may be the first row of a batch.  As loaded: what depends on
+    // the value waits for it, and is done by the store.
     __device__ __forceinline__ void load_flush(int jj, bool start, uint32_t (&so)[CPL]) {
-        const int rib = jj & (RB - 1);
-        if (start) v.fb += rib == 0 ? v.fbatch : 0;
+        if (start) v.fb += (jj & (RB - 1)) == 0 ? v.fbatch : 0;
 #pragma unroll
         for (int c = 0; c < CPL; ++c) {
-            if (FULL) {
-                so[c] = bld32(v.off, (uint32_t)v.lv, (uint32_t)v.fb);
-            } else {
-                const int p = (rib * CPL + c) * PB + v.lp - (WAVE * CPL - s.nr);
-                so[c] = bld32(v.off, (uint32_t)(v.lv + v.fb), 0u);
-                so[c] = p >= 0 && p < s.nr ? so[c] : QOFF_NONE;
-            }
-            so[c] |= jj >= RB ? 0u : BUF_OOB;
+            so[c] = FULL ? bld32(v.off, (uint32_t)v.lv, (uint32_t)v.fb) : bld32(v.off, (uint32_t)(v.lv + v.fb), 0u);
             v.fb += v.fstep;
         }
     }
@@ -205,7 +198,11 @@ struct Sweep2 {
         // jj: first row of the group of four, q: row within it
         const T* src = tile + (((jj / RB) & 1) ^ 1) * RB * LS + v.j * LS + v.lp + (jj & (RB - 1)) * CPL * PB;
 #pragma unroll
-        for (int c = 0; c < CPL; ++c) bst(src[(q * CPL + c) * PB], X, so[c]);
+        for (int c = 0; c < CPL; ++c) {
+            const int p = (((jj & (RB - 1)) + q) * CPL + c) * PB + v.lp - (WAVE * CPL - s.nr);
+            const uint32_t o = FULL || (p >= 0 && p < s.nr) ? so[c] : QOFF_NONE;
+            bst(src[(q * CPL + c) * PB], X, o | (jj >= RB ? 0u : BUF_OOB));      // no batch before the first
+        }
     }
     // after the last row: what is left of the last full batch, and the last one
     __device__ __forceinline__ void drain() const {
@@ -245,19 +242,16 @@ struct Sweep2 {
         if (ST == 1) {
             bld_dw<CPL>(b.so, v.off, v.v4, v.o4);
             v.o4 += v.s4;
-            if (!FULL)
-#pragma unroll
-                for (int c = 0; c < CPL; ++c) b.so[c] |= v.v4 == BUF_OOB ? BUF_OOB : 0u;   // lanes ahead of the row
         }
         if (ST == 2) load_flush(j, start, b.so);
     }
-    __device__ __forceinline__ void masks(Mask& m) {
-        load_mask(v.mask, m);
+    __device__ __forceinline__ void bits(Bits& m) {
+        load_bits(v.mask, m);
         v.mask += v.mstep;
     }
 
     // the part of the right-hand side that does not come from the row below
-    __device__ __forceinline__ T source(const QIn<T, CPL>& b, const Mask& m, int c, T ksb, T k0, T k1, T o0, T o1,
+    __device__ __forceinline__ T source(const QIn<T, CPL>& b, const Bits& m, int c, T ksb, T k0, T k1, T o0, T o1,
                                         T kk) const {
         T a;
         if (ADJB) {
@@ -289,7 +283,7 @@ struct Sweep2 {
         }
         if (ST == 1) {
 #pragma unroll
-            for (int c = 0; c < CPL; ++c) bst(y[c], X, b.so[c]);
+            for (int c = 0; c < CPL; ++c) bst(y[c], X, FULL ? b.so[c] : b.so[c] | (v.v4 & BUF_OOB));   // lanes ahead of the row
         }
         if (ST == 2) {
             T* dst = tile + ((jj / RB) & 1) * RB * LS + (jj & (RB - 1)) * LS + qr * LS + lane * CPL;
@@ -300,7 +294,7 @@ struct Sweep2 {
     }
 
     // sigma = 1: row jj + qr (jj: its group of four) with its masks
-    __device__ __forceinline__ void step(const QIn<T, CPL>& b, const Mask& m, int jj, int qr, T kc1, T kb0, T kb1, T ko0,
+    __device__ __forceinline__ void step(const QIn<T, CPL>& b, const Bits& m, const ScanMask& sm, int jj, int qr, T kc1, T kb0, T kb1, T ko0,
                                          T ko1, T ksb, T kk) {
         T a[CPL], q[CPL];
         T Al;
@@ -312,15 +306,15 @@ struct Sweep2 {
             Al = c == 0 ? a[c] : a[c] + q[c] * Al;
         }
         T A = Al;
-        const T om = ascan(A, k, m);
-        const T xin = readlane(A, WAVE - 1) * (lane_in(m.nb) ? k.rpt : T(1));
+        const T om = ascan(A, k, sm);
+        const T xin = readlane(A, WAVE - 1) * (lane_in(sm.nb) ? k.rpt : T(1));
         const T xe = A + om * xin;
         finish_row(a, q, dpp<0x138, 0xf>(xe, xin), b, jj, qr);        // wave_shr:1
     }
 
     // a sigma field: row jj + qr with its source-free part, and the next row's
-    __device__ __forceinline__ void step(const QIn<T, CPL>& b, const Mask& m, const QPart<T, CPL>& p, const QIn<T, CPL>& bn,
-                                         const Mask& mn, QPart<T, CPL>& pn, int jj, int qr, T c0, T c1) {
+    __device__ __forceinline__ void step(const QIn<T, CPL>& b, const Bits& m, const QPart<T, CPL>& p, const QIn<T, CPL>& bn,
+                                         const Bits& mn, QPart<T, CPL>& pn, int jj, int qr, T c0, T c1) {
         T Pn = qpart_cells(c0, c1, k, mn, bn.sg, pn);
         T a[CPL];
         T Al;
@@ -358,13 +352,32 @@ struct Sweep2 {
         if constexpr (S1) {
             const T kc1 = (T)s.c1 * k.rdv, kb0 = s.mb0 * k.rdv, kb1 = s.mb1 * k.rdv, ko0 = s.mo0 * k.rdv,
                     ko1 = s.mo1 * k.rdv, kk = s.sk * k.rdv, ksb = ADJ ? s.sdm * k.rdv : k.rdv;
-            Mask m;
-            masks(m);
+            // the bits of this row and the next; without sources also this
+            // row's scan masks, the next row's being formed while its chain
+            // runs (a storing sweep has no scalar registers left for them,
+            // and its sources to take meanwhile)
+            constexpr bool AHEAD = !WITH_B;
+            Bits m, m1;
+            ScanMask sm;
+            bits(m);
+            if constexpr (AHEAD) {
+                bits(m1);
+                scan_mask(m, sm);
+            }
             auto one = [&](const QIn<T, CPL>& b, int jj, int q) {
-                Mask n;
-                masks(n);
-                step(b, m, jj, q, kc1, kb0, kb1, ko0, ko1, ksb, kk);
-                m = n;
+                Bits n;
+                need_bits(AHEAD ? m1 : m);
+                bits(n);
+                ScanMask sn;
+                scan_mask(AHEAD ? m1 : m, sn);
+                step(b, m, AHEAD ? sm : sn, jj, q, kc1, kb0, kb1, ko0, ko1, ksb, kk);
+                if constexpr (AHEAD) {
+                    m = m1;
+                    m1 = n;
+                    sm = sn;
+                } else {
+                    m = n;
+                }
             };
             auto group = [&](int jj) {
                 load(jj + 3, false, b3);
@@ -385,18 +398,19 @@ struct Sweep2 {
             if (r + 2 < nw) one(b2, r, 2);
         } else {
             const T c0 = (T)s.c0, c1 = (T)s.c1;
-            Mask m0, m1;
+            Bits m0, m1;
             QPart<T, CPL> p0, p1;
-            masks(m0);
-            masks(m1);
+            bits(m0);
+            bits(m1);
             {
                 T P = qpart_cells(c0, c1, k, m0, b0.sg, p0);
                 pscan(P, p0.t);
                 qpart_close<T, CPL>(P, p0);
             }
             auto one = [&](const QIn<T, CPL>& b, const QIn<T, CPL>& bn, int jj, int q) {
-                Mask n;
-                masks(n);
+                Bits n;
+                need_bits(m1);
+                bits(n);
                 step(b, m0, p0, bn, m1, p1, jj, q, c0, c1);
                 m0 = m1;
                 m1 = n;
@@ -466,10 +480,10 @@ __device__ __forceinline__ void pass_system(const GeomDev* __restrict__ geoms, c
     // pairs across the wrap: the first row's inflow across the rows
     bool mk[CPL];
     {
-        RowMask<CPL, false, false> m0;
-        const int ms = row_mask_words(CPL);
-        load_mask((mview_t)(uni(s.tr ? g.qmask[1] : g.qmask[0]) +
-                            (size_t)((2 * s.negr + s.negw) * s.nw + (s.negw ? s.nw - 1 : 0)) * ms), m0);
+        RowBits<CPL, false> m0;
+        const mview_t row = (mview_t)(uni(s.tr ? g.qmask[1] : g.qmask[0]) +
+                                      (size_t)((2 * s.negr + s.negw) * s.nw + (s.negw ? s.nw - 1 : 0)) * row_mask_words(CPL, false));
+        load_bits(row, m0);
         VLOOP(mk[c] = lane_in(m0.yo[c]));
     }
     const bool has_wrap = g.periodic[s.tr ? 0 : 1] != 0;

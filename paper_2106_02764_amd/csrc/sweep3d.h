@@ -14,11 +14,9 @@
 // Q along took 79.  The pass inputs are laid out in the order the rows are
 // swept (two copies, one with the planes reversed: the eight octants walk one
 // of them forwards or backwards; a row's values are one block behind one
-// advancing resource), so a row takes 15 scalar instructions where indexing it
-// took 53.  Solutions are stored past the caches (non-temporal: the tables
-// stay in the L2).  64 x 64 x 16 membrane, 288 directions x 30 MFPs, FP32:
-// 1.97 -> 1.39 ms a launch; the masks' scalar loads, one row ahead, still cost
-// about a sixth of it.
+// advancing resource), so a row takes 27 scalar instructions, 20 of them its
+// scan masks (rows.h), where indexing it took 53.  Solutions are stored past
+// the caches (non-temporal: the tables stay in the L2).
 #pragma once
 #include "rows.h"
 
@@ -72,7 +70,8 @@ template <typename T, int CPL, bool ST, bool WITH_B, bool ADJ, bool S1, bool FUL
 struct Sweep3 {
     static constexpr bool ADJB = ADJ && WITH_B;
     static constexpr int ROW = WAVE * CPL;
-    using Mask = RowMask<CPL, S1, ADJB, true>;
+    static constexpr bool SCAN = S1 && sizeof(T) == 4 && row_mask_scan(CPL, true);
+    using Bits = RowBits<CPL, ADJB, true, SCAN>;
     const Sys3<T>& s;
     const QConst<T, CPL, FULL>& k;
     const int lane, nx, ny, nz;
@@ -117,7 +116,7 @@ struct Sweep3 {
         }
         row = uni(static_cast<const char*>(g.qtab[0]) + ((size_t)zrev * nrows + first) * rbytes);
         rstep = s.neg[1] ? -(long)rbytes : (long)rbytes;
-        constexpr int ms = row_mask_words3(CPL);
+        constexpr int ms = row_mask_words(CPL, true);
         mask = (mview_t)(uni(g.qmask[0]) + (size_t)((s.neg[0] * 4 + s.neg[1] * 2 + zrev) * nrows + first) * ms);
         mstep = s.neg[1] ? -ms : ms;
         kt = 0.0;
@@ -143,11 +142,11 @@ struct Sweep3 {
         }
         row += rstep;
     }
-    __device__ __forceinline__ void masks(Mask& m) {
-        load_mask(mask, m);
+    __device__ __forceinline__ void bits(Bits& m) {
+        load_bits(mask, m);
         mask += mstep;
     }
-    __device__ __forceinline__ T source(const In& r, const Mask& m, int c, T ksb, const T (&kb)[3], const T (&ko)[3], T kk) const {
+    __device__ __forceinline__ T source(const In& r, const Bits& m, int c, T ksb, const T (&kb)[3], const T (&ko)[3], T kk) const {
         T a;
         if (ADJB) {
             a = kk + ksb * r.sb[c];
@@ -208,11 +207,18 @@ struct Sweep3 {
             const T ky = (T)s.cd[1] * rdv, kz = (T)s.cd[2] * rdv, kk = s.sk * rdv, ksb = ADJ ? s.sdm * rdv : rdv;
             const T kb[3] = {s.mb[0] * rdv, s.mb[1] * rdv, s.mb[2] * rdv};
             const T ko[3] = {s.mo[0] * rdv, s.mo[1] * rdv, s.mo[2] * rdv};
-            Mask m;
-            masks(m);
+            // the bits of this row and the next, this row's scan masks: the
+            // next row's are formed while its chain runs
+            Bits m, m1;
+            ScanMask sm;
+            bits(m);
+            if constexpr (!SCAN) bits(m1);
+            scan_mask(m, sm);
             auto one = [&](const In& in, In& fill) {
-                Mask n;
-                masks(n);
+                Bits n;
+                bits(n);
+                ScanMask sn;
+                scan_mask(SCAN ? n : m1, sn);
                 load(fill);
                 T pn[CPL];
                 T* zr = advance(pn);
@@ -226,13 +232,15 @@ struct Sweep3 {
                     Al = c == 0 ? a[c] : a[c] + q[c] * Al;
                 }
                 T A = Al;
-                const T om = ascan(A, k, m);
-                const T xin = readlane(A, WAVE - 1) * (lane_in(m.nb) ? k.rpt : T(1));
+                const T om = ascan(A, k, sm);
+                const T xin = readlane(A, WAVE - 1) * (lane_in(sm.nb) ? k.rpt : T(1));
                 const T xe = A + om * xin;
                 finish_row(a, q, dpp<0x138, 0xf>(xe, xin), in, zr);      // wave_shr:1
 #pragma unroll
                 for (int c = 0; c < CPL; ++c) py[c] = pn[c];
-                m = n;
+                m = SCAN ? n : m1;
+                m1 = n;
+                sm = sn;
             };
             if (nrows >= 3) {
                 one(b0, b2);
@@ -248,10 +256,10 @@ struct Sweep3 {
             if (r + 1 < nrows) one(b1, b0);
         } else {
             const T c0 = (T)s.cd[0], cr = (T)(s.cd[1] + s.cd[2]), cy = (T)s.cd[1], cz = (T)s.cd[2];
-            Mask m0, m1;
+            Bits m0, m1;
             QPart<T, CPL> p0, p1;
-            masks(m0);
-            masks(m1);
+            bits(m0);
+            bits(m1);
             {
                 T P = qpart_cells(c0, cr, k, m0, b0.sg, p0);
                 pscan(P, p0.t);
@@ -259,8 +267,8 @@ struct Sweep3 {
             }
             auto one = [&](const In& in, const In& nxt, In& fill) {
                 load(fill);
-                Mask n;
-                masks(n);
+                Bits n;
+                bits(n);
                 T pn[CPL];
                 T* zr = advance(pn);
                 T Pn = qpart_cells(c0, cr, k, m1, nxt.sg, p1);
@@ -344,10 +352,10 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(CPL ==
     const int p0 = lane * CPL - (WAVE * CPL - nx);       // row position of this lane's first cell
     // pairs across the wrap: the first y row's inflow along y (its nz rows are
     // the first swept)
-    const int mstep = s.neg[1] ? -row_mask_words3(CPL) : row_mask_words3(CPL);
+    const int mstep = s.neg[1] ? -row_mask_words(CPL, true) : row_mask_words(CPL, true);
     const mview_t mrow = (mview_t)(uni(g.qmask[0]) + (size_t)((s.neg[0] * 4 + s.neg[1] * 2 + (s.neg[1] != s.neg[2])) * g.ny * nz +
-                                                              (s.neg[1] ? g.ny * nz - 1 : 0)) * row_mask_words3(CPL));
-    auto open = [&](int kp, int c) { return lane_in(mrow[(long)kp * mstep + 8 + CPL + c]); };
+                                                              (s.neg[1] ? g.ny * nz - 1 : 0)) * row_mask_words(CPL, true));
+    auto open = [&](int kp, int c) { return lane_in(mrow[(long)kp * mstep + CPL + c]); };
     const bool has_wrap = g.periodic[1] != 0;
     long long n_it = 0, n_sw = 0;
     int need = 0;
