@@ -388,7 +388,7 @@ Layout make_layout(const obte_mesh* m, const obte_solve_opts* o, bool tr) {
     L.T_L = take(nc * 8);
     L.ksys = take((size_t)m->n_sys * 8);
     L.kfsys = take((size_t)m->n_sys * 8);
-    L.iters = take((size_t)m->n_sys * 8);
+    L.iters = take((size_t)m->n_sys * 8);       // cleared together
     L.sweeps = take((size_t)m->n_sys * 8);
     L.ctrl = take(CTRL_N * 4);
     L.fx = take(fourier_scratch_doubles(nc) * 8);
@@ -1166,7 +1166,7 @@ obte_status solve_impl(obte_mesh* const* meshes, int n, const obte_solve_opts* o
             const size_t tsz = o->precision == OBTE_FP32 ? 4 : 8;
             HIPCHK(hipMemsetAsync(ws + L.U, 0, 2 * (size_t)m->n_sys * R.views[i].nwrap * tsz, st));
         }
-        HIPCHK(hipMemsetAsync(ws + L.iters, 0, 2 * (size_t)m->n_sys * 8, st));
+        HIPCHK(hipMemsetAsync(ws + L.iters, 0, L.sweeps - L.iters + (size_t)m->n_sys * 8, st));
         HIPCHK(hipMemsetAsync(ws + L.wres, 0, (size_t)m->n_sys * 8, st));
     }
     Timer tm;
@@ -1864,7 +1864,7 @@ obte_status obte_adjoint(obte_mesh* m, const obte_solve_opts* o, const double* s
     HIPCHK(hipMemsetAsync(ws + L.U + half, 0, half, st));
     HIPCHK(hipMemsetAsync(ws + L.bnd + 2 * (size_t)m->nf * m->ncells * 8, 0,
                           2 * (size_t)m->nf * m->ncells * 8, st));
-    HIPCHK(hipMemsetAsync(ws + L.iters, 0, 2 * (size_t)m->n_sys * 8, st));
+    HIPCHK(hipMemsetAsync(ws + L.iters, 0, L.sweeps - L.iters + (size_t)m->n_sys * 8, st));
     HIPCHK(hipMemsetAsync(ws + L.wres, 0, (size_t)m->n_sys * 8, st));
     HIPCHK(hipMemsetAsync(ws + L.ctrl, 0, CTRL_N * sizeof(int), st));
     HIPCHK(hipMemsetAsync(ws + L.ax, 0, ((size_t)m->ncells + m->nwalls) * 8, st));
