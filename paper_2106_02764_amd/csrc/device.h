@@ -9,8 +9,6 @@ namespace {
 constexpr int WAVE = 64;
 
 template <typename T>
-__device__ __forceinline__ T shfl_up(T v, int d) { return __shfl_up(v, d, WAVE); }
-template <typename T>
 __device__ __forceinline__ T shfl_at(T v, int l) { return __shfl(v, l, WAVE); }
 template <typename T>
 __device__ __forceinline__ T shfl_xor(T v, int m) { return __shfl_xor(v, m, WAVE); }
@@ -247,9 +245,6 @@ __device__ __forceinline__ gmut_t<T> gmut(T* p) { return (gmut_t<T>)p; }
 // the array's size is dropped (used for pores and beyond-row lanes).
 constexpr uint32_t BUF_OOB = 0x80000000u;
 typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ uint32_t bld16(rsrc_t r, uint32_t vo, uint32_t so) {
-    return (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(r, (int)vo, (int)so, 0);
-}
 __device__ __forceinline__ uint32_t bld32(rsrc_t r, uint32_t vo, uint32_t so) {
     return __builtin_amdgcn_raw_buffer_load_b32(r, (int)vo, (int)so, 0);
 }

@@ -16,7 +16,7 @@ __host__ __device__ inline int fc_class(uint16_t w, int f) { return (w >> (1 + 2
 enum { CTRL_DONE = 0, CTRL_PASS = 1, CTRL_CONVERGED = 2, CTRL_NONFINITE = 3, CTRL_N = 8 };
 
 // wrap-plane vectors per system kept in the workspace by the 3D pass kernel
-constexpr int KRY3_VECS = 11;
+constexpr int KRY3_VECS = 8;
 
 // Per-geometry view used by every kernel: static tables (library-owned) plus
 // the per-solve workspace carve (caller-owned).

@@ -23,7 +23,7 @@
 namespace {
 
 enum { KV_R, KV_E, KV_EB, KV_RH, KV_P, KV_V, KV_S, KV_T, KV_N };
-static_assert(KV_N <= KRY3_VECS, "workspace carve and kernel disagree on the 3D slab");
+static_assert(KV_N == KRY3_VECS, "workspace carve and kernel disagree on the 3D slab");
 
 template <typename T>
 struct Sys3 {
