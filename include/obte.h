@@ -255,13 +255,15 @@ obte_status obte_solve(obte_mesh* mesh, const obte_solve_opts* opts, const doubl
 
 /* obte_solve for callers that cannot allocate device or pinned host memory
  * (code under HIP graph capture, serving loops, harnesses that forbid
- * hipMalloc).  The workspace is a file-scope device array of
- * obte_noalloc_scratch_bytes() bytes (32 MiB) that the library holds on
- * every device it runs on until the process ends; the call takes the copy
- * of the current device (which must hold the mesh tables).  Arguments and
- * results as obte_solve, with: init = 0 (every call starts from the Fourier
- * guess), keep_state = 0 and timing = 0 (OBTE_ERR_ARG otherwise); a mesh
- * whose workspace (obte_workspace_size) exceeds the array returns
+ * hipMalloc).  The workspace is a file-scope device array (40 MiB) that the
+ * library holds on every device it runs on until the process ends; the call
+ * takes the copy of the current device (which must hold the mesh tables).
+ * Arguments and results as obte_solve, with: init = 0 (every call starts from
+ * the Fourier guess), keep_state = 0 and timing = 0 (OBTE_ERR_ARG otherwise).
+ * A mesh whose workspace (obte_workspace_size) is at most
+ * obte_noalloc_scratch_bytes() is admitted, and a larger one where the sweeps'
+ * row tables alone make it so (up to 88 bytes a cell in 3D; 2D meshes with
+ * ny > nx are then swept with rows along x only); any other returns
  * OBTE_ERR_NOMEM before any device work.  The call launches every kernel
  * directly on `stream` (no graph capture, no events, no pinned staging) and
  * allocates nothing; it synchronizes `stream` to read the results back.
@@ -270,7 +272,8 @@ obte_status obte_solve(obte_mesh* mesh, const obte_solve_opts* opts, const doubl
  * streams) race and must be serialised by the caller. */
 obte_status obte_solve_noalloc(obte_mesh* mesh, const obte_solve_opts* opts, const double* sigma_dev,
                                void* stream, double* T_L_dev, double* J_dev, obte_stats* stats);
-/* Bytes of the per-device array obte_solve_noalloc works in. */
+/* Bytes of workspace that obte_solve_noalloc admits on any mesh (32 MiB; the
+ * array has 8 MiB more, for the sweeps' row tables). */
 size_t obte_noalloc_scratch_bytes(void);
 
 /* Many independent geometries in one launch per pass (one per row-width

@@ -1729,10 +1729,21 @@ obte_status obte_solve(obte_mesh* m, const obte_solve_opts* o, const double* sig
 // ---------------------------------------------------------------------------
 namespace {
 constexpr size_t NOALLOC_BYTES = (size_t)32 << 20;
-// over the stated size: what the row tables take beyond the pass inputs that
-// the limit was set with (Layout::q_added), so that every mesh it admits fits
-// (at most 76 of the 500 bytes or more that a cell takes)
+// over the stated size: what a workspace takes beyond the form that the limit
+// was set with (noalloc_added), so that every mesh admitted then still is.  At
+// most 88 of the 380 bytes or more that a cell takes (two copies of a 3D FP64
+// row, 2 cells long, in 16-byte units: 144 bytes a cell for 56; 2D row tables
+// take less than the inputs in four orientations did), and 4 of the 600 or more
+// that a system takes
 constexpr size_t NOALLOC_ROWS = (size_t)8 << 20;
+
+// row tables for pass inputs by cell; five words for four a work item, and the
+// items that rows along y or wider rows add
+size_t noalloc_added(const obte_mesh* m, const obte_solve_opts* o, int W, bool tr) {
+    const size_t now = align256(count_items(m, W, o->precision, tr) * sizeof(Item));
+    const size_t then = align256((size_t)m->n_dir * n_groups(m, W) * 4 * sizeof(int));
+    return make_layout(m, o, tr).q_added + (now > then ? now - then : 0);
+}
 static __device__ __align__(256) unsigned char scratch[NOALLOC_BYTES + NOALLOC_ROWS];
 constexpr int NOALLOC_MAX_DEV = 64;
 std::mutex g_scratch_mu;
@@ -1773,19 +1784,25 @@ obte_status obte_solve_noalloc(obte_mesh* m, const obte_solve_opts* o, const dou
         return fail(OBTE_ERR_ARG, "the mesh tables are on device %d, the current device is %d", m->device, dev);
     // rows along y need a longer wrap inflow where ny > nx: without them where
     // it does not fit
-    size_t need = 0;
+    size_t need = 0, added = 0;
+    int Wc[5];
     bool tr = true;
     obte_status s = workspace_size(&m, 1, o, &need, true);
     if (s != OBTE_OK) return s;
-    size_t added = make_layout(m, o, m->q_tr).q_added;
-    if (need - added > NOALLOC_BYTES || need > NOALLOC_BYTES + NOALLOC_ROWS) {
+    if ((s = resolve_waves(&m, 1, o, Wc)) != OBTE_OK) return s;
+    const int W = Wc[(m->nx + 63) / 64];
+    auto fits = [&]() {
+        added = noalloc_added(m, o, W, m->q_tr && tr);
+        return need <= NOALLOC_BYTES + added && need <= NOALLOC_BYTES + NOALLOC_ROWS;
+    };
+    if (!fits()) {
         tr = false;
         if ((s = workspace_size(&m, 1, o, &need, false)) != OBTE_OK) return s;
-        added = make_layout(m, o, false).q_added;
+        if (!fits())
+            return fail(OBTE_ERR_NOMEM, "this solve needs %zu bytes of scratch, obte_solve_noalloc admits %zu "
+                                        "(use obte_solve with a caller workspace)", need,
+                        NOALLOC_BYTES + std::min(added, NOALLOC_ROWS));
     }
-    if (need - added > NOALLOC_BYTES || need > NOALLOC_BYTES + NOALLOC_ROWS)
-        return fail(OBTE_ERR_NOMEM, "this solve needs %zu bytes of scratch; obte_solve_noalloc has %zu "
-                                    "(use obte_solve with a caller workspace)", need, NOALLOC_BYTES);
     void* ws = nullptr;
     if ((s = scratch_on_current_device(&ws)) != OBTE_OK) return s;
     const double* sg[1] = {sigma_dev};
