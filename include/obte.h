@@ -174,10 +174,15 @@ typedef struct {
     int accel;
     /* Launch shape of the pass kernel (results do not depend on it; FP64 runs
      * are bitwise the same).  waves_by_class[c - 1]: systems per workgroup of
-     * the launch over meshes with c = ceil(n[0] / 64) cells per lane (0..8,
-     * 0 = waves_per_group; FP64 2D launches with c >= 3, and FP64 launches with
-     * dispatch = 2, take at most 4: larger explicit values are OBTE_ERR_ARG).  dispatch: 0 = each geometry's work items longest
-     * MFPs first (geometry by geometry), one launch per class; 1 = the
+     * meshes with c = ceil(n[0] / 64) (0..8, 0 = waves_per_group; FP64 2D
+     * meshes with c >= 3, and FP64 launches with dispatch = 2, take at most 4:
+     * larger explicit values are OBTE_ERR_ARG).  2D meshes periodic along y
+     * with n[1] <= 256 and ceil(n[1] / 64) <= 2 c are launched with the cells
+     * per lane of the longer side; their systems whose rows run along y take
+     * fewer per workgroup where 64 KiB of LDS hold no more (7, 5 and 3 with 2,
+     * 3 and 4 cells per lane), and at most 4 in FP64 with 3 or 4.  dispatch:
+     * 0 = each geometry's work items longest MFPs first (geometry by
+     * geometry), one launch per cells-per-lane class; 1 = the
      * longest-MFP items of every geometry of a launch first; 2 (2D meshes;
      * 3D takes 1) = one persistent launch over the items of every class,
      * longest MFPs first over all geometries: each workgroup takes the next
@@ -276,8 +281,8 @@ obte_status obte_solve_noalloc(obte_mesh* mesh, const obte_solve_opts* opts, con
  * array has 8 MiB more, for the sweeps' row tables). */
 size_t obte_noalloc_scratch_bytes(void);
 
-/* Many independent geometries in one launch per pass (one per row-width
- * class: ceil(nx / 64) cells per lane).  meshes[i]
+/* Many independent geometries in one launch per pass (one per
+ * cells-per-lane class, see obte_solve_opts).  meshes[i]
  * and sigma_dev[i] (nullable entries) as above; one workspace holds all, of
  * at least obte_workspace_size_batch bytes (OBTE_ERR_NOMEM otherwise); all
  * meshes must share the number of MFPs unless waves_per_group is set.  kappa_out: host, n doubles (kappa_cc).  stats: host,

@@ -643,7 +643,7 @@ struct Run {
     Item* d_items = nullptr;
     int* d_pending = nullptr;     // geometries whose Fourier CG still iterates
     size_t state_off = 0, state_bytes = 0;
-    // items grouped by cells per lane (ceil(nx / 64)): one launch per class,
+    // items grouped by cells per lane (launch_class): one launch per class,
     // so a narrow geometry of a batch does not run the widest row's kernel
     int cls_first[5] = {}, cls_count[5] = {};
     size_t cls_lds[5] = {};
@@ -698,11 +698,11 @@ size_t run_state_bytes(size_t n_views, size_t n_items) {
     return align256(n_views * sizeof(GeomDev)) + align256(n_items * sizeof(Item)) + 256;
 }
 
-// Systems per workgroup of each cells-per-lane launch class (Wc[c], c = 1..4
-// = ceil(nx / 64)) over these meshes; the same rule for the workspace size
-// and the solve.  A class takes opts.waves_by_class[c - 1], else
-// waves_per_group, else the automatic choice; in 3D every wave of a group
-// needs nz rows of LDS, which bounds the class's W.
+// Systems per workgroup of the meshes with c = 1..4 = ceil(nx / 64) (Wc[c]);
+// the same rule for the workspace size and the solve.  They take
+// opts.waves_by_class[c - 1], else waves_per_group, else the automatic choice;
+// in 3D every wave of a group needs nz rows of LDS, which bounds W (2D:
+// item_waves).
 obte_status resolve_waves(const obte_mesh* const* meshes, int n, const obte_solve_opts* o, int* Wc) {
     int base = o->waves_per_group;
     if (base == 0) {
@@ -722,7 +722,7 @@ obte_status resolve_waves(const obte_mesh* const* meshes, int n, const obte_solv
         const int set = o->waves_by_class[c - 1];
         int W = set ? set : base;
         // 3D: one row per z-plane in the compute type (2D keeps its rows in
-        // registers and needs no LDS)
+        // registers; rows along y stage what they store in LDS: item_waves)
         const size_t per_wave = nzm > 1 ? (size_t)nzm * 64 * c * tsz : 0;
         if (present[c] && per_wave > cap)
             return fail(OBTE_ERR_ARG, "a wave needs %zu bytes of LDS (nx, nz too large; limit %zu)", per_wave, cap);
@@ -746,7 +746,8 @@ obte_status resolve_waves(const obte_mesh* const* meshes, int n, const obte_solv
     return OBTE_OK;
 }
 
-// Launch class of a mesh: the cells per lane of its rows.
+// Launch class of a mesh: the cells per lane of its rows (2D: of the longer
+// where directions may take rows along y).
 int launch_class(const obte_mesh* m) { return m->q_cpl; }
 
 // Rows along y for direction l (2D, where they are in use at all).
@@ -1468,7 +1469,13 @@ obte_status obte_mesh_create(const obte_mesh_desc* d, obte_mesh** out) {
     }
     // 2D rows along y: where y is periodic (else there is no coupling across
     // rows along x to begin with), fit on a wave, and do not make the rows
-    // along x more than twice as wide on its lanes
+    // along x more than twice as wide on its lanes (both orientations share
+    // the cells per lane).  However few the cells along y: 256 short rows in
+    // sequence take no longer than the many sweeps of 8 long ones that wrap
+    // around y, and the mixed iteration needs a fraction of the passes (48 x 30
+    // systems, square grid cells, rows along x -> both: 256 x 8 FP32 mixed 97
+    // -> 23 ms, 10 plain FP64 passes 10.5 -> 9.6; 256 x 16 95 -> 14 and 14.8 ->
+    // 10.7; 128 x 4 59 -> 7.4 and 3.9 -> 3.0)
     {
         const int cx = (m->nx + 63) / 64, cy = (m->ny + 63) / 64;
         m->q_tr = nz == 1 && m->periodic[1] && cy <= 4 && cy <= 2 * cx;

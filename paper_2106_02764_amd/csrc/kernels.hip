@@ -815,7 +815,8 @@ __device__ __forceinline__ void fourier_cells(const GeomDev& g, const FView& v, 
 }
 
 // NF: faces of a cell (a batch is all 2D or all 3D).  2D runs
-// with all waves of 517 000 cells resident (64 registers, 8 waves a SIMD).
+// with all waves of 517 000 cells resident (64 registers and 5 spilled, 8 waves
+// a SIMD).
 template <int NF>
 __global__ void __launch_bounds__(FB_THREADS, NF == 4 ? 8 : 4) k_fourier_cg(const GeomDev* __restrict__ geoms, FGrid fg, int qq,
                                                          double tol, int max_iter) {

@@ -111,8 +111,8 @@ struct GeomDev {
     int n_plane[2];
 };
 
-// Store offset of a pore cell: past any stored array, also when doubled for
-// the FP64 copy of an FP32 solution (raw buffer stores there are dropped).
+// Store offset of a pore cell: past any stored array (raw buffer stores there
+// are dropped).
 constexpr uint32_t QOFF_NONE = 0x7FFFFFF0u;
 
 // Rows along y (2D): the row's own periodic closure is solved exactly and
