@@ -1473,9 +1473,9 @@ obte_status obte_mesh_create(const obte_mesh_desc* d, obte_mesh** out) {
     // the cells per lane).  However few the cells along y: 256 short rows in
     // sequence take no longer than the many sweeps of 8 long ones that wrap
     // around y, and the mixed iteration needs a fraction of the passes (48 x 30
-    // systems, square grid cells, rows along x -> both: 256 x 8 FP32 mixed 97
-    // -> 23 ms, 10 plain FP64 passes 10.5 -> 9.6; 256 x 16 95 -> 14 and 14.8 ->
-    // 10.7; 128 x 4 59 -> 7.4 and 3.9 -> 3.0)
+    // systems, square grid cells, rows along x -> both: 256 x 8 FP32 mixed 97,
+    // not converged in 1000 passes, -> 25 ms, 10 plain FP64 passes 10.5 -> 9.6;
+    // 256 x 16 95 -> 14 and 14.9 -> 10.7; 128 x 4 59 -> 8 and 3.9 -> 2.7)
     {
         const int cx = (m->nx + 63) / 64, cy = (m->ny + 63) / 64;
         m->q_tr = nz == 1 && m->periodic[1] && cy <= 4 && cy <= 2 * cx;
