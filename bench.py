@@ -62,8 +62,8 @@ REF = dict(precision=0, outer_tol=1e-10, stop_rule=0, accel=8, inner_tol=1e-12, 
 # operating point, per launch (rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE over one
 # solve, each scaled by the same counter on a plain 256 MiB copy); valid only
 # for the kernel source it was taken on.
-TRAFFIC = {"kernels_sha256": "10663e82f545d7058b76e90c459f084f589c6fb4bf68f6acdffb708651746763",
-           "fetch_bytes": 27375701, "write_bytes": 89442336}
+TRAFFIC = {"kernels_sha256": "c2fd81e3e651f545e95c1d92f90a1aeb7bf28bdbaf2183fbc7a18bf857e60bdd",
+           "fetch_bytes": 27333829, "write_bytes": 88499902}
 
 
 def parse():
