@@ -542,8 +542,13 @@ __device__ __forceinline__ double fourier_rhs(const GeomDev& g, uint16_t w, cons
     return b;
 }
 
-// (FGRID_MAX: geometries of one iteration launch, a multiple of 8)
-constexpr int FB_MAX = 256, FB_THREADS = 256, FGRID_MAX = 64;
+constexpr int FB_MAX = 256, FB_THREADS = 256;
+// geometries of one iteration launch (powers of 8; the table of block counts
+// is a kernel argument, 2 KB of the 4 there may be).  The larger table is
+// searched a level more, so it is taken where the smaller would need more
+// launches, each as long as an iteration's chain (200 geometries, 24 to 48
+// cells a side: 17.9 ms with four launches an iteration, 13.9 with one)
+constexpr int FGRID_MIN = 64, FGRID_MAX = 512;
 
 // This geometry's CG storage (in the fx region) and block b's cell range.
 // r, s = A r and q = A p are double buffered by iteration parity; gp / dp hold
@@ -724,8 +729,9 @@ __global__ void __launch_bounds__(FB_THREADS) k_fourier_s0(const GeomDev* __rest
 // the blocks that have cells are launched.  An iteration of the 128 x 128 cell:
 // 6.1 -> 5.2 us; of 24 geometries (517 000 cells, a grid of 6144 blocks for
 // 2017 with cells): 20 -> 16 us, where the 80 bytes a cell would take 8 us.
+template <int NG>
 struct FGrid {
-    int n, first[FGRID_MAX + 1];  // blocks per XCD before each geometry (INT_MAX past the last)
+    int n, first[NG + 1];         // blocks per XCD before each geometry (INT_MAX past the last)
 };
 
 template <int NF>
@@ -817,8 +823,8 @@ __device__ __forceinline__ void fourier_cells(const GeomDev& g, const FView& v, 
 // NF: faces of a cell (a batch is all 2D or all 3D).  2D runs
 // with all waves of 517 000 cells resident (64 registers and 5 spilled, 8 waves
 // a SIMD).
-template <int NF>
-__global__ void __launch_bounds__(FB_THREADS, NF == 4 ? 8 : 4) k_fourier_cg(const GeomDev* __restrict__ geoms, FGrid fg, int qq,
+template <int NF, int NG>
+__global__ void __launch_bounds__(FB_THREADS, NF == 4 ? 8 : 4) k_fourier_cg(const GeomDev* __restrict__ geoms, FGrid<NG> fg, int qq,
                                                          double tol, int max_iter) {
     __shared__ double red[40];
     // workgroups go to the eight XCDs in turn: an XCD takes consecutive blocks
@@ -828,11 +834,12 @@ __global__ void __launch_bounds__(FB_THREADS, NF == 4 ? 8 : 4) k_fourier_cg(cons
     int k = 0;
     if (fg.n > 1) {
 #pragma unroll
-        for (int i = 8; i < FGRID_MAX; i += 8) k += b >= fg.first[i] ? 8 : 0;
-        int d = 0;
+        for (int st = NG / 8; st > 0; st /= 8) {
+            int d = 0;
 #pragma unroll
-        for (int i = 1; i < 8; ++i) d += b >= fg.first[k + i] ? 1 : 0;
-        k += d;
+            for (int i = 1; i < 8; ++i) d += b >= fg.first[k + i * st] ? st : 0;
+            k += d;
+        }
     }
     const GeomDev& g = geoms[k];
     const int blk = xcd * (fg.first[k + 1] - fg.first[k]) + b - fg.first[k];
@@ -1201,21 +1208,28 @@ hipError_t launch_fourier_init(const GeomDev* geoms_dev, int n_geoms, int max_ce
     return hipGetLastError();
 }
 
-hipError_t launch_fourier_iter(const GeomDev* geoms_dev, const int* ncells, int n_geoms, int ndim, int parity, double tol,
-                               int max_iter, hipStream_t st) {
+template <int NG>
+static hipError_t launch_fourier_cg(const GeomDev* geoms_dev, const int* ncells, int n_geoms, int ndim, int parity, double tol,
+                                    int max_iter, hipStream_t st) {
     (void)hipGetLastError();
-    for (int g0 = 0; g0 < n_geoms; g0 += FGRID_MAX) {
-        FGrid fg;
-        fg.n = n_geoms - g0 < FGRID_MAX ? n_geoms - g0 : FGRID_MAX;
+    for (int g0 = 0; g0 < n_geoms; g0 += NG) {
+        FGrid<NG> fg;
+        fg.n = n_geoms - g0 < NG ? n_geoms - g0 : NG;
         int per = 0;
-        for (int k = 0; k <= FGRID_MAX; ++k) {
+        for (int k = 0; k <= NG; ++k) {
             fg.first[k] = k <= fg.n ? per : INT_MAX;
             if (k < fg.n) per += (fourier_blocks(ncells[g0 + k]) + 7) / 8;
         }
-        hipLaunchKernelGGL(ndim > 2 ? k_fourier_cg<6> : k_fourier_cg<4>, dim3(8 * per), dim3(FB_THREADS), 0, st,
+        hipLaunchKernelGGL((ndim > 2 ? k_fourier_cg<6, NG> : k_fourier_cg<4, NG>), dim3(8 * per), dim3(FB_THREADS), 0, st,
                            geoms_dev + g0, fg, parity, tol, max_iter);
     }
     return hipGetLastError();
+}
+
+hipError_t launch_fourier_iter(const GeomDev* geoms_dev, const int* ncells, int n_geoms, int ndim, int parity, double tol,
+                               int max_iter, hipStream_t st) {
+    return n_geoms <= FGRID_MIN ? launch_fourier_cg<FGRID_MIN>(geoms_dev, ncells, n_geoms, ndim, parity, tol, max_iter, st)
+                                : launch_fourier_cg<FGRID_MAX>(geoms_dev, ncells, n_geoms, ndim, parity, tol, max_iter, st);
 }
 
 hipError_t launch_fourier_pending(const GeomDev* geoms_dev, int n_geoms, int* pending_dev, hipStream_t st) {
