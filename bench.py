@@ -62,8 +62,8 @@ REF = dict(precision=0, outer_tol=1e-10, stop_rule=0, accel=8, inner_tol=1e-12, 
 # operating point, per launch (rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE over one
 # solve, each scaled by the same counter on a plain 256 MiB copy); valid only
 # for the kernel source it was taken on.
-TRAFFIC = {"kernels_sha256": "c2fd81e3e651f545e95c1d92f90a1aeb7bf28bdbaf2183fbc7a18bf857e60bdd",
-           "fetch_bytes": 27333829, "write_bytes": 88499902}
+TRAFFIC = {"kernels_sha256": "71a32952867f9f08b5fb6629e1aeb9e158356e62e952d6877406c39bdba15542",
+           "fetch_bytes": 27270122, "write_bytes": 88096960}
 
 
 def parse():
